@@ -354,6 +354,38 @@ lbm_status step_persist(lbm_ctx* c, int n) {
     return LBM_OK;
 }
 
+// Whether runs of steps go through the many-steps channel kernel: automatic
+// mode, where the plan made with the parameters expects it to be faster.  Not
+// under the caller's stream capture: the number of buffer swaps of a captured
+// run must not depend on the plan (an even number of steps leaves the state in
+// the buffer the replay starts from).
+bool use_chan_multi(const lbm_ctx* c) {
+    if (c->desc.lattice != LBM_D2Q9_D2Q5 || c->fusion != 0 || c->cmulti.steps < 2 || use_tb2(c))
+        return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+}
+
+// Enqueue left steps of a run by the many-steps channel kernel as launches of
+// nearly equal length; at most plan.steps each.
+template <typename S>
+hipError_t step_chan_multi(lbm_ctx* c, int left) {
+    while (left > 0) {
+        const int launches = (left + c->cmulti.steps - 1) / c->cmulti.steps;
+        const int m = (left + launches - 1) / launches;
+        double mods[kChanMultiMax];
+        for (int i = 0; i < m; ++i) mods[i] = flux_mod_at(c, c->t + i);
+        hipError_t e = launch_chan_multi<S>(c->ck, c->cmulti, (const S*)bufA(c), (S*)bufB(c),
+                                            aux_qw<S>(c), aux_uin<S>(c), aux_tin<S>(c), mods, m, 0,
+                                            c->stream);
+        if (e != hipSuccess) return e;
+        c->cur ^= 1;
+        c->t += m;
+        left -= m;
+    }
+    return hipSuccess;
+}
+
 // Enqueue m (1 or 2) steps, advancing the buffer parity and the step count;
 // *swaps receives the number of buffer swaps made.
 template <typename S>
@@ -771,6 +803,9 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
     if (d.lattice == LBM_D2Q9_D2Q5 && chan_tb2_fits(ck)) {
         DeviceGuard g(c->device);
         c->tb2_seg = d.prec == LBM_FP64 ? chan_tb2_seg<double>(ck) : chan_tb2_seg<float>(ck);
+        if (!c->cmulti_made)  // depends on the grid and its boundaries only
+            c->cmulti = d.prec == LBM_FP64 ? chan_multi_plan<double>(ck) : chan_multi_plan<float>(ck);
+        c->cmulti_made = true;
     }
     c->dk = dk;
     c->d3k = d3k;
@@ -944,6 +979,10 @@ lbm_status step_run(lbm_ctx* c, int n) {
     }
     const bool f64 = c->desc.prec == LBM_FP64;
     if (n > 0 && use_persist(c)) return f64 ? step_persist<double>(c, n) : step_persist<float>(c, n);
+    if (n > 1 && use_chan_multi(c)) {
+        hipError_t e = f64 ? step_chan_multi<double>(c, n) : step_chan_multi<float>(c, n);
+        return e == hipSuccess ? LBM_OK : hip_fail(c, e, "step kernel");
+    }
     int s = 0;
     if (n >= 2 * c->graph_steps && graph_usable(c)) {
         for (; s + c->graph_steps <= n; s += c->graph_steps) {

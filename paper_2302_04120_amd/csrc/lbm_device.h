@@ -161,8 +161,8 @@ __device__ __forceinline__ void chan_flow_macros(const S* __restrict__ f, int np
 // Lattice body force at a node whose temperature is T = T_ref + th: the
 // constant force plus, when on, the Boussinesq force -rho_ref beta th g of
 // Eq. buoyancy_force (App. D).
-template <typename C>
-__device__ __forceinline__ void chan_force(const ChanK& k, C th, C& fx, C& fy) {
+template <typename C, typename K>
+__device__ __forceinline__ void chan_force(const K& k, C th, C& fx, C& fy) {
     fx = C(k.Ft[0]);
     fy = C(k.Ft[1]);
     if (k.buoy) {

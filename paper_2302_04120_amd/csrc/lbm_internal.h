@@ -114,6 +114,13 @@ struct P3K {
     double c, cs2;        // outputs
 };
 
+// Tiles and steps per launch of the many-steps channel kernel (lbm_chan_multi.hip);
+// steps 0: not used.
+constexpr int kChanMultiMax = 16;
+struct ChanMultiPlan {
+    int steps = 0, ntx = 0, nty = 0;
+};
+
 struct D1K {
     int n, q;
     double w_tau;         // dt / tau
@@ -176,6 +183,8 @@ struct lbm_ctx {
     // two-phase steps: 0 automatic, 1 single-step kernel only, 2 two-step
     // kernel whenever the grid allows it, 3 many steps per cooperative launch
     int fusion = 0;
+    lbm::ChanMultiPlan cmulti;          // channel: many steps per launch (automatic mode)
+    bool cmulti_made = false;
     int tb2_seg = 0;                    // rows per two-step workgroup (0: kernel not usable)
     unsigned* persist_flags = nullptr;  // kPersistMaxTiles step counters, then the error word
     unsigned persist_epoch = 0;         // steps taken by persistent launches since the reset
@@ -201,6 +210,16 @@ int chan_tb2_seg(const ChanK& k);
 template <typename S>
 hipError_t launch_chan_tb2(const ChanK& k, const S* a, S* b, const S* qw, const S* uin,
                            const S* tin, double mod0, double mod1, int seg, hipStream_t s);
+// nsteps (at most plan.steps) channel steps in one launch: the last state into
+// b (tape 0), or the state after step s into b + s tape.  mods: the wall-flux
+// modulation of each step.  chan_multi_plan gives steps 0 where the kernel
+// does not cover the configuration or another kernel is faster.
+template <typename S>
+ChanMultiPlan chan_multi_plan(const ChanK& k);
+template <typename S>
+hipError_t launch_chan_multi(const ChanK& k, const ChanMultiPlan& plan, const S* a, S* b,
+                             const S* qw, const S* uin, const S* tin, const double* mods,
+                             int nsteps, long long tape, hipStream_t s);
 // one two-phase step from state a to state b (node-block layout); arith64:
 // evaluate the step in FP64 on FP32 storage (S = float)
 template <typename S>
