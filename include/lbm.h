@@ -304,10 +304,17 @@ LBM_API lbm_status lbm_set_graph_steps(lbm_ctx* ctx, int steps);
  *           by a launch-round model when the parameters are set) number at
  *           least 512 and, with x-tiles, at least 90 % of the launched lanes
  *           hold stored columns; else mode 1 (always mode 1 with
- *           LBM_FP32_DEV_ARITH64).
+ *           LBM_FP32_DEV_ARITH64).  Smaller LBM_D2Q9_D2Q5 grids with flow
+ *           and temperature take runs of several steps per launch where a
+ *           cost model expects them to be faster than single steps.
+ *   LBM_D3Q19: mode 2 runs two steps per launch on boxes of at least 2 nodes
+ *           per axis, mode 0 where a cost model expects that to be faster,
+ *           the others single steps.
+ *   While the caller captures the stream, mode 0 on LBM_D2Q9_D2Q5 launches no
+ *           runs of several steps, and LBM_D3Q19 only single steps.
  * The kernels evaluate the same per-node arithmetic in the same order, so
  * the modes agree to the last bit.  Not an operation of the paper: a
- * performance control.  Other lattices ignore it.  LBM_E_ARG on an unknown
+ * performance control.  The other lattices ignore it.  LBM_E_ARG on an unknown
  * mode. */
 LBM_API lbm_status lbm_set_step_fusion(lbm_ctx* ctx, int mode);
 

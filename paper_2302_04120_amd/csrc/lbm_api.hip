@@ -386,11 +386,32 @@ hipError_t step_chan_multi(lbm_ctx* c, int left) {
     return hipSuccess;
 }
 
+// Whether the next two D3Q19 steps go through the two-step kernel: automatic
+// mode where the plan expects it to be faster, mode 2 wherever it applies.
+// Not under the caller's stream capture: two captured steps have always ended
+// in the buffer they started from, so that their replay goes on from there.
+bool use_d3_tb2(const lbm_ctx* c) {
+    if (c->desc.lattice != LBM_D3Q19 || c->d3tb2.ntx < 1 ||
+        !(c->fusion == 2 || (c->fusion == 0 && c->d3tb2.fast)))
+        return false;
+    if (c->own_capture) return true;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+}
+
 // Enqueue m (1 or 2) steps, advancing the buffer parity and the step count;
 // *swaps receives the number of buffer swaps made.
 template <typename S>
 hipError_t advance(lbm_ctx* c, int m, int* swaps) {
     *swaps = 0;
+    if (m == 2 && use_d3_tb2(c)) {
+        hipError_t e = launch_d3_tb2<S>(c->d3k, c->d3tb2, (const S*)bufA(c), (S*)bufB(c), c->stream);
+        if (e != hipSuccess) return e;
+        c->cur ^= 1;
+        c->t += 2;
+        *swaps = 1;
+        return hipSuccess;
+    }
     if (m == 2 && use_tb2(c)) {
         hipError_t e =
             c->desc.lattice == LBM_D2Q9_D2Q5
@@ -449,6 +470,7 @@ hipError_t step_replay(lbm_ctx* c) {
         const hipStream_t user = c->stream;
         const int cur0 = c->cur;
         c->stream = c->cap_stream;
+        c->own_capture = true;
         const long long t0 = c->t;
         hipError_t el = hipSuccess;
         int swaps = 0;
@@ -458,6 +480,7 @@ hipError_t step_replay(lbm_ctx* c) {
             swaps += sw;
         }
         c->stream = user;
+        c->own_capture = false;
         c->cur = cur0;
         c->t = t0;
         c->graph_swaps[p0] = swaps;
@@ -806,6 +829,11 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
         if (!c->cmulti_made)  // depends on the grid and its boundaries only
             c->cmulti = d.prec == LBM_FP64 ? chan_multi_plan<double>(ck) : chan_multi_plan<float>(ck);
         c->cmulti_made = true;
+    }
+    if (d.lattice == LBM_D3Q19) {
+        DeviceGuard g(c->device);
+        if (c->d3tb2.ntx < 1)  // depends on the grid only
+            c->d3tb2 = d.prec == LBM_FP64 ? d3_tb2_plan<double>(d3k) : d3_tb2_plan<float>(d3k);
     }
     c->dk = dk;
     c->d3k = d3k;

@@ -121,6 +121,13 @@ struct ChanMultiPlan {
     int steps = 0, ntx = 0, nty = 0;
 };
 
+// Tiles per plane and z segments per replica of the two-step D3Q19 kernel;
+// ntx 0: not used.
+struct D3Tb2Plan {
+    int ntx = 0, nty = 0, nseg = 0;
+    bool fast = false;  // expected to beat single steps (automatic mode takes it)
+};
+
 struct D1K {
     int n, q;
     double w_tau;         // dt / tau
@@ -178,6 +185,7 @@ struct lbm_ctx {
     // on a private stream and replayed on `stream`; 0 disables
     int graph_steps = 64;
     hipStream_t cap_stream = nullptr;
+    bool own_capture = false;  // while step graphs are being captured
     hipGraphExec_t step_graph[2] = {nullptr, nullptr};
     int graph_swaps[2] = {0, 0};  // buffer swaps made by each captured graph
     // two-phase steps: 0 automatic, 1 single-step kernel only, 2 two-step
@@ -185,6 +193,7 @@ struct lbm_ctx {
     int fusion = 0;
     lbm::ChanMultiPlan cmulti;          // channel: many steps per launch (automatic mode)
     bool cmulti_made = false;
+    lbm::D3Tb2Plan d3tb2;               // D3Q19: two steps per launch (automatic mode)
     int tb2_seg = 0;                    // rows per two-step workgroup (0: kernel not usable)
     unsigned* persist_flags = nullptr;  // kPersistMaxTiles step counters, then the error word
     unsigned persist_epoch = 0;         // steps taken by persistent launches since the reset
@@ -268,6 +277,11 @@ hipError_t launch_d1_init(const D1K& k, const double* T, double* g, hipStream_t 
 long long d3_tiles(const D3K& k);
 template <typename S>
 hipError_t launch_d3_step(const D3K& k, const S* fc, S* fn, hipStream_t s);
+// two steps in one launch; d3_tb2_plan gives ntx 0 where single steps are faster
+template <typename S>
+D3Tb2Plan d3_tb2_plan(const D3K& k);
+template <typename S>
+hipError_t launch_d3_tb2(const D3K& k, const D3Tb2Plan& plan, const S* fc, S* fn, hipStream_t s);
 template <typename S>
 hipError_t launch_d3_init(const D3K& k, const double* fields, S* f, hipStream_t s);
 template <typename S>
