@@ -366,13 +366,19 @@ bool use_chan_multi(const lbm_ctx* c) {
     return hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
 }
 
+// Steps of the next launch when left steps go in launches of at most `most`
+// steps of nearly equal length.
+int even_share(int left, int most) {
+    const int launches = (left + most - 1) / most;
+    return (left + launches - 1) / launches;
+}
+
 // Enqueue left steps of a run by the many-steps channel kernel as launches of
 // nearly equal length; at most plan.steps each.
 template <typename S>
 hipError_t step_chan_multi(lbm_ctx* c, int left) {
     while (left > 0) {
-        const int launches = (left + c->cmulti.steps - 1) / c->cmulti.steps;
-        const int m = (left + launches - 1) / launches;
+        const int m = even_share(left, c->cmulti.steps);
         double mods[kChanMultiMax];
         for (int i = 0; i < m; ++i) mods[i] = flux_mod_at(c, c->t + i);
         hipError_t e = launch_chan_multi<S>(c->ck, c->cmulti, (const S*)bufA(c), (S*)bufB(c),
@@ -756,6 +762,18 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
             }
             ak.qgrad = dt / (dx * p->rho_cp);
             ck.qdt = p->qvol / p->rho_cp * dt;
+        }
+        {
+            const double d9[9] = {9, 36, 36, 6, 12, 6, 12, 4, 4};  // squared row norms of M
+            const double d5[5] = {5, 2, 2, 20, 4};
+            for (int q = 0; q < 9; ++q) {
+                ak.cLf[q] = -ak.dLf[q] / (ck.flow_mrt ? d9[q] : 1.0);
+                if (ak.dLf[q] != 0.0) ak.rows_f |= 1 << q;
+            }
+            for (int q = 0; q < 5; ++q) {
+                ak.cLt[q] = -ak.dLt[q] / d5[q];
+                if (ak.dLt[q] != 0.0) ak.rows_t |= 1 << q;
+            }
         }
         ck.c = cc;
         ck.T_ref = p->T_ref;
@@ -1292,7 +1310,7 @@ lbm_status rec_layout(const lbm_ctx* c, int nsteps, int K, RecLayout* R, std::st
     r.state = align256((size_t)c->nplanes * c->P * c->esize);
     r.nseg = (nsteps + K - 1) / K;
     const int Kt = K < nsteps ? K : nsteps;
-    r.tiles = chan_tiles(c->ck);
+    r.tiles = std::max(chan_tiles(c->ck), c->cmulti.ntx * c->cmulti.nty);
     size_t off = 0;
     r.offCk = off; off += (size_t)r.nseg * r.state;
     r.offTape = off; off += (size_t)(Kt + 1) * r.state;
@@ -1303,13 +1321,6 @@ lbm_status rec_layout(const lbm_ctx* c, int nsteps, int K, RecLayout* R, std::st
     r.total = off;
     *R = r;
     return LBM_OK;
-}
-
-template <typename S>
-hipError_t chan_step_ptr(lbm_ctx* c, const S* a, S* b, long long t) {
-    const double mod = 1.0 + c->flux_amp * std::sin(c->flux_omega * (double)t * c->dt);
-    return launch_chan_step<S>(c->ck, a, b, aux_qw<S>(c), aux_uin<S>(c), aux_tin<S>(c), mod,
-                               c->stream);
 }
 
 template <typename S>
@@ -1339,18 +1350,33 @@ hipError_t grad_impl(lbm_ctx* c, const RecLayout& R, double scale) {
         e = hipMemcpyAsync(tape, w + R.offCk + (size_t)sg * R.state, R.state, hipMemcpyDeviceToDevice,
                            c->stream);
         if (e != hipSuccess) return e;
-        for (int j = 0; j < len; ++j) {
-            e = chan_step_ptr<S>(c, (const S*)((char*)tape + (size_t)j * R.state),
-                                 (S*)((char*)tape + (size_t)(j + 1) * R.state), t0 + j);
+        // the tape and the reverse steps, in launches of several steps where the
+        // forward run takes them
+        const long long stride = (long long)(R.state / sizeof(S));
+        auto at = [&](int j) { return tape + j * stride; };
+        const int most = use_chan_multi(c) ? c->cmulti.steps : 1;
+        double mods[kChanMultiMax];
+        for (int j = 0; j < len;) {
+            const int m = even_share(len - j, most);
+            for (int i = 0; i < m; ++i) mods[i] = flux_mod_at(c, t0 + j + i);
+            e = m > 1 ? launch_chan_multi<S>(c->ck, c->cmulti, at(j), at(j + 1), aux_qw<S>(c),
+                                             aux_uin<S>(c), aux_tin<S>(c), mods, m, stride, c->stream)
+                      : launch_chan_step<S>(c->ck, at(j), at(j + 1), aux_qw<S>(c), aux_uin<S>(c),
+                                            aux_tin<S>(c), mods[0], c->stream);
             if (e != hipSuccess) return e;
+            j += m;
         }
-        for (int j = len - 1; j >= 0; --j) {
-            const S* st = (const S*)((char*)tape + (size_t)j * R.state);
-            const double mod = 1.0 + c->flux_amp * std::sin(c->flux_omega * (double)(t0 + j) * c->dt);
-            e = launch_adj_step<S>(c->ck, c->ak, st, lam[cur], lam[cur ^ 1], mod, dq, dq + nx, acc,
-                                   c->stream);
+        const int most_adj = most > 1 && adj_multi_fast<S>(c->ck, c->cmulti) ? most : 1;
+        for (int j = len - 1; j >= 0;) {
+            const int m = even_share(j + 1, most_adj);
+            for (int i = 0; i < m; ++i) mods[i] = flux_mod_at(c, t0 + j - i);
+            e = m > 1 ? launch_adj_multi<S>(c->ck, c->ak, c->cmulti, at(j), -stride, lam[cur],
+                                            lam[cur ^ 1], mods, m, dq, dq + nx, acc, c->stream)
+                      : launch_adj_step<S>(c->ck, c->ak, at(j), lam[cur], lam[cur ^ 1], mods[0], dq,
+                                           dq + nx, acc, c->stream);
             if (e != hipSuccess) return e;
             cur ^= 1;
+            j -= m;
         }
     }
     return launch_adj_final(nx, R.tiles, scale, dq, dq + nx, dq + 2 * nx, dq + 3 * nx, acc, grad,

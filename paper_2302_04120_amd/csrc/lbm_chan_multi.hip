@@ -19,34 +19,6 @@
 namespace lbm {
 namespace {
 
-// ChanK in the type the kernel computes in: the constants of the collision
-// stay in scalar registers over the steps.
-template <typename C>
-struct ChanKT {
-    int nx, ny, batch, bcx, bcy, flow, thermal, flow_mrt, buoy;
-    C rho_ref, qdt, Lf[9], Lt[9], Ft[2], Bt[2], Tw[2];
-};
-
-template <typename C>
-ChanKT<C> chan_kt(const ChanK& k) {
-    ChanKT<C> r{};
-    r.nx = k.nx; r.ny = k.ny; r.batch = k.batch;
-    r.bcx = k.bcx; r.bcy = k.bcy;
-    r.flow = k.flow; r.thermal = k.thermal; r.flow_mrt = k.flow_mrt; r.buoy = k.buoy;
-    r.rho_ref = C(k.rho_ref);
-    r.qdt = C(k.qdt);
-    for (int q = 0; q < 9; ++q) {
-        r.Lf[q] = C(k.Lf[q]);
-        r.Lt[q] = C(k.Lt[q]);
-    }
-    for (int q = 0; q < 2; ++q) {
-        r.Ft[q] = C(k.Ft[q]);
-        r.Bt[q] = C(k.Bt[q]);
-        r.Tw[q] = C(k.Tw[q]);
-    }
-    return r;
-}
-
 template <typename C>
 struct ChanMultiArgs {
     ChanKT<C> k;
@@ -64,13 +36,6 @@ constexpr int cm_planes(int qt) { return 8 + (qt - 1) + 2; }
 template <typename S, int QT, int NT>
 constexpr int cm_sets() {
     return 2 * cm_planes(QT) * NT * int(sizeof(S)) <= 160 * 1024 ? 2 : 1;
-}
-
-// q = a / b, r = a mod b for 0 <= a < 2^21: (a + 1/2) / b stays 1 / 2 b away
-// from every integer, more than the reciprocal's 1 ulp moves it.
-__device__ __forceinline__ void cm_divide(int a, int b, int& q, int& r) {
-    q = int((float(a) + 0.5f) * __builtin_amdgcn_rcpf(float(b)));
-    r = a - q * b;
 }
 
 __device__ __forceinline__ int cm_wrap(int v, int n) {
@@ -93,8 +58,8 @@ __global__ __launch_bounds__(NT) void k_chan_multi(const ChanMultiArgs<S> p, con
     int w;
     if (!xcd_tile(p.ntx * p.nty * k.batch, w)) return;  // whole workgroup, before any barrier
     int tx, ty, b;
-    cm_divide(w, p.ntx, w, tx);
-    cm_divide(w, p.nty, b, ty);
+    block_divide(w, p.ntx, w, tx);
+    block_divide(w, p.nty, b, ty);
     const bool xends = k.bcx != 0, yends = k.bcy != 0, io = k.bcx == 1;
     // the tile's own nodes [x0, x1) x [y0, y1) and its region with the overlap
     const int x0 = tx * p.wx + min(tx, p.ex), x1 = x0 + p.wx + (tx < p.ex);
@@ -104,7 +69,7 @@ __global__ __launch_bounds__(NT) void k_chan_multi(const ChanMultiArgs<S> p, con
     const int rw = rx1 - rx0, rh = ry1 - ry0;
     const int t = threadIdx.x;
     int rx, ry;
-    cm_divide(t, rw, ry, rx);
+    block_divide(t, rw, ry, rx);
     const int vx = rx0 + rx, vy = ry0 + ry;
     const int x = xends ? vx : cm_wrap(vx, nx), y = yends ? vy : cm_wrap(vy, ny);
     // m: nodes between this one and the nearest edge of the region that cuts
@@ -240,7 +205,7 @@ __global__ __launch_bounds__(NT) void k_chan_multi(const ChanMultiArgs<S> p, con
 // whose LDS planes take twice the space.
 template <typename S>
 constexpr int cm_max_nodes() {
-    return sizeof(S) == 4 ? 1024 : 512;
+    return chan_multi_max_nodes(sizeof(S));
 }
 
 }  // namespace
@@ -257,6 +222,14 @@ long long cm_span(int n, int tiles, int h, bool ends) {
 long long cm_region(const ChanK& k, int ntx, int nty, int h) {
     return cm_span(k.nx, ntx, h, k.bcx != 0) * cm_span(k.ny, nty, h, k.bcy != 0);
 }
+
+}  // namespace
+
+long long chan_multi_region(const ChanK& k, const ChanMultiPlan& p, int h) {
+    return p.ntx > 0 && p.nty > 0 ? cm_region(k, p.ntx, p.nty, h) : 0;
+}
+
+namespace {
 
 // The kernel instance for a workgroup of that many threads.
 template <typename S>
@@ -344,7 +317,7 @@ template <typename S>
 hipError_t launch_chan_multi(const ChanK& k, const ChanMultiPlan& plan, const S* a, S* b,
                              const S* qw, const S* uin, const S* tin, const double* mods,
                              int nsteps, long long tape, hipStream_t s) {
-    const long long nodes = cm_region(k, plan.ntx, plan.nty, nsteps);
+    const long long nodes = chan_multi_region(k, plan, nsteps);
     const long long tiles = (long long)plan.ntx * plan.nty * k.batch;
     if (nsteps < 1 || nsteps > plan.steps || nodes < 1 || nodes > cm_max_nodes<S>() || tiles >= (1 << 21))
         return hipErrorInvalidValue;

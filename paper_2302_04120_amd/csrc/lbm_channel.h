@@ -8,6 +8,34 @@
 namespace lbm {
 namespace {
 
+// ChanK in the type the kernel computes in: the constants of the collision
+// stay in scalar registers over the steps.
+template <typename C>
+struct ChanKT {
+    int nx, ny, batch, bcx, bcy, flow, thermal, flow_mrt, buoy;
+    C rho_ref, qdt, Lf[9], Lt[9], Ft[2], Bt[2], Tw[2];
+};
+
+template <typename C>
+ChanKT<C> chan_kt(const ChanK& k) {
+    ChanKT<C> r{};
+    r.nx = k.nx; r.ny = k.ny; r.batch = k.batch;
+    r.bcx = k.bcx; r.bcy = k.bcy;
+    r.flow = k.flow; r.thermal = k.thermal; r.flow_mrt = k.flow_mrt; r.buoy = k.buoy;
+    r.rho_ref = C(k.rho_ref);
+    r.qdt = C(k.qdt);
+    for (int q = 0; q < 9; ++q) {
+        r.Lf[q] = C(k.Lf[q]);
+        r.Lt[q] = C(k.Lt[q]);
+    }
+    for (int q = 0; q < 2; ++q) {
+        r.Ft[q] = C(k.Ft[q]);
+        r.Bt[q] = C(k.Bt[q]);
+        r.Tw[q] = C(k.Tw[q]);
+    }
+    return r;
+}
+
 // Thermal lattice of the channel: D2Q5 (QT = 5) or D2Q9 (QT = 9, the set of
 // Sec. 3 and App. D).
 template <int QT> __device__ __forceinline__ int tex(int i) { return QT == 9 ? EX[i] : EX5[i]; }

@@ -202,13 +202,6 @@ __device__ constexpr int kD3Dn[4] = {12, 13, 16, 17};           // + (0, 0, -1),
 // LDS plane of mover i (all but 0, 5 and 6, which stay in their column)
 __device__ constexpr int d3_plane(int i) { return i < 5 ? i - 1 : i - 3; }
 
-// q = a / b, r = a mod b for 0 <= a < 2^21: (a + 1/2) / b stays 1 / 2 b away
-// from every integer, more than the reciprocal's 1 ulp moves it.
-__device__ __forceinline__ void d3_divide(int a, int b, int& q, int& r) {
-    q = int((float(a) + 0.5f) * __builtin_amdgcn_rcpf(float(b)));
-    r = a - q * b;
-}
-
 template <typename S, int NT, bool ALIGNED>
 __global__ __launch_bounds__(NT) void k_d3_tb2(const D3Tb2Args<S> p, const S* __restrict__ A,
                                                S* __restrict__ B) {
@@ -218,9 +211,9 @@ __global__ __launch_bounds__(NT) void k_d3_tb2(const D3Tb2Args<S> p, const S* __
     const int nx = k.nx, ny = k.ny, nz = k.nz;
     int w, tx, ty, sg, b;
     if (!xcd_tile(p.ntx * p.nty * p.nseg * k.batch, w)) return;  // whole workgroup
-    d3_divide(w, p.ntx, w, tx);
-    d3_divide(w, p.nty, w, ty);
-    d3_divide(w, p.nseg, b, sg);
+    block_divide(w, p.ntx, w, tx);
+    block_divide(w, p.nty, w, ty);
+    block_divide(w, p.nseg, b, sg);
     const int x0 = tx * p.wx + min(tx, p.ex), x1 = x0 + p.wx + (tx < p.ex);
     const int y0 = ty * p.wy + min(ty, p.ey), y1 = y0 + p.wy + (ty < p.ey);
     const int a = sg * p.wz + min(sg, p.ez), e = a + p.wz + (sg < p.ez);
@@ -231,7 +224,7 @@ __global__ __launch_bounds__(NT) void k_d3_tb2(const D3Tb2Args<S> p, const S* __
     const bool whole = p.ntx == 1;
     const int th = threadIdx.x;
     int rx, ry;
-    d3_divide(th, wc, ry, rx);
+    block_divide(th, wc, ry, rx);
     bool in = ry < rh;
     if (!in && !whole) {
         const int q = th - rh * wc;

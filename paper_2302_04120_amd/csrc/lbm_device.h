@@ -110,6 +110,13 @@ __device__ __forceinline__ bool xcd_tile(int ntiles, int& t) {
     return t < ntiles;
 }
 
+// q = a / b, r = a mod b for 0 <= a < 2^21: (a + 1/2) / b stays 1 / 2 b away
+// from every integer, more than the reciprocal's 1 ulp moves it.
+__device__ __forceinline__ void block_divide(int a, int b, int& q, int& r) {
+    q = int((float(a) + 0.5f) * __builtin_amdgcn_rcpf(float(b)));
+    r = a - q * b;
+}
+
 // Stores of the next state: that buffer is read back only in the next step,
 // after the whole state (far larger than the caches) has streamed through.
 #ifndef LBM_NT_STORE

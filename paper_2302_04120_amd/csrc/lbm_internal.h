@@ -81,6 +81,8 @@ struct AdjK {
     double dLf[9];
     double dLt[5];
     double qgrad;
+    double cLf[9], cLt[5];  // -dL / squared row norm (MRT); BGK: cLf[7] = -dLf[7]
+    int rows_f, rows_t;     // bit q: cLf[q], cLt[q] is not zero
 };
 
 // D3Q19 momentum: lattice-normalised like ChanK
@@ -223,8 +225,14 @@ hipError_t launch_chan_tb2(const ChanK& k, const S* a, S* b, const S* qw, const 
 // b (tape 0), or the state after step s into b + s tape.  mods: the wall-flux
 // modulation of each step.  chan_multi_plan gives steps 0 where the kernel
 // does not cover the configuration or another kernel is faster.
+// chan_multi_region: nodes of the largest region of the plan's tiles for
+// launches of h steps.
 template <typename S>
 ChanMultiPlan chan_multi_plan(const ChanK& k);
+long long chan_multi_region(const ChanK& k, const ChanMultiPlan& p, int h);
+// largest workgroup (nodes of a region): 1024 threads in FP32, 512 in FP64,
+// whose LDS planes take twice the space
+constexpr int chan_multi_max_nodes(size_t value_bytes) { return value_bytes == 4 ? 1024 : 512; }
 template <typename S>
 hipError_t launch_chan_multi(const ChanK& k, const ChanMultiPlan& plan, const S* a, S* b,
                              const S* qw, const S* uin, const S* tin, const double* mods,
@@ -333,6 +341,15 @@ template <typename S>
 hipError_t launch_adj_step(const ChanK& k, const AdjK& a, const S* st, const S* ln, S* l,
                            double mod, double* dq_bot, double* dq_top, double* dtau_acc,
                            hipStream_t s);
+// nsteps reverse steps in one launch on the tiles of a channel plan: st the
+// state of the first, stride (in values, negative) to the next; mods in that
+// order.  adj_multi_fast: whether that beats single reverse steps.
+template <typename S>
+bool adj_multi_fast(const ChanK& k, const ChanMultiPlan& plan);
+template <typename S>
+hipError_t launch_adj_multi(const ChanK& k, const AdjK& a, const ChanMultiPlan& plan, const S* st,
+                            long long stride, const S* ln, S* l, const double* mods, int nsteps,
+                            double* dq_bot, double* dq_top, double* dtau_acc, hipStream_t s);
 // gradient assembly (fixed order): grad_flux[nx], grad_tau[2]
 hipError_t launch_adj_final(int nx, int ntiles, double scale, const double* dq_bot,
                             const double* dq_top, const double* dq_direct,

@@ -1524,29 +1524,46 @@ __global__ void k_reduce2(const double* __restrict__ partial, double* __restrict
     out[t] = s;
 }
 
-// channel diagnostics of replica 0: one thread per column
+// Channel diagnostics of replica 0.  A workgroup takes kNuCols columns: its
+// threads evaluate the nodes of kNuRows rows at a time into LDS and one thread
+// per column adds them in row order (one thread per column doing both waited
+// for memory row after row: 143 us on 1600 x 80).
+constexpr int kNuCols = 16, kNuRows = 64;
 template <typename S>
-__global__ void k_nusselt(ChanK k, const S* __restrict__ A, const S* __restrict__ qw,
-                          double qsi, double Dh, double kc, double dx,
-                          double* __restrict__ Tb, double* __restrict__ Tw,
-                          double* __restrict__ Nu) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= k.nx) return;
+__global__ __launch_bounds__(256) void k_nusselt(ChanK k, const S* __restrict__ A,
+                                                 const S* __restrict__ qw, double qsi, double Dh,
+                                                 double kc, double dx, double* __restrict__ Tb,
+                                                 double* __restrict__ Tw, double* __restrict__ Nu) {
+    __shared__ double su_[kNuRows][kNuCols], sT_[kNuRows][kNuCols];
+    const int c = threadIdx.x % kNuCols, r0 = threadIdx.x / kNuCols;
+    const int x = blockIdx.x * kNuCols + c;
     double su = 0, suT = 0, T0 = 0, T1 = 0;
-    for (int y = 0; y < k.ny; ++y) {
-        const long long n = (long long)y * k.nx + x;
-        double s = 0;
-        for (int i = 0; i < k.tq; ++i) s += double(A[bidx(k.npl, 9 + i, n)]);
-        const double T = k.T_ref + s + 0.5 * k.qdt;
-        double fx, fy;
-        chan_force(k, T - k.T_ref, fx, fy);
-        double d[9], drho, rho, ux, uy;
-        chan_flow_macros<double, S>(A, k.npl, n, k.rho_ref, fx, fy, d, drho, rho, ux, uy);
-        su += ux;
-        suT += ux * T;
-        if (y == 0) T0 = T;
-        if (y == k.ny - 1) T1 = T;
+    for (int yb = 0; yb < k.ny; yb += kNuRows) {
+        const int rows = min(kNuRows, k.ny - yb);
+        if (x < k.nx)
+            for (int r = r0; r < rows; r += 256 / kNuCols) {
+                const long long n = (long long)(yb + r) * k.nx + x;
+                double s = 0;
+                for (int i = 0; i < k.tq; ++i) s += double(A[bidx(k.npl, 9 + i, n)]);
+                const double T = k.T_ref + s + 0.5 * k.qdt;
+                double fx, fy;
+                chan_force(k, T - k.T_ref, fx, fy);
+                double d[9], drho, rho, ux, uy;
+                chan_flow_macros<double, S>(A, k.npl, n, k.rho_ref, fx, fy, d, drho, rho, ux, uy);
+                su_[r][c] = ux;
+                sT_[r][c] = T;
+            }
+        __syncthreads();
+        if (r0 == 0)
+            for (int r = 0; r < rows; ++r) {
+                su += su_[r][c];
+                suT += su_[r][c] * sT_[r][c];
+                if (yb + r == 0) T0 = sT_[r][c];
+                if (yb + r == k.ny - 1) T1 = sT_[r][c];
+            }
+        __syncthreads();
     }
+    if (r0 != 0 || x >= k.nx) return;
     const double q = double(qw[x]) * qsi;  // W/m^2 including the time modulation
     const double tb = suT / su;
     // wall temperature: mean of the two wall-adjacent nodes, or the lower one
@@ -1557,13 +1574,22 @@ __global__ void k_nusselt(ChanK k, const S* __restrict__ A, const S* __restrict_
     Nu[x] = q * Dh / (kc * (tw - tb));
 }
 
-__global__ void k_nusselt_mean(const double* __restrict__ Nu, const double* __restrict__ Tb,
-                               int nx, int x_dev, double* __restrict__ out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// mean of Nu over x >= x_dev (strided partial sums, then a tree) and T_b at the outlet
+__global__ __launch_bounds__(256) void k_nusselt_mean(const double* __restrict__ Nu,
+                                                      const double* __restrict__ Tb, int nx,
+                                                      int x_dev, double* __restrict__ out) {
+    __shared__ double part[256];
     double s = 0;
-    for (int x = x_dev; x < nx; ++x) s += Nu[x];
-    out[0] = s / double(nx - x_dev);
-    out[1] = Tb[nx - 1];
+    for (int x = x_dev + int(threadIdx.x); x < nx; x += 256) s += Nu[x];
+    part[threadIdx.x] = s;
+    for (int half = 128; half > 0; half /= 2) {
+        __syncthreads();
+        if (int(threadIdx.x) < half) part[threadIdx.x] += part[threadIdx.x + half];
+    }
+    if (threadIdx.x == 0) {
+        out[0] = part[0] / double(nx - x_dev);
+        out[1] = Tb[nx - 1];
+    }
 }
 
 inline unsigned grid1(long long N, int bs) {
@@ -1964,11 +1990,11 @@ template <typename S>
 hipError_t launch_nusselt(const ChanK& k, const S* a, const S* qw, double qsi, double Dh,
                           double kc, double dx, int x_dev, double* Tb, double* Tw, double* Nu,
                           double* small, hipStream_t s) {
-    hipLaunchKernelGGL(k_nusselt<S>, dim3((k.nx + 255) / 256), dim3(256), 0, s, k, a, qw, qsi,
+    hipLaunchKernelGGL(k_nusselt<S>, dim3((k.nx + kNuCols - 1) / kNuCols), dim3(256), 0, s, k, a, qw, qsi,
                        Dh, kc, dx, Tb, Tw, Nu);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_nusselt_mean, dim3(1), dim3(64), 0, s, Nu, Tb, k.nx, x_dev, small);
+    hipLaunchKernelGGL(k_nusselt_mean, dim3(1), dim3(256), 0, s, Nu, Tb, k.nx, x_dev, small);
     return hipGetLastError();
 }
 
