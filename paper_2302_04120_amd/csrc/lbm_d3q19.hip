@@ -391,21 +391,20 @@ __global__ void k_d3_init(D3K k, const double* __restrict__ fld, S* __restrict__
     }
 }
 
-// FP64 macros of the stored state into staging slots 0 rho, 2 ux, 3 uy, 7 uz
+// FP64 macros of the stored state
 template <typename S>
-__global__ void k_d3_macros(D3K k, const S* __restrict__ f, double* __restrict__ out) {
+__global__ void k_d3_macros(D3K k, const S* __restrict__ f, MacroOut out) {
     const long long N = (long long)k.batch * k.nx * k.ny * k.nz;
-    const long long P = k.P;
     for (long long n = blockIdx.x * (long long)blockDim.x + threadIdx.x; n < N;
          n += (long long)gridDim.x * blockDim.x) {
         double d[19], m[19];
         for (int i = 0; i < 19; ++i) d[i] = double(f[bidx(19, i, n)]);
         moments19(d, m);
         const double rho = k.rho_ref + m[0];
-        out[n] = rho;
-        out[2 * P + n] = (m[3] + 0.5 * k.Ft[0]) / rho * k.c;
-        out[3 * P + n] = (m[5] + 0.5 * k.Ft[1]) / rho * k.c;
-        out[7 * P + n] = (m[7] + 0.5 * k.Ft[2]) / rho * k.c;
+        out.put(0, n, rho);
+        out.put(2, n, (m[3] + 0.5 * k.Ft[0]) / rho * k.c);
+        out.put(3, n, (m[5] + 0.5 * k.Ft[1]) / rho * k.c);
+        out.put(7, n, (m[7] + 0.5 * k.Ft[2]) / rho * k.c);
     }
 }
 
@@ -554,7 +553,7 @@ hipError_t launch_d3_init(const D3K& k, const double* fields, S* f, hipStream_t 
 }
 
 template <typename S>
-hipError_t launch_d3_macros(const D3K& k, const S* f, double* out, hipStream_t s) {
+hipError_t launch_d3_macros(const D3K& k, const S* f, const MacroOut& out, hipStream_t s) {
     const long long N = (long long)k.batch * k.nx * k.ny * k.nz;
     hipLaunchKernelGGL(k_d3_macros<S>, dim3(grid_1d(N, 256)), dim3(256), 0, s, k, f, out);
     return hipGetLastError();
@@ -566,7 +565,7 @@ hipError_t launch_d3_macros(const D3K& k, const S* f, double* out, hipStream_t s
     template hipError_t launch_d3_tb2<S>(const D3K&, const D3Tb2Plan&, const S*, S*,     \
                                          hipStream_t);                                   \
     template hipError_t launch_d3_init<S>(const D3K&, const double*, S*, hipStream_t);   \
-    template hipError_t launch_d3_macros<S>(const D3K&, const S*, double*, hipStream_t);
+    template hipError_t launch_d3_macros<S>(const D3K&, const S*, const MacroOut&, hipStream_t);
 LBM_D3_INST(float)
 LBM_D3_INST(double)
 

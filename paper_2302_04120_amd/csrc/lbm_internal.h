@@ -116,6 +116,15 @@ struct P3K {
     double c, cs2;        // outputs
 };
 
+// Where the macro kernels put the FP64 fields (rho, p, ux, uy, T, phi, mu, uz,
+// the bits of the macro mask): null where a field is not wanted.
+struct MacroOut {
+    double* p[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+    __device__ __forceinline__ void put(int field, long long n, double v) const {
+        if (p[field]) p[field][n] = v;
+    }
+};
+
 // Tiles and steps per launch of the many-steps channel kernel (lbm_chan_multi.hip);
 // steps 0: not used.
 constexpr int kChanMultiMax = 16;
@@ -293,7 +302,7 @@ hipError_t launch_d3_tb2(const D3K& k, const D3Tb2Plan& plan, const S* fc, S* fn
 template <typename S>
 hipError_t launch_d3_init(const D3K& k, const double* fields, S* f, hipStream_t s);
 template <typename S>
-hipError_t launch_d3_macros(const D3K& k, const S* f, double* out, hipStream_t s);
+hipError_t launch_d3_macros(const D3K& k, const S* f, const MacroOut& out, hipStream_t s);
 
 // 3D two-phase (lbm_phase3d.hip).  A step is two launches: phi of the stored
 // state into one plane, then the step kernel, which reads phi through an LDS
@@ -304,15 +313,14 @@ hipError_t launch_p3_step(const P3K& k, const S* a, S* b, S* phi, hipStream_t s)
 template <typename S>
 hipError_t launch_p3_init(const P3K& k, const double* fields, S* a, hipStream_t s);
 template <typename S>
-hipError_t launch_p3_macros(const P3K& k, const S* a, S* phi, double* out, hipStream_t s);
+hipError_t launch_p3_macros(const P3K& k, const S* a, S* phi, const MacroOut& out, hipStream_t s);
 
-// macros into staging slots [8][P]: rho, p, ux, uy, T, phi, mu, uz
+// macroscopic fields of the stored state
 template <typename S>
-hipError_t launch_chan_macros(const ChanK& k, const S* a, double* out, hipStream_t s);
+hipError_t launch_chan_macros(const ChanK& k, const S* a, const MacroOut& out, hipStream_t s);
 template <typename S>
-hipError_t launch_phase_macros(const PhaseK& k, const S* a, double* out, hipStream_t s);
-hipError_t launch_d1_macros(const D1K& k, const double* g, double* out, long long P,
-                            hipStream_t s);
+hipError_t launch_phase_macros(const PhaseK& k, const S* a, const MacroOut& out, hipStream_t s);
+hipError_t launch_d1_macros(const D1K& k, const double* g, const MacroOut& out, hipStream_t s);
 
 // per-replica FP64 sums: out[b*4 + f], f = mass, phase, energy, nonfinite
 template <typename S>

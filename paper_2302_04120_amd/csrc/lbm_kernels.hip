@@ -728,7 +728,7 @@ __device__ __forceinline__ void phase_collide(const PhaseK& k, const PhaseLocal<
 // one barrier).  Returns early for threads without a node, after the barrier.
 template <typename S, typename C, bool MACROS, int TX, int TY>
 __device__ __forceinline__ void phase_tile(const PhaseK& k, int tile, const S* __restrict__ A,
-                                           S* __restrict__ B, double* __restrict__ mout,
+                                           S* __restrict__ B, const MacroOut& mout,
                                            C (&sphi)[TY + 2][TX + 2]) {
     constexpr bool RMASS = std::is_same<S, float>::value;
     using PL = PhasePlanes<S>;
@@ -788,14 +788,12 @@ __device__ __forceinline__ void phase_tile(const PhaseK& k, int tile, const S* _
     const PhaseLocal<C> L = phase_local(k, pn, z);
 
     if constexpr (MACROS) {
-        const long long Q = k.P;
-        mout[0 * Q + n] = double(L.rho);
-        mout[1 * Q + n] = double(L.ph) * k.cs2;
-        mout[2 * Q + n] = double(L.ux) * k.c;
-        mout[3 * Q + n] = double(L.uy) * k.c;
-        mout[4 * Q + n] = 0.0;
-        mout[5 * Q + n] = double(L.phi);
-        mout[6 * Q + n] = double(L.mu);
+        mout.put(0, n, double(L.rho));
+        mout.put(1, n, double(L.ph) * k.cs2);
+        mout.put(2, n, double(L.ux) * k.c);
+        mout.put(3, n, double(L.uy) * k.c);
+        mout.put(5, n, double(L.phi));
+        mout.put(6, n, double(L.mu));
         return;
     } else {
         C hs[9], zst[9], pux, puy;
@@ -825,7 +823,7 @@ __device__ __forceinline__ void phase_tile(const PhaseK& k, int tile, const S* _
 
 template <typename S, typename C, bool MACROS, int TX = lbm::TX, int TY = lbm::TY>
 __global__ __launch_bounds__(TX * TY) void k_phase(PhaseK k, const S* __restrict__ A,
-                                               S* __restrict__ B, double* __restrict__ mout) {
+                                               S* __restrict__ B, MacroOut mout) {
     static_assert(2 * (TX + 2) + 2 * TY <= TX * TY, "the ring must fit in one pass of the block");
     __shared__ C sphi[TY + 2][TX + 2];
     const int gx = (k.nx + TX - 1) / TX, gy = (k.ny + TY - 1) / TY;
@@ -918,7 +916,7 @@ __global__ __launch_bounds__(TX * TY) void k_phase_persist(PhaseK k, S* __restri
         if (bad) return;  // uniform: every thread read it after the barrier
         const S* a = (s & 1) ? B : A;
         S* o = (s & 1) ? A : B;
-        phase_tile<S, C, false, TX, TY>(k, tile, a, o, (double*)nullptr, sphi);
+        phase_tile<S, C, false, TX, TY>(k, tile, a, o, MacroOut{}, sphi);
         // Every wave waits until its stores have reached the L2 (vmcnt counts
         // stores on this GPU), the barrier orders them before the first
         // lane's device-scope release, whose L2 write-back then carries the
@@ -1379,9 +1377,8 @@ __global__ void k_d1_init(D1K k, const double* __restrict__ T, double* __restric
 // FP64 macros of the stored state
 // ---------------------------------------------------------------------------
 template <typename S>
-__global__ void k_chan_macros(ChanK k, const S* __restrict__ A, double* __restrict__ out) {
+__global__ void k_chan_macros(ChanK k, const S* __restrict__ A, MacroOut out) {
     const long long N = (long long)k.batch * k.nx * k.ny;
-    const long long P = k.P;
     for (long long n = blockIdx.x * (long long)blockDim.x + threadIdx.x; n < N;
          n += (long long)gridDim.x * blockDim.x) {
         double th = 0.0;
@@ -1394,20 +1391,19 @@ __global__ void k_chan_macros(ChanK k, const S* __restrict__ A, double* __restri
         chan_force(k, th, fx, fy);
         double d[9], drho, rho, ux, uy;
         chan_flow_macros<double, S>(A, k.npl, n, k.rho_ref, fx, fy, d, drho, rho, ux, uy);
-        out[n] = rho;
-        out[2 * P + n] = ux * k.c;
-        out[3 * P + n] = uy * k.c;
-        out[4 * P + n] = k.T_ref + th;
+        out.put(0, n, rho);
+        out.put(2, n, ux * k.c);
+        out.put(3, n, uy * k.c);
+        out.put(4, n, k.T_ref + th);
     }
 }
 
-__global__ void k_d1_macros(D1K k, const double* __restrict__ g, double* __restrict__ out,
-                            long long P) {
+__global__ void k_d1_macros(D1K k, const double* __restrict__ g, MacroOut out) {
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= k.n) return;
     double s = 0;
     for (int i = 0; i < k.q; ++i) s += g[i * k.n + x];
-    out[4 * P + x] = s + 0.5 * k.qdt;
+    out.put(4, x, s + 0.5 * k.qdt);
 }
 
 // ---------------------------------------------------------------------------
@@ -1724,7 +1720,7 @@ hipError_t launch_chan_tb2(const ChanK& k, const S* a, S* b, const S* qw, const 
 // or, for nx in {4, 8, 16, 32}, nx x (512 / nx); half as many rows for FP32
 // steps.
 template <typename S, typename C, bool MACROS>
-hipError_t launch_phase_kernel(const PhaseK& k, const S* a, S* b, double* out, unsigned lds,
+hipError_t launch_phase_kernel(const PhaseK& k, const S* a, S* b, const MacroOut& out, unsigned lds,
                                hipStream_t s) {
     auto ntiles = [&](int tx, int ty) {
         return (long long)((k.nx + tx - 1) / tx) * ((k.ny + ty - 1) / ty) * k.batch;
@@ -1826,9 +1822,9 @@ hipError_t launch_phase_step(const PhaseK& k, const S* a, S* b, bool arith64, hi
     const unsigned lds = std::is_same<S, float>::value ? kPhaseLdsReserve : 0u;  // half tiles
     if (arith64) {  // FP32 storage, every step evaluated in FP64
         if (!std::is_same<S, float>::value) return hipErrorInvalidValue;
-        return launch_phase_kernel<S, double, false>(k, a, b, (double*)nullptr, lds, s);
+        return launch_phase_kernel<S, double, false>(k, a, b, MacroOut{}, lds, s);
     }
-    return launch_phase_kernel<S, S, false>(k, a, b, (double*)nullptr, lds, s);
+    return launch_phase_kernel<S, S, false>(k, a, b, MacroOut{}, lds, s);
 }
 
 // The two-step kernel takes a whole row per workgroup when nx is a multiple
@@ -1941,20 +1937,19 @@ hipError_t launch_d1_init(const D1K& k, const double* T, double* g, hipStream_t 
 }
 
 template <typename S>
-hipError_t launch_chan_macros(const ChanK& k, const S* a, double* out, hipStream_t s) {
+hipError_t launch_chan_macros(const ChanK& k, const S* a, const MacroOut& out, hipStream_t s) {
     const long long N = (long long)k.batch * k.nx * k.ny;
     hipLaunchKernelGGL(k_chan_macros<S>, dim3(grid1(N, 256)), dim3(256), 0, s, k, a, out);
     return hipGetLastError();
 }
 
 template <typename S>
-hipError_t launch_phase_macros(const PhaseK& k, const S* a, double* out, hipStream_t s) {
+hipError_t launch_phase_macros(const PhaseK& k, const S* a, const MacroOut& out, hipStream_t s) {
     return launch_phase_kernel<S, double, true>(k, a, (S*)nullptr, out, 0u, s);
 }
 
-hipError_t launch_d1_macros(const D1K& k, const double* g, double* out, long long P,
-                            hipStream_t s) {
-    hipLaunchKernelGGL(k_d1_macros, dim3((k.n + 255) / 256), dim3(256), 0, s, k, g, out, P);
+hipError_t launch_d1_macros(const D1K& k, const double* g, const MacroOut& out, hipStream_t s) {
+    hipLaunchKernelGGL(k_d1_macros, dim3((k.n + 255) / 256), dim3(256), 0, s, k, g, out);
     return hipGetLastError();
 }
 
@@ -2011,8 +2006,8 @@ hipError_t launch_nusselt(const ChanK& k, const S* a, const S* qw, double qsi, d
                                                 unsigned*, bool, hipStream_t);                    \
     template hipError_t launch_chan_init<S>(const ChanK&, const double*, S*, hipStream_t);       \
     template hipError_t launch_phase_init<S>(const PhaseK&, const double*, S*, hipStream_t);    \
-    template hipError_t launch_chan_macros<S>(const ChanK&, const S*, double*, hipStream_t);    \
-    template hipError_t launch_phase_macros<S>(const PhaseK&, const S*, double*, hipStream_t);  \
+    template hipError_t launch_chan_macros<S>(const ChanK&, const S*, const MacroOut&, hipStream_t); \
+    template hipError_t launch_phase_macros<S>(const PhaseK&, const S*, const MacroOut&, hipStream_t); \
     template hipError_t launch_reduce<S>(int, const ChanK&, const PhaseK&, const D1K&,           \
                                          const D3K&, const P3K&, const S*, int, double*,          \
                                          double*, hipStream_t);                                   \

@@ -94,7 +94,7 @@ template <typename S, bool MACROS>
 __device__ __forceinline__ void p3_node(const P3K& k, const S (&pn)[19], const S (&h)[19], S hlo,
                                         const S (&zz)[19], const S (&pu)[3], long long n, int x,
                                         int y, int z, long long base, S* __restrict__ b,
-                                        double* __restrict__ mout, long long P) {
+                                        const MacroOut& mout) {
     using C = S;
     constexpr bool RMASS = std::is_same<S, float>::value;
     constexpr int PU = RMASS ? 39 : 38;  // first (phi u) plane
@@ -151,14 +151,13 @@ __device__ __forceinline__ void p3_node(const P3K& k, const S (&pn)[19], const S
     const C ph = C(1.5) * (zsum + C(1.5) * drl * ug - C(0.5) * rho * uu);
 
     if constexpr (MACROS) {
-        mout[n] = double(rho);
-        mout[P + n] = double(ph) * k.cs2;
-        mout[2 * P + n] = double(u[0]) * k.c;
-        mout[3 * P + n] = double(u[1]) * k.c;
-        mout[4 * P + n] = 0.0;
-        mout[5 * P + n] = double(phi);
-        mout[6 * P + n] = double(mu);
-        mout[7 * P + n] = double(u[2]) * k.c;
+        mout.put(0, n, double(rho));
+        mout.put(1, n, double(ph) * k.cs2);
+        mout.put(2, n, double(u[0]) * k.c);
+        mout.put(3, n, double(u[1]) * k.c);
+        mout.put(5, n, double(phi));
+        mout.put(6, n, double(mu));
+        mout.put(7, n, double(u[2]) * k.c);
         return;
     } else {
         // ---- interface populations (Eq. eq_lattice_boltzmann_interface,
@@ -264,7 +263,7 @@ template <typename S, bool MACROS>
 __global__ __launch_bounds__(P3Tile<S>::Threads) void k_p3_step(P3K k, const S* __restrict__ a,
                                                         S* __restrict__ b,
                                                         const S* __restrict__ phig,
-                                                        double* __restrict__ mout) {
+                                                        MacroOut mout) {
     using C = S;
     constexpr bool RMASS = std::is_same<S, float>::value;
     constexpr int PU = RMASS ? 39 : 38;  // first (phi u) plane
@@ -272,7 +271,6 @@ __global__ __launch_bounds__(P3Tile<S>::Threads) void k_p3_step(P3K k, const S* 
     constexpr int kPX = T::X, kPY = T::Y, kPZ = T::Z, kHX = T::HX, kHY = T::HY;
     __shared__ C sphi[T::HZ][T::HY][T::HX];
     const int nx = k.nx, ny = k.ny, nz = k.nz;
-    const long long P = k.P;
     const int gx = (nx + kPX - 1) / kPX, gy = (ny + kPY - 1) / kPY, gz = (nz + kPZ - 1) / kPZ;
     int tile;
     if (!xcd_tile(gx * gy * gz * k.batch, tile)) return;  // whole workgroup, before the barrier
@@ -312,7 +310,7 @@ __global__ __launch_bounds__(P3Tile<S>::Threads) void k_p3_step(P3K k, const S* 
     C pn[19];
 #pragma unroll
     for (int i = 0; i < 19; ++i) pn[i] = sphi[tz + 1 + E3Z[i]][ty + 1 + E3Y[i]][tx + 1 + E3X[i]];
-    p3_node<S, MACROS>(k, pn, h, hlo, zz, pu, n, x, y, z, base, b, mout, P);
+    p3_node<S, MACROS>(k, pn, h, hlo, zz, pu, n, x, y, z, base, b, mout);
 }
 
 
@@ -379,7 +377,7 @@ hipError_t launch_p3_step(const P3K& k, const S* a, S* b, S* phi, hipStream_t s)
     const long long tiles = p3_tiles<S>(k);
     dim3 blk(P3Tile<S>::X, P3Tile<S>::Y, P3Tile<S>::Z), grd(unsigned((tiles + kXCD - 1) / kXCD * kXCD));
     hipLaunchKernelGGL((k_p3_step<S, false>), grd, blk, 0, s, k, a, b, (const S*)phi,
-                       (double*)nullptr);
+                       MacroOut{});
     return hipGetLastError();
 }
 
@@ -391,7 +389,7 @@ hipError_t launch_p3_init(const P3K& k, const double* fields, S* a, hipStream_t 
 }
 
 template <typename S>
-hipError_t launch_p3_macros(const P3K& k, const S* a, S* phi, double* out, hipStream_t s) {
+hipError_t launch_p3_macros(const P3K& k, const S* a, S* phi, const MacroOut& out, hipStream_t s) {
     hipError_t e = launch_phi<S>(k, a, phi, s);
     if (e != hipSuccess) return e;
     const long long tiles = p3_tiles<S>(k);
@@ -403,7 +401,7 @@ hipError_t launch_p3_macros(const P3K& k, const S* a, S* phi, double* out, hipSt
 #define LBM_P3_INST(S)                                                                       \
     template hipError_t launch_p3_step<S>(const P3K&, const S*, S*, S*, hipStream_t);        \
     template hipError_t launch_p3_init<S>(const P3K&, const double*, S*, hipStream_t);       \
-    template hipError_t launch_p3_macros<S>(const P3K&, const S*, S*, double*, hipStream_t);
+    template hipError_t launch_p3_macros<S>(const P3K&, const S*, S*, const MacroOut&, hipStream_t);
 LBM_P3_INST(float)
 LBM_P3_INST(double)
 
