@@ -1244,57 +1244,77 @@ __global__ __launch_bounds__(kTbMaxNx) void k_phase_tb2(PhaseK k, const S* __res
 }
 
 // ---------------------------------------------------------------------------
-// 1D thermal BGK, whole run in one block (n <= 1024): LDS streaming
+// 1D thermal BGK, whole run in one workgroup of WAVES waves (n <= 64 WAVES M).
+// A step is a serial chain of a few FP64 operations, so what it pays for is
+// latency: a lane keeps M consecutive nodes in registers, its neighbours'
+// values come by a shift across the wave, and only a run of several waves
+// exchanges its ends through LDS (one barrier per step).  With one node per
+// thread, LDS streaming and two barriers of a 1024-thread workgroup a step took
+// 0.59 us whatever n.  Q = 2 (D1Q2) or 3 (D1Q3).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_d1(D1K k, double* __restrict__ g, int nsteps) {
-    __shared__ double sg[3][1024];
-    const int x = threadIdx.x;
-    const int n = k.n, q = k.q;
-    int ex[3];
-    double w[3];
-    if (q == 3) {
-        ex[0] = 0; ex[1] = 1; ex[2] = -1;
-        w[0] = 4.0 / 6; w[1] = 1.0 / 6; w[2] = 1.0 / 6;
-    } else {
-        ex[0] = 1; ex[1] = -1; ex[2] = 0;
-        w[0] = 0.5; w[1] = 0.5; w[2] = 0.0;
-    }
-    double v[3] = {0, 0, 0};
-    const bool act = x < n;
-    if (act)
-        for (int i = 0; i < q; ++i) v[i] = g[i * n + x];
+// v of the lane before (shr) or after (shl) in the wave; 0 at its end
+__device__ __forceinline__ double wave_shr1(double v) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x138, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, lo, 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double wave_shl1(double v) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x130, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, lo, 0x130, 0xf, 0xf, false));
+}
+
+template <int Q, int M, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_d1(D1K k, double* __restrict__ g, int nsteps) {
+    __shared__ double ends[2][WAVES + 2][2];  // per wave: leaving to the right, to the left
+    constexpr int ex[3] = {Q == 3 ? 0 : 1, Q == 3 ? 1 : -1, Q == 3 ? -1 : 0};
+    constexpr double w[3] = {Q == 3 ? 4.0 / 6 : 0.5, Q == 3 ? 1.0 / 6 : 0.5, Q == 3 ? 1.0 / 6 : 0.0};
+    constexpr int R = Q == 3 ? 1 : 0, L = Q == 3 ? 2 : 1;  // right and left movers
+    const int n = k.n, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int x0 = int(threadIdx.x) * M;
+    double v[M][Q];
+#pragma unroll
+    for (int j = 0; j < M; ++j)
+#pragma unroll
+        for (int i = 0; i < Q; ++i) v[j][i] = x0 + j < n ? g[i * n + x0 + j] : 0.0;
     for (int s = 0; s < nsteps; ++s) {
-        if (act) {
+        double sg[M][Q];
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
             double T = 0;
-            for (int i = 0; i < q; ++i) T += v[i];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) T += v[j][i];
             T += 0.5 * k.qdt;
-            for (int i = 0; i < q; ++i) {
+#pragma unroll
+            for (int i = 0; i < Q; ++i) {
                 const double geq = w[i] * T * (1.0 + k.ufac * ex[i]);
-                sg[i][x] = v[i] - k.w_tau * (v[i] - geq) + (1.0 - 0.5 * k.w_tau) * w[i] * k.qdt;
+                sg[j][i] = v[j][i] - k.w_tau * (v[j][i] - geq) + (1.0 - 0.5 * k.w_tau) * w[i] * k.qdt;
             }
         }
-        __syncthreads();
-        if (act) {
-            int unknown = -1;
-            double known = 0.0;
-            for (int i = 0; i < q; ++i) {
-                const int xs = x - ex[i];
-                if (xs >= 0 && xs < n) {
-                    v[i] = sg[i][xs];
-                    known += v[i];
-                } else {
-                    unknown = i;
-                }
-            }
-            if (unknown >= 0) {  // wet-node Dirichlet with the half source
-                const double Tw = (x == 0) ? k.T0 : k.TL;
-                v[unknown] = Tw - 0.5 * k.qdt - known;
-            }
+        double from_left = wave_shr1(sg[M - 1][R]), from_right = wave_shl1(sg[0][L]);
+        if constexpr (WAVES > 1) {
+            if (lane == 63) ends[s & 1][wv + 1][0] = sg[M - 1][R];
+            if (lane == 0) ends[s & 1][wv + 1][1] = sg[0][L];
+            __syncthreads();  // the other buffer's reads ended a step ago
+            if (lane == 0) from_left = ends[s & 1][wv][0];
+            if (lane == 63) from_right = ends[s & 1][wv + 2][1];
         }
-        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            if constexpr (Q == 3) v[j][0] = sg[j][0];
+            v[j][R] = j > 0 ? sg[j > 0 ? j - 1 : 0][R] : from_left;
+            v[j][L] = j < M - 1 ? sg[j < M - 1 ? j + 1 : 0][L] : from_right;
+            // wet-node Dirichlet with the half source: the unknown population
+            const int x = x0 + j;
+            if (x == 0) v[j][R] = k.T0 - 0.5 * k.qdt - (Q == 3 ? v[j][0] + v[j][L] : v[j][L]);
+            if (x == n - 1) v[j][L] = k.TL - 0.5 * k.qdt - (Q == 3 ? v[j][0] + v[j][R] : v[j][R]);
+        }
     }
-    if (act)
-        for (int i = 0; i < q; ++i) g[i * n + x] = v[i];
+#pragma unroll
+    for (int j = 0; j < M; ++j)
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            if (x0 + j < n) g[i * n + x0 + j] = v[j][i];
 }
 
 // ---------------------------------------------------------------------------
@@ -1912,9 +1932,22 @@ hipError_t launch_phase_tb2(const PhaseK& k, const S* a, S* b, int seg, hipStrea
     return hipGetLastError();
 }
 
+// One wave of 1, 2 or 4 nodes a lane up to 256 nodes, then four waves.
 hipError_t launch_d1(const D1K& k, double* g, int nsteps, hipStream_t s) {
-    hipLaunchKernelGGL(k_d1, dim3(1), dim3(1024), 0, s, k, g, nsteps);
-    return hipGetLastError();
+    if (k.n < 3 || k.n > 1024) return hipErrorInvalidValue;
+    auto go = [&](auto kern, int waves) {
+        hipLaunchKernelGGL(kern, dim3(1), dim3(64 * waves), 0, s, k, g, nsteps);
+        return hipGetLastError();
+    };
+    auto pick = [&](auto q) {
+        constexpr int Q = decltype(q)::value;
+        if (k.n <= 64) return go(k_d1<Q, 1, 1>, 1);
+        if (k.n <= 128) return go(k_d1<Q, 2, 1>, 1);
+        if (k.n <= 256) return go(k_d1<Q, 4, 1>, 1);
+        if (k.n <= 512) return go(k_d1<Q, 2, 4>, 4);
+        return go(k_d1<Q, 4, 4>, 4);
+    };
+    return k.q == 3 ? pick(std::integral_constant<int, 3>{}) : pick(std::integral_constant<int, 2>{});
 }
 
 template <typename S>
