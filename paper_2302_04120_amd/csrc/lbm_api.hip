@@ -392,6 +392,29 @@ hipError_t step_chan_multi(lbm_ctx* c, int left) {
     return hipSuccess;
 }
 
+// Whether runs of two-phase steps go through the many-steps kernel: as for the
+// channel.
+bool use_phase_multi(const lbm_ctx* c) {
+    if (c->desc.lattice != LBM_D2Q9_PHASE || c->fusion != 0 || c->pmulti.steps < 1 || use_tb2(c))
+        return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+}
+
+template <typename S>
+hipError_t step_phase_multi(lbm_ctx* c, int left) {
+    while (left > 0) {
+        const int m = even_share(left, c->pmulti.steps);
+        hipError_t e = launch_phase_multi<S>(c->pk, c->pmulti, (const S*)bufA(c), (S*)bufB(c),
+                                             c->desc.prec == LBM_FP32_DEV_ARITH64, m, c->stream);
+        if (e != hipSuccess) return e;
+        c->cur ^= 1;
+        c->t += m;
+        left -= m;
+    }
+    return hipSuccess;
+}
+
 // Whether the next two D3Q19 steps go through the two-step kernel: automatic
 // mode where the plan expects it to be faster, mode 2 wherever it applies.
 // Not under the caller's stream capture: two captured steps have always ended
@@ -841,6 +864,13 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
                      : d.prec == LBM_FP32_DEV_ARITH64 ? 0  // the two-step kernel computes in S
                                                        : phase_tb2_seg<float>(pk);
     }
+    if (d.lattice == LBM_D2Q9_PHASE) {
+        DeviceGuard g(c->device);
+        if (!c->pmulti_made)  // depends on the grid and its boundaries only
+            c->pmulti = d.prec == LBM_FP64 ? phase_multi_plan<double>(pk, false)
+                                           : phase_multi_plan<float>(pk, d.prec == LBM_FP32_DEV_ARITH64);
+        c->pmulti_made = true;
+    }
     if (d.lattice == LBM_D2Q9_D2Q5 && chan_tb2_fits(ck)) {
         DeviceGuard g(c->device);
         c->tb2_seg = d.prec == LBM_FP64 ? chan_tb2_seg<double>(ck) : chan_tb2_seg<float>(ck);
@@ -1027,6 +1057,10 @@ lbm_status step_run(lbm_ctx* c, int n) {
     if (n > 0 && use_persist(c)) return f64 ? step_persist<double>(c, n) : step_persist<float>(c, n);
     if (n > 1 && use_chan_multi(c)) {
         hipError_t e = f64 ? step_chan_multi<double>(c, n) : step_chan_multi<float>(c, n);
+        return e == hipSuccess ? LBM_OK : hip_fail(c, e, "step kernel");
+    }
+    if (n > 1 && use_phase_multi(c)) {
+        hipError_t e = f64 ? step_phase_multi<double>(c, n) : step_phase_multi<float>(c, n);
         return e == hipSuccess ? LBM_OK : hip_fail(c, e, "step kernel");
     }
     int s = 0;

@@ -268,13 +268,8 @@ ChanMultiPlan chan_multi_plan(const ChanK& k) {
                                   : (k.tq == 9 ? Cost{5.6, 2.5, 0.51, 0.76} : Cost{4.8, 1.8, 0.48, 0.48});
     constexpr int kWaves = cm_max_nodes<S>() / 64;
     int resident[kWaves + 1] = {};  // workgroups of that many waves per CU
-    for (int wv = 1; wv <= kWaves; ++wv) {
-        int r = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, cm_kernel<S>(k.tq, wv * 64), wv * 64, 0) !=
-            hipSuccess)
-            return best;
-        resident[wv] = r;
-    }
+    for (int wv = 1; wv <= kWaves; ++wv)
+        resident[wv] = resident_workgroups((const void*)cm_kernel<S>(k.tq, wv * 64), wv);
     const double bytes = double(k.nx) * k.ny * k.batch * k.npl * sizeof(S) * 2;
     double best_cost = 0.85 * (4.6 + bytes / 5.6e6);
     for (int h = 2; h <= 10; ++h)

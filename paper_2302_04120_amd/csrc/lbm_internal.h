@@ -73,6 +73,9 @@ struct PhaseK {
     double dxW;           // dx / W
     double Geps;          // |G| threshold for n = 0 (= normal_eps dx / 3)
     double c, cs2;        // outputs
+    __host__ __device__ __forceinline__ double drho() const { return rho_l - rho_g; }
+    __host__ __device__ __forceinline__ double dnuh() const { return nuh_l - nuh_g; }
+    __host__ __device__ __forceinline__ double dzh() const { return zh_l - zh_g; }
 };
 
 // Derivatives of the relaxation rates (times dt) with respect to tau and tau_T,
@@ -129,6 +132,13 @@ struct MacroOut {
 // steps 0: not used.
 constexpr int kChanMultiMax = 16;
 struct ChanMultiPlan {
+    int steps = 0, ntx = 0, nty = 0;
+};
+
+// Tiles and steps per launch of the many-steps two-phase kernel
+// (lbm_phase_multi.hip); steps 0: not used.
+constexpr int kPhaseMultiMax = 8;
+struct PhaseMultiPlan {
     int steps = 0, ntx = 0, nty = 0;
 };
 
@@ -204,6 +214,8 @@ struct lbm_ctx {
     int fusion = 0;
     lbm::ChanMultiPlan cmulti;          // channel: many steps per launch (automatic mode)
     bool cmulti_made = false;
+    lbm::PhaseMultiPlan pmulti;         // two-phase D2Q9: many steps per launch (automatic mode)
+    bool pmulti_made = false;
     lbm::D3Tb2Plan d3tb2;               // D3Q19: two steps per launch (automatic mode)
     int tb2_seg = 0;                    // rows per two-step workgroup (0: kernel not usable)
     unsigned* persist_flags = nullptr;  // kPersistMaxTiles step counters, then the error word
@@ -211,6 +223,18 @@ struct lbm_ctx {
 };
 
 namespace lbm {
+
+// Workgroups of `waves` waves of a kernel that a CU holds at once, from its
+// registers (512 per lane and SIMD, at most 8 waves) and LDS (160 KB); 0 on
+// error.
+inline int resident_workgroups(const void* kernel, int waves) {
+    hipFuncAttributes f;
+    if (hipFuncGetAttributes(&f, kernel) != hipSuccess || waves < 1) return 0;
+    const int regs = f.numRegs > 0 ? (f.numRegs + 7) / 8 * 8 : 8;
+    const int slots = 4 * (512 / regs < 8 ? 512 / regs : 8);
+    const int lds = f.sharedSizeBytes > 0 ? int(163840 / f.sharedSizeBytes) : slots;
+    return slots / waves < lds ? slots / waves : lds;
+}
 
 constexpr int kRedBlocks = 256;  // first-pass blocks per replica and field
 
@@ -250,6 +274,13 @@ hipError_t launch_chan_multi(const ChanK& k, const ChanMultiPlan& plan, const S*
 // evaluate the step in FP64 on FP32 storage (S = float)
 template <typename S>
 hipError_t launch_phase_step(const PhaseK& k, const S* a, S* b, bool arith64, hipStream_t s);
+// nsteps (at most plan.steps) two-phase steps in one launch; phase_multi_plan
+// gives steps 0 where another kernel is faster
+template <typename S>
+PhaseMultiPlan phase_multi_plan(const PhaseK& k, bool arith64);
+template <typename S>
+hipError_t launch_phase_multi(const PhaseK& k, const PhaseMultiPlan& plan, const S* a, S* b,
+                              bool arith64, int nsteps, hipStream_t s);
 // two steps in one launch; the whole state (populations and (phi u)) moves
 // from buffer a to buffer b; needs phase_tb2_fits.  seg: rows per workgroup
 // (phase_tb2_seg, fixed when the parameters are set)
