@@ -269,7 +269,9 @@ hipError_t step_once(lbm_ctx* c) {
     S* a = (S*)bufA(c);
     S* b = (S*)bufB(c);
     if (lat == LBM_D3Q19) return launch_d3_step<S>(c->d3k, a, b, c->stream);
-    if (lat == LBM_D3Q19_PHASE) return launch_p3_step<S>(c->p3k, a, b, (S*)c->phi3, c->stream);
+    if (lat == LBM_D3Q19_PHASE)
+        return launch_p3_step<S>(c->p3k, c->fusion == 1 ? P3MarchPlan{} : c->p3march, a, b,
+                                 (S*)c->phi3, c->stream);
     if (lat == LBM_D2Q9_D2Q5) {
         return launch_chan_step<S>(c->ck, a, b, aux_qw<S>(c), aux_uin<S>(c), aux_tin<S>(c),
                                    flux_mod(c), c->stream);
@@ -877,6 +879,12 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
         if (!c->cmulti_made)  // depends on the grid and its boundaries only
             c->cmulti = d.prec == LBM_FP64 ? chan_multi_plan<double>(ck) : chan_multi_plan<float>(ck);
         c->cmulti_made = true;
+    }
+    if (d.lattice == LBM_D3Q19_PHASE) {
+        DeviceGuard g(c->device);
+        if (!c->p3march_made)  // depends on the grid only
+            c->p3march = d.prec == LBM_FP64 ? p3_march_plan<double>(p3k) : p3_march_plan<float>(p3k);
+        c->p3march_made = true;
     }
     if (d.lattice == LBM_D3Q19) {
         DeviceGuard g(c->device);

@@ -117,6 +117,9 @@ struct P3K {
     double dxW;           // dx / W
     double Geps;          // |G| threshold for n = 0
     double c, cs2;        // outputs
+    __host__ __device__ __forceinline__ double drho() const { return rho_l - rho_g; }
+    __host__ __device__ __forceinline__ double dnuh() const { return nuh_l - nuh_g; }
+    __host__ __device__ __forceinline__ double dzh() const { return zh_l - zh_g; }
 };
 
 // Where the macro kernels put the FP64 fields (rho, p, ux, uy, T, phi, mu, uz,
@@ -140,6 +143,12 @@ struct ChanMultiPlan {
 constexpr int kPhaseMultiMax = 8;
 struct PhaseMultiPlan {
     int steps = 0, ntx = 0, nty = 0;
+};
+
+// Tiles per plane and z segments per replica of the 3D two-phase step that
+// sums phi as it marches; ntx 0: not used.
+struct P3MarchPlan {
+    int ntx = 0, nty = 0, nseg = 0;
 };
 
 // Tiles per plane and z segments per replica of the two-step D3Q19 kernel;
@@ -216,6 +225,8 @@ struct lbm_ctx {
     bool cmulti_made = false;
     lbm::PhaseMultiPlan pmulti;         // two-phase D2Q9: many steps per launch (automatic mode)
     bool pmulti_made = false;
+    lbm::P3MarchPlan p3march;           // 3D two-phase: one marching launch per step
+    bool p3march_made = false;
     lbm::D3Tb2Plan d3tb2;               // D3Q19: two steps per launch (automatic mode)
     int tb2_seg = 0;                    // rows per two-step workgroup (0: kernel not usable)
     unsigned* persist_flags = nullptr;  // kPersistMaxTiles step counters, then the error word
@@ -335,12 +346,16 @@ hipError_t launch_d3_init(const D3K& k, const double* fields, S* f, hipStream_t 
 template <typename S>
 hipError_t launch_d3_macros(const D3K& k, const S* f, const MacroOut& out, hipStream_t s);
 
-// 3D two-phase (lbm_phase3d.hip).  A step is two launches: phi of the stored
-// state into one plane, then the step kernel, which reads phi through an LDS
-// tile with a one-node halo.  Buffer planes: h 0-18, z 19-37, the low part of
-// h_0 at 38 (FP32 only), then (phi u) of the previous step (3 planes).
+// 3D two-phase (lbm_phase3d.hip).  A step is one launch that sums phi as it
+// marches (plan from p3_march_plan), or, with an empty plan, two: phi of the
+// stored state into one plane, then the step kernel, which reads phi through an
+// LDS tile with a one-node halo.  Buffer planes: h 0-18, z 19-37, the low part
+// of h_0 at 38 (FP32 only), then (phi u) of the previous step (3 planes).
 template <typename S>
-hipError_t launch_p3_step(const P3K& k, const S* a, S* b, S* phi, hipStream_t s);
+P3MarchPlan p3_march_plan(const P3K& k);
+template <typename S>
+hipError_t launch_p3_step(const P3K& k, const P3MarchPlan& plan, const S* a, S* b, S* phi,
+                          hipStream_t s);
 template <typename S>
 hipError_t launch_p3_init(const P3K& k, const double* fields, S* a, hipStream_t s);
 template <typename S>
