@@ -167,8 +167,8 @@ def run_wide(cells, steps, warmup, prec, fusion=0):
 
 def run_channel(nx, ny, steps, warmup, prec, fusion=1):
     """The heated-channel step (D2Q9 MRT flow + D2Q5 thermal, velocity inlet,
-    pressure outlet, flux walls) on a roofline-sized grid; fusion 2 runs two
-    steps per launch (the state crosses HBM once per two steps)."""
+    pressure outlet, flux walls) on a roofline-sized grid; fusion 2 runs
+    several steps per launch (the state crosses HBM once per launch)."""
     import torch
     from paper_2302_04120_amd import lbm, workloads as WL
     prm, ini = WL.channel(nx=nx, ny=ny)
@@ -196,13 +196,14 @@ def run_channel(nx, ny, steps, warmup, prec, fusion=1):
         raise RuntimeError("non-finite populations after the timed steps")
     L.close()
     S = "float" if prec == "fp32" else "double"
-    two = fusion != 1  # the library's choice at this size is the two-step kernel
-    per_step = CHAN_BYTES_PER_LU[prec] * nodes / (2 if two else 1)  # bytes a step moves
+    # steps per launch of the library's choice at this size
+    spl = 1 if fusion == 1 else (4 if prec == "fp32" else 3)
+    per_step = CHAN_BYTES_PER_LU[prec] * nodes / spl  # bytes a step moves
     return dict(mlups=nodes * steps / wall / 1e6, kernel_ms=kernel_ms,
                 hbm_frac=per_step / (kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                 grid="%dx%d" % (nx, ny), fusion=fusion,
-                kernel=("k_chan_tb2<%s, %s, false, 5>" % (S, "true" if nx % 64 == 0 else "false")
-                        if two else "k_chan_step<%s, 5>" % S))
+                kernel=("k_chan_march<%s, %s, false, 5, %d>" % (S, "true" if nx % 64 == 0 else "false", spl)
+                        if spl > 1 else "k_chan_step<%s, 5>" % S))
 
 
 def run_d3(n, steps, warmup, prec, mrt=True):
@@ -231,14 +232,15 @@ def run_d3(n, steps, warmup, prec, mrt=True):
     kernel_ms = e0.elapsed_time(e1) / steps
     nodes = n ** 3
     L.close()
-    gbs = D3_BYTES_PER_LU[prec] * nodes / (kernel_ms * 1e-3) / 1e9
+    # two steps per launch: the state crosses HBM once per two steps
+    gbs = D3_BYTES_PER_LU[prec] / 2 * nodes / (kernel_ms * 1e-3) / 1e9
     return dict(mlups=nodes * steps / wall / 1e6, kernel_ms=kernel_ms, hbm_GBps=gbs,
                 hbm_frac=gbs / HBM_PEAK_GBS, grid="%d^3" % n, collision="mrt" if mrt else "bgk",
-                kernel="k_d3_step<%s>" % ("float" if prec == "fp32" else "double"))
+                kernel="k_d3_tb2<%s>" % ("float" if prec == "fp32" else "double"))
 
 
 def run_p3(n, steps, warmup, prec, cell=64, R_nodes=16.0):
-    """The 3D two-phase step (phi pass + step kernel) on an n^3 periodic box
+    """The 3D two-phase step on an n^3 periodic box
     filled with air spheres of radius R_nodes in water, one per cell^3 (the
     air-water system of the Sec. 4.3 property table, density ratio 842)."""
     import torch
@@ -271,8 +273,7 @@ def run_p3(n, steps, warmup, prec, cell=64, R_nodes=16.0):
     gbs = P3_BYTES_PER_LU[prec] * nodes / (step_ms * 1e-3) / 1e9
     return dict(mlups=nodes * steps / wall / 1e6, step_ms=step_ms, state_GBps=gbs,
                 state_frac=gbs / HBM_PEAK_GBS, grid="%d^3" % n,
-                kernels="k_p3_phi<%s> + k_p3_step<%s,false>" % ((("float",) * 2) if prec == "fp32"
-                                                               else (("double",) * 2)))
+                kernel="k_p3_march<%s>" % ("float" if prec == "fp32" else "double"))
 
 
 def run_layered_batch(batch, steps, warmup, prec):

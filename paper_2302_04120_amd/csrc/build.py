@@ -15,7 +15,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 PKG = os.path.dirname(HERE)
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "liblbm.so")
-SOURCES = ["lbm_api.hip", "lbm_kernels.hip", "lbm_chan_multi.hip", "lbm_phase_multi.hip",
+SOURCES = ["lbm_api.hip", "lbm_kernels.hip", "lbm_chan_multi.hip", "lbm_chan_march.hip",
+           "lbm_phase_multi.hip",
            "lbm_adjoint.hip", "lbm_d3q19.hip", "lbm_phase3d.hip"]
 
 

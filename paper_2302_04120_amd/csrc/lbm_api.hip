@@ -279,20 +279,23 @@ hipError_t step_once(lbm_ctx* c) {
     return launch_phase_step<S>(c->pk, a, b, c->desc.prec == LBM_FP32_DEV_ARITH64, c->stream);
 }
 
-// Whether the next two steps go through a two-step kernel (mode 2 takes it
-// where the kernel covers the configuration).  Automatic mode takes it when
-// its workgroups (one per row segment, x-tile and replica; two or three are
-// resident per CU) fill the 256 CUs and, for rows in x-tiles, at least 90 %
-// of the launched lanes hold stored columns; smaller or narrow grids keep
-// the single-step kernel, whose tiles spread over more CUs.
+// Whether the next two two-phase steps go through the two-step kernel (mode 2
+// takes it where the kernel covers the configuration).  Automatic mode takes it
+// when its workgroups (one per row segment, x-tile and replica; two are resident
+// per CU) fill the 256 CUs and, for rows in x-tiles, at least 90 % of the
+// launched lanes hold stored columns; smaller or narrow grids keep the
+// single-step kernel, whose tiles spread over more CUs.
 bool use_tb2(const lbm_ctx* c) {
-    if (c->fusion == 1 || c->tb2_seg < 1) return false;
-    if (c->desc.lattice == LBM_D2Q9_D2Q5)
-        return c->fusion == 2 || (c->fusion == 0 && chan_tb2_workgroups(c->ck, c->tb2_seg) >= 512 &&
-                                  chan_tb2_lane_use(c->ck) >= 0.9);
-    if (c->desc.lattice != LBM_D2Q9_PHASE) return false;
+    if (c->desc.lattice != LBM_D2Q9_PHASE || c->fusion == 1 || c->tb2_seg < 1) return false;
     if (c->fusion == 2) return true;
     return phase_tb2_workgroups(c->pk, c->tb2_seg) >= 512 && phase_tb2_lane_use(c->pk) >= 0.9;
+}
+
+// Whether channel steps go through the marching kernel: mode 2 wherever it covers
+// the configuration, automatic mode where its plan expects it to be fastest.
+bool use_march(const lbm_ctx* c) {
+    if (c->desc.lattice != LBM_D2Q9_D2Q5 || c->cmarch.steps < 2) return false;
+    return c->fusion == 2 || (c->fusion == 0 && c->cmarch.fast);
 }
 
 // The many-steps kernel needs the grid split into at most kPersistMaxTiles
@@ -356,16 +359,22 @@ lbm_status step_persist(lbm_ctx* c, int n) {
     return LBM_OK;
 }
 
+// Whether the caller is capturing the stream (as opposed to the context's own
+// step graphs).
+bool caller_captures(const lbm_ctx* c) {
+    if (c->own_capture) return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
+}
+
 // Whether runs of steps go through the many-steps channel kernel: automatic
 // mode, where the plan made with the parameters expects it to be faster.  Not
 // under the caller's stream capture: the number of buffer swaps of a captured
 // run must not depend on the plan (an even number of steps leaves the state in
 // the buffer the replay starts from).
 bool use_chan_multi(const lbm_ctx* c) {
-    if (c->desc.lattice != LBM_D2Q9_D2Q5 || c->fusion != 0 || c->cmulti.steps < 2 || use_tb2(c))
-        return false;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+    return c->desc.lattice == LBM_D2Q9_D2Q5 && c->fusion == 0 && c->cmulti.steps >= 2 &&
+           !caller_captures(c);
 }
 
 // Steps of the next launch when left steps go in launches of at most `most`
@@ -397,10 +406,8 @@ hipError_t step_chan_multi(lbm_ctx* c, int left) {
 // Whether runs of two-phase steps go through the many-steps kernel: as for the
 // channel.
 bool use_phase_multi(const lbm_ctx* c) {
-    if (c->desc.lattice != LBM_D2Q9_PHASE || c->fusion != 0 || c->pmulti.steps < 1 || use_tb2(c))
-        return false;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+    return c->desc.lattice == LBM_D2Q9_PHASE && c->fusion == 0 && c->pmulti.steps >= 1 &&
+           !use_tb2(c) && !caller_captures(c);
 }
 
 template <typename S>
@@ -425,45 +432,37 @@ bool use_d3_tb2(const lbm_ctx* c) {
     if (c->desc.lattice != LBM_D3Q19 || c->d3tb2.ntx < 1 ||
         !(c->fusion == 2 || (c->fusion == 0 && c->d3tb2.fast)))
         return false;
-    if (c->own_capture) return true;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(c->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+    return !caller_captures(c);
 }
 
-// Enqueue m (1 or 2) steps, advancing the buffer parity and the step count;
-// *swaps receives the number of buffer swaps made.
+// Enqueue the next launch of a run of `left` steps, advancing the buffer parity
+// and the step count; *done receives its steps and *swaps the number of buffer
+// swaps made.  While the caller captures the stream, a marching channel launch
+// takes two steps.
 template <typename S>
-hipError_t advance(lbm_ctx* c, int m, int* swaps) {
-    *swaps = 0;
-    if (m == 2 && use_d3_tb2(c)) {
-        hipError_t e = launch_d3_tb2<S>(c->d3k, c->d3tb2, (const S*)bufA(c), (S*)bufB(c), c->stream);
-        if (e != hipSuccess) return e;
-        c->cur ^= 1;
-        c->t += 2;
-        *swaps = 1;
-        return hipSuccess;
+hipError_t advance(lbm_ctx* c, int left, int* done, int* swaps) {
+    hipError_t e;
+    *swaps = 1;
+    if (left >= 2 && use_d3_tb2(c)) {
+        *done = 2;
+        e = launch_d3_tb2<S>(c->d3k, c->d3tb2, (const S*)bufA(c), (S*)bufB(c), c->stream);
+    } else if (left >= 2 && use_march(c)) {
+        const int m = caller_captures(c) ? 2 : even_share(left, c->cmarch.steps);
+        double mods[4];
+        for (int i = 0; i < m; ++i) mods[i] = flux_mod_at(c, c->t + i);
+        *done = m;
+        e = launch_chan_march<S>(c->ck, m, (const S*)bufA(c), (S*)bufB(c), aux_qw<S>(c),
+                                 aux_uin<S>(c), aux_tin<S>(c), mods, c->cmarch.nseg, c->stream);
+    } else if (left >= 2 && use_tb2(c)) {
+        *done = 2;
+        e = launch_phase_tb2<S>(c->pk, (const S*)bufA(c), (S*)bufB(c), c->tb2_seg, c->stream);
+    } else {
+        *done = 1;
+        e = step_once<S>(c);
     }
-    if (m == 2 && use_tb2(c)) {
-        hipError_t e =
-            c->desc.lattice == LBM_D2Q9_D2Q5
-                ? launch_chan_tb2<S>(c->ck, (const S*)bufA(c), (S*)bufB(c), aux_qw<S>(c),
-                                     aux_uin<S>(c), aux_tin<S>(c), flux_mod_at(c, c->t),
-                                     flux_mod_at(c, c->t + 1), c->tb2_seg, c->stream)
-                : launch_phase_tb2<S>(c->pk, (const S*)bufA(c), (S*)bufB(c), c->tb2_seg,
-                                      c->stream);
-        if (e != hipSuccess) return e;
-        c->cur ^= 1;
-        c->t += 2;
-        *swaps = 1;
-        return hipSuccess;
-    }
-    for (int k = 0; k < m; ++k) {
-        hipError_t e = step_once<S>(c);
-        if (e != hipSuccess) return e;
-        c->cur ^= 1;
-        c->t += 1;
-        ++*swaps;
-    }
+    if (e != hipSuccess) return e;
+    c->cur ^= 1;
+    c->t += *done;
     return hipSuccess;
 }
 
@@ -505,10 +504,11 @@ hipError_t step_replay(lbm_ctx* c) {
         const long long t0 = c->t;
         hipError_t el = hipSuccess;
         int swaps = 0;
-        for (int k = 0; k < c->graph_steps && el == hipSuccess; k += 2) {
-            int sw = 0;
-            el = advance<S>(c, 2, &sw);
+        for (int k = 0; k < c->graph_steps && el == hipSuccess;) {
+            int sw = 0, did = 1;
+            el = advance<S>(c, c->graph_steps - k, &did, &sw);
             swaps += sw;
+            k += did;
         }
         c->stream = user;
         c->own_capture = false;
@@ -638,7 +638,7 @@ lbm_status lbm_set_step_fusion(lbm_ctx* c, int mode) {
                        "many-steps kernel needs at most 16 tiles of 512 nodes over all replicas");
     if (mode == 2 && c->desc.lattice == LBM_D2Q9_PHASE && c->desc.prec == LBM_FP32_DEV_ARITH64)
         return set_err(c, LBM_E_UNSUPPORTED, "two-step kernel: not with FP64 arithmetic on FP32 storage");
-    if (mode == 2 && c->desc.lattice == LBM_D2Q9_D2Q5 && c->has_params && !chan_tb2_fits(c->ck))
+    if (mode == 2 && c->desc.lattice == LBM_D2Q9_D2Q5 && c->has_params && !chan_march_fits(c->ck))
         return set_err(c, LBM_E_UNSUPPORTED,
                        "two-step channel kernel: needs both flow and temperature");
     if (mode != c->fusion) {
@@ -873,12 +873,16 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
                                            : phase_multi_plan<float>(pk, d.prec == LBM_FP32_DEV_ARITH64);
         c->pmulti_made = true;
     }
-    if (d.lattice == LBM_D2Q9_D2Q5 && chan_tb2_fits(ck)) {
+    if (d.lattice == LBM_D2Q9_D2Q5 && !c->cplans_made) {  // depend on the grid and its boundaries only
         DeviceGuard g(c->device);
-        c->tb2_seg = d.prec == LBM_FP64 ? chan_tb2_seg<double>(ck) : chan_tb2_seg<float>(ck);
-        if (!c->cmulti_made)  // depends on the grid and its boundaries only
-            c->cmulti = d.prec == LBM_FP64 ? chan_multi_plan<double>(ck) : chan_multi_plan<float>(ck);
-        c->cmulti_made = true;
+        const bool f64 = d.prec == LBM_FP64;
+        c->cmulti = f64 ? chan_multi_plan<double>(ck) : chan_multi_plan<float>(ck);
+        c->cmarch = f64 ? chan_march_plan<double>(ck) : chan_march_plan<float>(ck);
+        const double single = chan_single_cost(2.0 * c->N * ck.npl * (f64 ? 8 : 4));
+        // the marching model is up to 15 % optimistic
+        c->cmarch.fast = c->cmarch.steps > 0 &&
+                         1.1 * c->cmarch.cost < (c->cmulti.steps > 0 ? c->cmulti.cost : 0.95 * single);
+        c->cplans_made = true;
     }
     if (d.lattice == LBM_D3Q19_PHASE) {
         DeviceGuard g(c->device);
@@ -1063,7 +1067,7 @@ lbm_status step_run(lbm_ctx* c, int n) {
     }
     const bool f64 = c->desc.prec == LBM_FP64;
     if (n > 0 && use_persist(c)) return f64 ? step_persist<double>(c, n) : step_persist<float>(c, n);
-    if (n > 1 && use_chan_multi(c)) {
+    if (n > 1 && !use_march(c) && use_chan_multi(c)) {
         hipError_t e = f64 ? step_chan_multi<double>(c, n) : step_chan_multi<float>(c, n);
         return e == hipSuccess ? LBM_OK : hip_fail(c, e, "step kernel");
     }
@@ -1080,9 +1084,8 @@ lbm_status step_run(lbm_ctx* c, int n) {
         }
     }
     while (s < n) {
-        const int m = n - s >= 2 ? 2 : 1;
-        int sw = 0;
-        hipError_t e = f64 ? advance<double>(c, m, &sw) : advance<float>(c, m, &sw);
+        int sw = 0, m = 1;
+        hipError_t e = f64 ? advance<double>(c, n - s, &m, &sw) : advance<float>(c, n - s, &m, &sw);
         if (e != hipSuccess) return hip_fail(c, e, "step kernel");
         s += m;
     }

@@ -250,15 +250,14 @@ auto cm_kernel(int qt, int threads) {
 // least 1) and rounds the number of times the workgroups fill the GPU.  T0 is
 // the launch gap with the load and the store, b the issue time of one wave's
 // step.  More steps per launch share T0 but widen the overlap, so W grows.
-// Against the single-step kernel, 4.6 us plus its bytes at 5.6 TB/s
-// (measured: 5.2 us on 800 x 40, 22.2 us on 3000 x 300 FP32), a plan is taken
-// where it saves at least 15 %.  Measured per step, single -> plan: 800 x 40
+// A plan is taken where it saves at least 15 % of the single step
+// (chan_single_cost).  Measured per step, single -> plan: 800 x 40
 // FP32 5.2 -> 1.7 us, 1600 x 80 6.5 -> 2.6, 2000 x 50 with the D2Q9 thermal
 // set 8.0 -> 3.1, 65 x 65 cavity FP64 5.6 -> 2.7, 3000 x 300 22.2 -> 13.8.
 template <typename S>
 ChanMultiPlan chan_multi_plan(const ChanK& k) {
     ChanMultiPlan best{};
-    if (!chan_tb2_fits(k)) return best;
+    if (!chan_march_fits(k)) return best;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
@@ -271,7 +270,7 @@ ChanMultiPlan chan_multi_plan(const ChanK& k) {
     for (int wv = 1; wv <= kWaves; ++wv)
         resident[wv] = resident_workgroups((const void*)cm_kernel<S>(k.tq, wv * 64), wv);
     const double bytes = double(k.nx) * k.ny * k.batch * k.npl * sizeof(S) * 2;
-    double best_cost = 0.85 * (4.6 + bytes / 5.6e6);
+    double best_cost = 0.85 * chan_single_cost(bytes);
     for (int h = 2; h <= 10; ++h)
         for (int nty = 1; nty <= std::min(k.ny, 512); ++nty) {
             // one plan per height of the widest tile: the fewest tiles of it
@@ -298,7 +297,7 @@ ChanMultiPlan chan_multi_plan(const ChanK& k) {
                                      (rem ? std::max<double>(1.0, double(((rem + cus - 1) / cus * wv + 3) / 4)) : 0.0);
                 const double cost = (c.t0 + c.t1 * (rounds - 1) + h * (c.a * rounds + c.b * waves)) / h;
                 if (cost < best_cost) {
-                    best_cost = cost;
+                    best_cost = best.cost = cost;
                     best.steps = h;
                     best.ntx = ntx;
                     best.nty = nty;

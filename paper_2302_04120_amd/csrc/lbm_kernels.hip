@@ -161,346 +161,6 @@ __global__ __launch_bounds__(64) void k_chan_step(ChanK k, const S* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Two channel steps per launch (temporal blocking) for flow with temperature
-// (QT: the D2Q5 or D2Q9 thermal set; Boussinesq force optional), x periodic,
-// inlet/outlet or fixed-temperature end walls and y periodic, walls, or a wall
-// below and the symmetry plane above.  A workgroup of 256 lanes takes one x-tile of one
-// row segment [a, e) of one replica: lane l holds column c = 252 t - 2 + l
-// (modulo nx for periodic x; with x ends, lanes whose column lies outside
-// [0, nx) read a clamped column and their results are never used).  At row v
-// it collides step n at row v and step n + 1 at row v - 1:
-//   - step n hands its x-moving post-collision values (and u, for the
-//     outlet's wall velocity) to the neighbour lanes through LDS and
-//     accumulates them into the step-(n + 1) state of rows v - 1, v and
-//     v + 1, which stays in registers; row v - 1 is complete once row v has
-//     collided;
-//   - step n + 1 at row v - 1 pushes straight to memory with the streaming
-//     and boundary rules of k_chan_step; its u reaches the next lane through
-//     LDS for the outlet (a second barrier, inlet/outlet channels only).
-// Step n is exact on every lane, the step-(n + 1) state on lanes 1..254 and
-// the step-(n + 1) outlet velocity on lanes 2..254: lanes 2..253 store, so
-// neighbouring tiles store disjoint columns.  Step n runs on rows a - 1 .. e
-// (those that exist), step n + 1 on the segment's own rows, and every slot
-// of the new state is written by its source node only.  Per node the
-// arithmetic is that of k_chan_step (chan_th, chan_collide and the boundary
-// values), so two steps here equal two single steps bit for bit.  mod0 and
-// mod1 are the wall-flux modulations at t and t + dt.
-// ALIGNED: nx a multiple of 64 and a row's node blocks under 2 GiB, so every
-// row starts on a node block and an access is the row's block base (uniform)
-// plus a 32-bit lane offset.  ENDS: the code for the cavity's end walls and
-// the symmetry plane is compiled in (kept out of the other configurations:
-// with it the 16384 x 2048 channel step took 0.462 ms instead of 0.419).
-// ---------------------------------------------------------------------------
-constexpr int kCtLanes = 256;
-constexpr int kCtHalo = 2;                      // overlap columns per side
-constexpr int kCtOut = kCtLanes - 2 * kCtHalo;  // stored columns per tile
-// values per node (f 0-8, g from 9) and LDS exchange rows of step n (6 flow
-// x movers, the thermal x movers 1 and 3, u, then the thermal diagonals 5-8)
-constexpr int ct_nv(int qt) { return 9 + qt; }
-constexpr int ct_x(int qt) { return qt == 9 ? 14 : 10; }
-
-template <typename S, bool ALIGNED, bool ENDS, int QT>
-__global__ __launch_bounds__(kCtLanes) void k_chan_tb2(ChanK k, const S* __restrict__ A,
-                                                      S* __restrict__ B, const S* __restrict__ qw,
-                                                      const S* __restrict__ uin,
-                                                      const S* __restrict__ tin, S mod0, S mod1,
-                                                      int seg) {
-    using C = S;
-    constexpr int NV = ct_nv(QT), G = 9, NX = ct_x(QT);
-    const int nx = k.nx, ny = k.ny;
-    const int nseg = (ny + seg - 1) / seg;
-    const int ntx = (nx + kCtOut - 1) / kCtOut;
-    int w;
-    if (!xcd_tile(ntx * nseg * k.batch, w)) return;  // whole workgroup, before any barrier
-    const int tx = w % ntx;  // x fastest
-    w /= ntx;
-    const int b = w / nseg;
-    const int a = (w - b * nseg) * seg;
-    const int e = min(a + seg, ny);
-    const bool walls = k.bcy != 0;  // y ends: a wall at y-, a wall or the symmetry plane at y+
-    const bool symy = ENDS && k.bcy == 2;  // the symmetry plane of Eq. simetria at y+
-    const bool xends = k.bcx != 0;  // x not periodic: the channel has a left and a right end
-    const bool io = ENDS ? k.bcx == 1 : xends;  // velocity inlet (left), pressure outlet (right)
-    const bool xw = ENDS && k.bcx == 2;  // fixed-temperature no-slip walls at both ends
-    const int s1 = walls ? max(a - 1, 0) : a - 1;   // first row of step n
-    const int e1 = walls ? min(e + 1, ny) : e + 1;  // end of the step-n rows
-    const long long base = (long long)b * ny * nx;
-    const unsigned lx = threadIdx.x;
-    const int col = tx * kCtOut - kCtHalo + int(lx);
-    const unsigned x = unsigned(xends ? min(max(col, 0), nx - 1) : ((col % nx) + nx) % nx);
-    const bool own = int(lx) >= kCtHalo && int(lx) < kCtLanes - kCtHalo && col < nx;
-    const bool x_lo = xends && col == 0, x_hi = xends && col == nx - 1;  // the end columns
-    const bool at_in = io && x_lo, at_out = io && x_hi;
-    const unsigned xm = x == 0 ? nx - 1 : x - 1;
-    const unsigned xp = x == unsigned(nx - 1) ? 0u : x + 1;
-    const unsigned lxm = lx == 0 ? 0u : lx - 1;
-    const unsigned lxp = lx == kCtLanes - 1 ? lx : lx + 1;
-    const C rho_ref = C(k.rho_ref), qdt = C(k.qdt);
-    const C q = C(qw[x]);
-    const C tw_lo = C(k.Tw[0]), tw_hi = C(k.Tw[1]);
-
-    __shared__ C xch[2][NX][kCtLanes];  // step n: x movers and u, rows v mod 2
-    __shared__ C un1[2][2][kCtLanes];     // step n + 1: u, rows v mod 2
-
-    // memory row of virtual row v: step-n rows of a periodic segment lie in
-    // [-1, ny], so one correction wraps them
-    auto rowof = [&](int v) { return v < 0 ? v + ny : (v >= ny ? v - ny : v); };
-    // value i of the node in column slot c (0: x, 1: x - 1, 2: x + 1) of row v
-    const unsigned xcol[3] = {x, xm, xp};
-    unsigned boff[3];  // ALIGNED: byte offset of value 0 of those columns within a row
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-        boff[c] = unsigned(((xcol[c] >> 6) * NV * kBlk + (xcol[c] & (kBlk - 1))) * sizeof(S));
-    auto at = [&](auto* P, int v, int c, int i) {
-        const long long ro = base + (long long)rowof(v) * nx;
-        if constexpr (ALIGNED) {
-            using B8 = std::conditional_t<std::is_const_v<std::remove_pointer_t<decltype(P)>>,
-                                          const char, char>;
-            auto* row = (B8*)P + (ro >> 6) * (long long)(NV * kBlk * sizeof(S));
-            return (decltype(P))(row + boff[c]) + i * kBlk;
-        } else {
-            return P + bidx(NV, i, ro + xcol[c]);
-        }
-    };
-    auto load_row = [&](int v, C (&s)[NV]) {
-#pragma unroll
-        for (int i = 0; i < NV; ++i) s[i] = C(*at(A, v, 0, i));
-    };
-    // macros and both collisions of one node, as in k_chan_step
-    auto collide = [&](const C (&s)[NV], C& ux, C& uy, C (&ds)[9], C (&es)[QT]) {
-        C d[9], g[QT], drho, rho, ftx, fty;
-#pragma unroll
-        for (int i = 0; i < 9; ++i) d[i] = s[i];
-#pragma unroll
-        for (int i = 0; i < QT; ++i) g[i] = s[G + i];
-        const C th = chan_th<QT, C>(g, qdt);
-        chan_force(k, th, ftx, fty);
-        chan_flow_macros_v<C>(d, rho_ref, ftx, fty, drho, rho, ux, uy);
-        chan_collide<C, QT, ChanK>(k, d, drho, rho, ux, uy, ftx, fty, g, th, qdt, ds, es);
-    };
-
-    // Register slots: slot (u - s1) mod 3 holds the accumulated step-(n + 1)
-    // state of row u (rows v - 1 .. v + 1 are live).  The row loop is
-    // unrolled three times, so every slot index is a compile-time constant.
-    // The stored state of row v is read at the start of its own row step:
-    // reading it a row ahead (in registers) took 6 % longer.
-    C Ld[NV], Ac[3][NV];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int i = 0; i < NV; ++i) Ac[j][i] = C(0);
-
-    auto row_step = [&](int v, auto Jc) {
-        constexpr int J = decltype(Jc)::value;
-        constexpr int s0 = J, sn = (J + 1) % 3, sm1 = (J + 2) % 3;  // rows v, v + 1, v - 1
-        const bool do_n = v < e1;
-        // unconditional (the last row step re-reads an existing row)
-        load_row(do_n ? v : e1 - 1, Ld);
-        C(&xb)[NX][kCtLanes] = xch[v & 1];
-        // ---- step n at row v
-        C ds[9], es[QT], ux = C(0), uy = C(0);
-        if (do_n) {
-            collide(Ld, ux, uy, ds, es);
-            xb[0][lx] = ds[1];
-            xb[1][lx] = ds[3];
-            xb[2][lx] = ds[5];
-            xb[3][lx] = ds[6];
-            xb[4][lx] = ds[7];
-            xb[5][lx] = ds[8];
-            xb[6][lx] = es[1];
-            xb[7][lx] = es[3];
-            if constexpr (QT == 9) {
-                xb[10][lx] = es[5];
-                xb[11][lx] = es[6];
-                xb[12][lx] = es[7];
-                xb[13][lx] = es[8];
-            }
-            xb[8][lx] = ux;
-            xb[9][lx] = uy;
-        }
-        __syncthreads();  // the other buffer's reads ended a row ago
-        if (do_n) {
-            // pushes of row v: rest and x movers to row v, +y movers to row
-            // v + 1, -y movers to row v - 1 (x movers from the lanes x -+ 1)
-            C(&A0)[NV] = Ac[s0];
-            C(&Ap)[NV] = Ac[sn];
-            C(&A1)[NV] = Ac[sm1];
-            const bool top = k.bcy == 1 && v == ny - 1, bottom = walls && v == 0;
-            const bool stop = symy && v == ny - 1;  // top row under the symmetry plane
-            C uwx = C(0), uwy = C(0), u_in = C(0), t_in = C(0);
-            if (io) {
-                const int y = rowof(v);
-                u_in = C(uin[y]);
-                t_in = C(0.5) * (C(tin[y]) + C(tin[y]));  // the inlet link stays in row y
-                uwx = C(1.5) * ux - C(0.5) * xb[8][lxm];
-                uwy = C(1.5) * uy - C(0.5) * xb[9][lxm];
-            }
-            // an end wall (xw) bounces back like the y walls (u_w = 0)
-            A0[0] = ds[0];
-            A0[1] = x_lo ? (io ? chan_inlet_f<C>(3, ds[3], rho_ref, u_in) : ds[3]) : xb[0][lxm];
-            A0[3] = x_hi ? (io ? chan_outlet_f<C>(1, ds[1], rho_ref, uwx, uwy) : ds[1])
-                         : xb[1][lxp];
-            // the -y slots take the top wall's values; below the top row the
-            // next row's pushes overwrite them (not the inlet's and outlet's
-            // own values)
-            A0[4] = ds[2];
-            A0[7] = at_out && !top ? chan_outlet_f<C>(5, ds[5], rho_ref, uwx, uwy) : ds[5];
-            A0[8] = at_in && !top ? chan_inlet_f<C>(6, ds[6], rho_ref, u_in) : ds[6];
-            // under the symmetry plane the +y movers come back mirrored at
-            // x + c_x (Eq. simetria), from the neighbour lanes
-            A0[7] = stop && !x_hi ? xb[3][lxp] : A0[7];
-            A0[8] = stop && !x_lo ? xb[2][lxm] : A0[8];
-            // the +y slots hold the row below's pushes, except at the bottom
-            // wall and where the source lies beyond an x end
-            A0[2] = bottom ? ds[4] : A0[2];
-            A0[5] = bottom ? ds[7]
-                           : (x_lo ? (io ? chan_inlet_f<C>(7, ds[7], rho_ref, u_in) : ds[7])
-                                   : A0[5]);
-            A0[6] = bottom ? ds[8]
-                           : (x_hi ? (io ? chan_outlet_f<C>(8, ds[8], rho_ref, uwx, uwy) : ds[8])
-                                   : A0[6]);
-            Ap[2] = ds[2];
-            Ap[5] = xb[2][lxm];
-            Ap[6] = xb[3][lxp];
-            A1[4] = ds[4];
-            A1[7] = x_hi ? A1[7] : xb[4][lxp];
-            A1[8] = x_lo ? A1[8] : xb[5][lxm];
-            // temperature: Dirichlet inlet or end walls (anti-bounce-back),
-            // outlet extrapolation (the value its left neighbour receives:
-            // the outlet node's own), flux walls
-            if constexpr (QT == 5) {
-                A0[G + 0] = es[0];
-                A0[G + 1] = x_lo ? chan_antibb_g<QT, C>(3, es[3], io ? t_in : tw_lo) : xb[6][lxm];
-                A0[G + 3] = x_hi ? (io ? es[3] : chan_antibb_g<QT, C>(1, es[1], tw_hi)) : xb[7][lxp];
-                A0[G + 4] = stop ? es[2] : chan_flux_g<QT, C>(2, es[2], q, mod0);
-                A0[G + 2] = bottom ? chan_flux_g<QT, C>(4, es[4], q, mod0) : A0[G + 2];
-                Ap[G + 2] = es[2];
-                A1[G + 4] = es[4];
-            } else {
-                // D2Q9 thermal set: the diagonals follow the flow's pattern.
-                // Inlet temperature where a link crosses the inlet: the mean
-                // of its two rows (the row's own value if the other is beyond
-                // the channel).
-                C tw6 = C(0), tw7 = C(0);
-                if (io) {
-                    const int y = rowof(v);
-                    tw6 = y + 1 < ny ? C(0.5) * (C(tin[y]) + C(tin[y + 1])) : C(tin[y]);
-                    tw7 = y - 1 >= 0 ? C(0.5) * (C(tin[y]) + C(tin[y - 1])) : C(tin[y]);
-                }
-                const C l8 = chan_antibb_g<QT, C>(6, es[6], io ? tw6 : tw_lo);
-                const C l5 = chan_antibb_g<QT, C>(7, es[7], io ? tw7 : tw_lo);
-                A0[G + 0] = es[0];
-                A0[G + 1] = x_lo ? chan_antibb_g<QT, C>(3, es[3], io ? t_in : tw_lo) : xb[6][lxm];
-                A0[G + 3] = x_hi ? (io ? es[3] : chan_antibb_g<QT, C>(1, es[1], tw_hi)) : xb[7][lxp];
-                // -y slots: top wall flux, mirrored movers under the symmetry
-                // plane, else provisional (the row above overwrites them, but
-                // not the end columns' own values)
-                A0[G + 4] = stop ? es[2] : chan_flux_g<QT, C>(2, es[2], q, mod0);
-                A0[G + 7] = top ? chan_flux_g<QT, C>(5, es[5], q, mod0)
-                          : x_hi ? (io ? es[6] : chan_antibb_g<QT, C>(5, es[5], tw_hi))
-                                 : xb[11][lxp];
-                A0[G + 8] = top ? chan_flux_g<QT, C>(6, es[6], q, mod0) : x_lo ? l8 : xb[10][lxm];
-                // +y slots: bottom wall flux, the end columns' own values
-                A0[G + 2] = bottom ? chan_flux_g<QT, C>(4, es[4], q, mod0) : A0[G + 2];
-                A0[G + 5] = bottom ? chan_flux_g<QT, C>(7, es[7], q, mod0) : x_lo ? l5 : A0[G + 5];
-                A0[G + 6] = bottom ? chan_flux_g<QT, C>(8, es[8], q, mod0)
-                          : (x_hi && xw) ? chan_antibb_g<QT, C>(8, es[8], tw_hi) : A0[G + 6];
-                Ap[G + 2] = es[2];
-                Ap[G + 5] = xb[10][lxm];
-                Ap[G + 6] = at_out ? es[6] : xb[11][lxp];
-                A1[G + 4] = es[4];
-                A1[G + 7] = (x_hi && xw) ? A1[G + 7] : at_out ? es[7] : xb[12][lxp];
-                A1[G + 8] = x_lo ? A1[G + 8] : xb[13][lxm];
-            }
-        }
-        // ---- step n + 1 at row r = v - 1, complete now, straight to memory
-        const int r = v - 1;
-        const bool do_n1 = r >= a && r < e;
-        C ds1[9], es1[QT], ux1 = C(0), uy1 = C(0);
-        if (do_n1) {
-            collide(Ac[sm1], ux1, uy1, ds1, es1);
-            if (io) {
-                un1[v & 1][0][lx] = ux1;
-                un1[v & 1][1][lx] = uy1;
-            }
-        }
-        if (io) __syncthreads();
-        if (do_n1 && own) {
-            C uwx = C(0), uwy = C(0), u_in = C(0), t_in = C(0);
-            if (io) {
-                u_in = C(uin[r]);
-                t_in = C(0.5) * (C(tin[r]) + C(tin[r]));
-                uwx = C(1.5) * ux1 - C(0.5) * un1[v & 1][0][lxm];
-                uwy = C(1.5) * uy1 - C(0.5) * un1[v & 1][1][lxm];
-            }
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                const int ty = r + EY[i];
-                // under the symmetry plane a +y mover comes back mirrored into the
-                // top row (a separate branch keeps every value index a constant)
-                const bool sym = symy && ty >= ny;
-                const bool outy = walls && !sym && (ty < 0 || ty >= ny);
-                const bool outx = (EX[i] < 0 && x_lo) || (EX[i] > 0 && x_hi);
-                if (sym && !outx) {
-                    st(at(B, r, EX[i] == 0 ? 0 : (EX[i] > 0 ? 2 : 1), MIRY[i]), S(ds1[i]));
-                } else if (!outy && !outx) {
-                    st(at(B, ty, EX[i] == 0 ? 0 : (EX[i] > 0 ? 2 : 1), i), S(ds1[i]));
-                } else {
-                    C val;
-                    if (outy || xw)
-                        val = ds1[i];
-                    else if (EX[i] < 0)
-                        val = chan_inlet_f<C>(i, ds1[i], rho_ref, u_in);
-                    else
-                        val = chan_outlet_f<C>(i, ds1[i], rho_ref, uwx, uwy);
-                    st(at(B, r, 0, OPP[i]), S(val));
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < QT; ++i) {
-                const int cx = tex<QT>(i), cy = tey<QT>(i);
-                const int ty = r + cy;
-                const bool sym = symy && ty >= ny;
-                const bool outy = walls && !sym && (ty < 0 || ty >= ny);
-                const bool outx = (cx < 0 && x_lo) || (cx > 0 && x_hi);
-                const int col = cx == 0 ? 0 : (cx > 0 ? 2 : 1);
-                // outlet extrapolation: what column nx - 2 receives in a slot
-                // with c_x < 0 (never a slot a wall rule owns here: its
-                // source is this row or, mirrored, the row itself)
-                if (sym && !outx) {
-                    st(at(B, r, col, G + tmir<QT>(i)), S(es1[i]));
-                    if (tex<QT>(tmir<QT>(i)) < 0 && at_out) st(at(B, r, 0, G + tmir<QT>(i)), S(es1[i]));
-                } else if (!outy && !outx) {
-                    st(at(B, ty, col, G + i), S(es1[i]));
-                    if (cx < 0 && at_out) st(at(B, ty, 0, G + i), S(es1[i]));
-                } else if (outy) {
-                    st(at(B, r, 0, G + topp<QT>(i)), S(chan_flux_g<QT, C>(i, es1[i], q, mod1)));
-                } else if (xw) {
-                    st(at(B, r, 0, G + topp<QT>(i)),
-                       S(chan_antibb_g<QT, C>(i, es1[i], cx < 0 ? tw_lo : tw_hi)));
-                } else if (cx < 0) {
-                    // the inlet temperature where the link crosses the inlet
-                    const int y2 = r + cy;
-                    const C tw = cy == 0 ? t_in
-                               : (y2 >= 0 && y2 < ny) ? C(0.5) * (C(tin[r]) + C(tin[y2]))
-                                                      : C(tin[r]);
-                    st(at(B, r, 0, G + topp<QT>(i)), S(chan_antibb_g<QT, C>(i, es1[i], tw)));
-                }
-                // the outlet's own +x movers leave; their slots are extrapolated
-            }
-        }
-    };
-    const int vend = e + 1;
-    for (int v = s1; v < vend; v += 3) {
-        row_step(v, std::integral_constant<int, 0>{});
-        if (v + 1 >= vend) break;
-        row_step(v + 1, std::integral_constant<int, 1>{});
-        if (v + 2 >= vend) break;
-        row_step(v + 2, std::integral_constant<int, 2>{});
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Two-phase model: conservative Allen-Cahn h_i (BGK) + pressure z_i (MRT/BGK)
 // State planes (node-block layout, PhasePlanes): 0-8 h_i, 9-17 z_i, then
 // (FP32 storage only) the low part of h_0, then (phi u) of the previous step
@@ -1448,89 +1108,6 @@ hipError_t launch_chan_step(const ChanK& k, const S* a, S* b, const S* qw, const
     return hipGetLastError();
 }
 
-// The two-step channel kernel covers flow with temperature (D2Q5 or the D2Q9
-// set, with or without the Boussinesq force), every x and y boundary of the
-// channel lattice, and at least two columns and rows.
-bool chan_tb2_fits(const ChanK& k) {
-    return k.flow && k.thermal && (k.tq == 5 || k.tq == 9) && k.npl == ct_nv(k.tq) &&
-           k.bcx >= 0 && k.bcx <= 2 && k.bcy >= 0 && k.bcy <= 2 && k.nx >= 2 && k.ny >= 2;
-}
-int chan_tb2_ntx(const ChanK& k) { return (k.nx + kCtOut - 1) / kCtOut; }
-// Share of the launched lanes whose columns are stored.
-double chan_tb2_lane_use(const ChanK& k) {
-    return double(k.nx) / (double(chan_tb2_ntx(k)) * kCtLanes);
-}
-template <typename S>
-bool chan_tb2_aligned(const ChanK& k) {
-    return k.nx % kBlk == 0 && (long long)k.nx * ct_nv(k.tq) * (long long)sizeof(S) < (1LL << 31);
-}
-long long chan_tb2_workgroups(const ChanK& k, int seg) {
-    return (long long)((k.ny + seg - 1) / seg) * k.batch * chan_tb2_ntx(k);
-}
-
-// Rows per segment, by the launch-round model of the two-phase kernel: a
-// workgroup marches seg + 2 rows (its segment, one row of overlap below and
-// one of lag above), the GPU holds `slots` workgroups at once, and the
-// segment length (at least 32 rows, or the whole replica) minimises
-// ceil(workgroups / slots) (seg + 2).  On the 16384 x 2048 channel (66
-// x-tiles, three workgroups per CU) it picks 90 rows, the fastest of 32 to
-// 512 rows in a sweep (0.420 ms per step; 187 rows 0.427, 64 rows 0.434,
-// 128 rows 0.541, 256 rows 0.525).
-// The instance of the two-step channel kernel for a configuration.
-template <typename S>
-auto chan_tb2_kernel(const ChanK& k) {
-    const bool ends = k.bcx == 2 || k.bcy == 2;
-    if (k.tq == 9) {
-        if (chan_tb2_aligned<S>(k))
-            return ends ? k_chan_tb2<S, true, true, 9> : k_chan_tb2<S, true, false, 9>;
-        return ends ? k_chan_tb2<S, false, true, 9> : k_chan_tb2<S, false, false, 9>;
-    }
-    if (chan_tb2_aligned<S>(k))
-        return ends ? k_chan_tb2<S, true, true, 5> : k_chan_tb2<S, true, false, 5>;
-    return ends ? k_chan_tb2<S, false, true, 5> : k_chan_tb2<S, false, false, 5>;
-}
-
-template <typename S>
-int chan_tb2_seg(const ChanK& k) {
-    const int ny = k.ny;
-    int dev = 0, cus = 0, per_cu = 0;
-    long long slots = 1024;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, chan_tb2_kernel<S>(k), kCtLanes, 0) ==
-            hipSuccess &&
-        cus > 0 && per_cu > 0)
-        slots = (long long)cus * per_cu;
-    const long long units = (long long)k.batch * chan_tb2_ntx(k);
-    const int lo = ny < 32 ? ny : 32;
-    int best = ny;
-    long long best_cost = -1;
-    for (int seg = ny; seg >= lo; --seg) {
-        const long long nseg = (ny + seg - 1) / seg;
-        if (seg < ny && seg - 1 >= lo && (ny + seg - 2) / (seg - 1) == nseg)
-            continue;  // a shorter segment gives the same count: take the shortest of them
-        const long long rounds = (units * nseg + slots - 1) / slots;
-        const long long cost = rounds * (seg + 2);
-        if (best_cost < 0 || cost < best_cost) {
-            best_cost = cost;
-            best = seg;
-        }
-    }
-    return best;
-}
-
-template <typename S>
-hipError_t launch_chan_tb2(const ChanK& k, const S* a, S* b, const S* qw, const S* uin,
-                           const S* tin, double mod0, double mod1, int seg, hipStream_t s) {
-    if (!chan_tb2_fits(k) || seg < 1) return hipErrorInvalidValue;
-    const long long wgs = chan_tb2_workgroups(k, seg);
-    if ((wgs + kXCD - 1) / kXCD * kXCD > 0x7fffffffLL) return hipErrorInvalidValue;
-    dim3 grd(unsigned((wgs + kXCD - 1) / kXCD * kXCD)), blk(kCtLanes);
-    hipLaunchKernelGGL(chan_tb2_kernel<S>(k), grd, blk, 0, s, k, a, b, qw, uin, tin, S(mod0),
-                       S(mod1), seg);
-    return hipGetLastError();
-}
-
 // FP32 steps run on 256-node tiles, four resident per CU (kPhaseLdsReserve).
 // Measured against 512-node tiles (two per CU): equal on 1024 replicas of
 // 256^2, faster on smaller grids (64 replicas 146 -> 141 us per step, C4's
@@ -1832,9 +1409,6 @@ hipError_t launch_nusselt(const ChanK& k, const S* a, const S* qw, double qsi, d
                                             const S*, double, hipStream_t);                       \
     template hipError_t launch_phase_step<S>(const PhaseK&, const S*, S*, bool, hipStream_t);    \
     template hipError_t launch_phase_tb2<S>(const PhaseK&, const S*, S*, int, hipStream_t);      \
-    template hipError_t launch_chan_tb2<S>(const ChanK&, const S*, S*, const S*, const S*,      \
-                                           const S*, double, double, int, hipStream_t);           \
-    template int chan_tb2_seg<S>(const ChanK&);                                                  \
     template int phase_tb2_seg<S>(const PhaseK&);                                                \
     template hipError_t launch_phase_persist<S>(const PhaseK&, S*, S*, int, unsigned, unsigned*,  \
                                                 unsigned*, bool, hipStream_t);                    \
