@@ -5,8 +5,8 @@ conservative Allen-Cahn populations, 256 x 256 periodic cell, liquid/gas
 density ratio ~43 300, viscosity ratio ~470, radii cycling over 20/30/40/50
 nodes with seeded centre jitter) run as a batch of independent replicas, FP32
 deviation storage.  One step = one stream-collide update of every node of
-every replica; by default the library's two-step kernel performs two steps
-per launch (--fusion 1 times the single-step kernel instead).  Inputs are
+every replica; by default the library's marching kernel performs three steps
+per launch (two in FP64; --fusion 1 times the single-step kernel instead).  Inputs are
 synthetic and resident in HBM before timing starts.
 
 Prints ONE JSON line (see the keys below).  ``--gpus`` above 1 is refused:
@@ -39,7 +39,19 @@ P3_BYTES_PER_LU = {"fp32": (19 + 1 + 19 + 3) * 4 * 2, "fp64": (19 + 19 + 3) * 8 
 # buffer layout it streams through
 KERNEL_SOURCES = ("paper_2302_04120_amd/csrc/lbm_kernels.hip", "paper_2302_04120_amd/csrc/lbm_device.h",
                   "paper_2302_04120_amd/csrc/lbm_internal.h", "paper_2302_04120_amd/csrc/build.py",
-                  "paper_2302_04120_amd/csrc/lbm_api.hip")
+                  "paper_2302_04120_amd/csrc/lbm_api.hip", "paper_2302_04120_amd/csrc/lbm_phase.h",
+                  "paper_2302_04120_amd/csrc/lbm_phase_march.hip")
+
+
+def phase_steps_per_launch(prec, fusion):
+    """Steps per launch of the library's choice on grids that fill the GPU."""
+    return 1 if fusion == 1 or prec == "fp32_arith64" else 3 if prec == "fp32" else 2
+
+
+def phase_march_name(prec, whole, aligned, spl):
+    return "k_phase_march<%s, %s, %s, %d>" % ("float" if prec == "fp32" else "double",
+                                              "true" if whole else "false",
+                                              "true" if aligned else "false", spl)
 
 
 def kernel_source_hash():
@@ -137,8 +149,8 @@ def run_gpu(batch, steps, warmup, prec, n=256, fusion=0, windows=0):
 def run_wide(cells, steps, warmup, prec, fusion=0):
     """One periodic domain of cells x cells bubble cells (256^2 each, radii
     cycling, jitter per cell): 32 x 32 gives the 8192^2 bubble array.  Its
-    rows are wider than 256 nodes, so the two-step kernel takes them in
-    x-tiles of 250 stored columns."""
+    rows are wider than 256 nodes, so the marching kernel takes them in
+    x-tiles."""
     import torch
     from paper_2302_04120_amd import lbm, workloads as WL
     prm, ini, _ = WL.bubble_array(cells, 256, seed=0)
@@ -155,14 +167,12 @@ def run_wide(cells, steps, warmup, prec, fusion=0):
         raise RuntimeError("non-finite populations after the timed steps")
     L.close()
     nodes = n * n
-    spl = 2 if fusion != 1 else 1
-    launch_ms = ms / steps * spl
+    spl = phase_steps_per_launch(prec, fusion)
+    launch_ms = ms / -(-steps // spl)
     return dict(mlups=nodes * steps / (ms * 1e-3) / 1e6, grid="%dx%d" % (n, n),
                 ms_per_step=ms / steps, launch_ms=launch_ms,
                 hbm_frac=BYTES_PER_LU[prec] * nodes / (launch_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                kernel="k_phase_tb2<%s, true, %s>" % ("float" if prec == "fp32" else "double",
-                                                      "true" if n % 64 == 0 else "false")
-                if spl == 2 else "k_phase")
+                kernel=phase_march_name(prec, False, n % 64 == 0, spl) if spl > 1 else "k_phase")
 
 
 def run_channel(nx, ny, steps, warmup, prec, fusion=1):
@@ -476,7 +486,7 @@ def cpu_baseline(seconds=8.0):
 
 def parity_vs_oracle(prm, ini, mo_long, steps_long, steps_short=20):
     """The GPU path on the oracle's sample (replica 0 of the bench workload;
-    FP32 deviation storage with the bench's two-step kernel, and FP64).
+    FP32 deviation storage with the bench's marching kernel, and FP64).
     Pointwise after a short horizon: max |GPU - oracle| per field relative to
     the field's scale (1 for phi; max |p| or sigma / W for p; max |u| for u).
     After the CPU sample's long horizon, where the model amplifies rounding
@@ -572,7 +582,7 @@ def main():
     ap.add_argument("--batch", type=int, default=1024, help="256x256 replicas per step")
     ap.add_argument("--prec", default="fp32", choices=("fp32", "fp64", "fp32_arith64"))
     ap.add_argument("--fusion", type=int, default=2, choices=(0, 1, 2),
-                    help="2 two-step kernel (default), 1 single-step, 0 library's choice (the "
+                    help="2 marching kernel (default), 1 single-step, 0 library's choice (the "
                          "two-phase workloads and --leg channel)")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-extras", action="store_true", help="skip the FP64 and batch-4 legs")
@@ -634,7 +644,7 @@ def main():
               file=sys.stderr)
         return 2
     if args.steps % 2 and args.fusion == 2:
-        print("--steps must be even with the two-step kernel", file=sys.stderr)
+        print("--steps must be even with several steps per launch", file=sys.stderr)
         return 2
     log("bench: phase workload batch=%d steps=%d warmup=%d prec=%s fusion=%d" %
         (args.batch, args.steps, args.warmup, args.prec, args.fusion))
@@ -642,21 +652,21 @@ def main():
                 windows=0 if args.no_extras else 5)
     mlups = r["nodes"] * args.steps / r["wall"] / 1e6
     bpl = BYTES_PER_LU[args.prec]
-    spl = 2 if args.fusion == 2 else 1  # steps per launch
-    kname = ("k_phase_tb2<%s, false, true>" % ("float" if args.prec == "fp32" else "double")
-             if spl == 2 else
+    spl = phase_steps_per_launch(args.prec, args.fusion) if args.fusion == 2 else 1
+    kname = (phase_march_name(args.prec, True, True, spl) if spl > 1 else
              "k_phase<%s>" % {"fp32": "float,float,false", "fp64": "double,double,false",
                               "fp32_arith64": "float,double,false"}[args.prec])
-    launch_ms = r["kernel_ms"] * spl
+    lu_per_launch = r["nodes"] * args.steps / -(-args.steps // spl)  # the last launch may be shorter
+    launch_ms = r["kernel_ms"] * lu_per_launch / r["nodes"]
     # Bytes one launch must move: the stored state (21 FP32 values per node: h,
     # the low part of h_0, z and (phi u)) read once and written once, whatever
-    # the number of steps the launch performs -- bpl x nodes.  The two-step
-    # kernel keeps the intermediate state on chip, so per lattice update it
-    # needs bpl / 2; the step-equivalent rate (bpl per update) is reported
+    # the number of steps the launch performs -- bpl x nodes.  The marching
+    # kernel keeps the intermediate states on chip, so per lattice update it
+    # needs bpl / steps; the step-equivalent rate (bpl per update) is reported
     # beside it and is not a fraction of any peak.
     launch_bytes = bpl * r["nodes"]
     achieved = launch_bytes / (launch_ms * 1e-3) / 1e9
-    step_equivalent = bpl * r["nodes"] * spl / (launch_ms * 1e-3) / 1e9
+    step_equivalent = bpl * lu_per_launch / (launch_ms * 1e-3) / 1e9
     traffic = None
     if os.path.exists(args.traffic):
         with open(args.traffic) as f:
@@ -671,10 +681,11 @@ def main():
         s64 = max(20, args.steps // 4) // 2 * 2
         r64 = run_gpu(max(1, args.batch // 4), s64, 6, "fp64", fusion=args.fusion)
         extras["fp64_mlups"] = r64["nodes"] * s64 / r64["wall"] / 1e6
-        # the state (20 FP64 values per node) once in and once out per launch of spl steps
-        l64 = r64["kernel_ms"] * spl * 1e-3
+        # the state (20 FP64 values per node) once in and once out per launch of spl64 steps
+        spl64 = phase_steps_per_launch("fp64", args.fusion) if args.fusion == 2 else 1
+        l64 = r64["kernel_ms"] * spl64 * 1e-3
         extras["fp64_hbm_frac"] = BYTES_PER_LU["fp64"] * r64["nodes"] / l64 / 1e9 / HBM_PEAK_GBS
-        extras["fp64_step_equivalent_GBps"] = BYTES_PER_LU["fp64"] * r64["nodes"] * spl / l64 / 1e9
+        extras["fp64_step_equivalent_GBps"] = BYTES_PER_LU["fp64"] * r64["nodes"] * spl64 / l64 / 1e9
         log("bench: single-step kernel on the same workload")
         r1 = run_gpu(args.batch, 100, 6, "fp32", fusion=1)
         extras["single_step_fp32"] = dict(
@@ -732,7 +743,7 @@ def main():
                      "bytes_per_node_per_launch": bpl, "nodes_per_launch": r["nodes"],
                      "launch_bytes": launch_bytes, "kernel": kname, "steps_per_launch": spl,
                      "launch_ms": launch_ms,
-                     "lu_per_launch": r["nodes"] * spl,
+                     "lu_per_launch": lu_per_launch,
                      "bytes_per_lu_single_step": bpl,
                      "step_equivalent_GBps": step_equivalent,
                      "hbm_measured_GBps": (traffic / (launch_ms * 1e-3) / 1e9

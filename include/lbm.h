@@ -51,7 +51,7 @@
  *     layer at small dt falls below the resolution of the moments it is added
  *     to, and runs of 1e7 steps and more drift (the layered channel at the
  *     paper's finest grid: 9-12 % against FP64's 1.2 %; in this mode it
- *     matches FP64); the two-step kernel is not available in this mode.
+ *     matches FP64); step fusion mode 2 is not available in this mode.
  *     Reductions are FP64 in all modes.
  */
 #ifndef LBM_H
@@ -271,14 +271,13 @@ LBM_API lbm_status lbm_set_graph_steps(lbm_ctx* ctx, int steps);
  *   mode 2: several steps run as one launch of a kernel that keeps the
  *           intermediate states on chip and so moves the state once per
  *           launch; a last step left over uses the single-step kernel.
- *           LBM_D2Q9_PHASE takes two steps per launch, LBM_D2Q9_D2Q5 two to
- *           four (FP64 two or three, chosen by a cost model when the
- *           parameters are first set).
- *           LBM_D2Q9_PHASE: a whole row per workgroup when nx is a multiple
- *           of 64 up to 256, otherwise x-tiles of 256 lanes that store 250
- *           columns each and overlap their neighbours by 3 columns per side
- *           (any nx); LBM_E_UNSUPPORTED with LBM_FP32_DEV_ARITH64; ny < 4
- *           uses the single-step kernel.
+ *           LBM_D2Q9_PHASE takes two or three steps per launch (FP64 two),
+ *           LBM_D2Q9_D2Q5 two to four (FP64 two or three), chosen by a cost
+ *           model when the parameters are first set.
+ *           LBM_D2Q9_PHASE: a whole row per workgroup up to 256 columns,
+ *           otherwise x-tiles of 256 lanes that overlap their neighbours by
+ *           two columns per step and side; LBM_E_UNSUPPORTED with
+ *           LBM_FP32_DEV_ARITH64; ny < 4 uses the single-step kernel.
  *           LBM_D2Q9_D2Q5: x-tiles of 256 lanes that overlap by one column
  *           per step and side; covers flow with temperature (either
  *           thermal set, with or without buoyancy) and every boundary;
@@ -302,22 +301,21 @@ LBM_API lbm_status lbm_set_graph_steps(lbm_ctx* ctx, int steps);
  *           counters live in the context's buffer and are reset by
  *           lbm_init_fields and lbm_load_state.  On LBM_D2Q9_D2Q5, mode 3
  *           steps as mode 1.
- *   mode 0 (default), LBM_D2Q9_PHASE: mode 2 where it applies and its
- *           workgroups (one per x-tile and row segment of a replica, the
- *           segment length chosen by a launch-round model when the
- *           parameters are set) number at least 512 and, with x-tiles, at
- *           least 90 % of the launched lanes hold stored columns (never with
- *           LBM_FP32_DEV_ARITH64).  Other grids, and LBM_D2Q9_D2Q5 with flow
- *           and temperature, take the kernel that a cost model expects to be
- *           fastest: single steps, mode 2 (channel), or runs of up to ten
- *           steps per launch in LDS tiles on grids that do not fill the GPU.
+ *   mode 0 (default), LBM_D2Q9_PHASE, and LBM_D2Q9_D2Q5 with flow and
+ *           temperature: the kernel that a cost model expects to be fastest:
+ *           single steps, mode 2, or runs of several steps per launch in LDS
+ *           tiles on grids that do not fill the GPU (mode 2 never with
+ *           LBM_FP32_DEV_ARITH64).
  *   LBM_D3Q19: mode 2 runs two steps per launch on boxes of at least 2 nodes
  *           per axis, mode 0 where a cost model expects that to be faster,
  *           the others single steps.
  *   LBM_D3Q19_PHASE: mode 1 runs a phi pass and the step kernel, the other
  *           modes one launch that sums phi as it goes where that is faster.
- *   While the caller captures the stream, mode 2 on LBM_D2Q9_D2Q5 takes two
- *           steps per launch, no tiles of several steps are launched, and
+ *   While the caller captures the stream, mode 2 on the 2D lattices takes two
+ *           steps per launch, mode 0 two on grids that fill the GPU with row
+ *           segments and one on others (a rule on the grid alone: a launch
+ *           swaps the state buffers, and a replay starts from the buffer the
+ *           capture started in), no tiles of several steps are launched, and
  *           LBM_D3Q19 takes single steps.
  * The kernels evaluate the same per-node arithmetic in the same order, so
  * the modes agree to the last bit.  Not an operation of the paper: a

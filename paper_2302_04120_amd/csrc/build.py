@@ -16,7 +16,7 @@ PKG = os.path.dirname(HERE)
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "liblbm.so")
 SOURCES = ["lbm_api.hip", "lbm_kernels.hip", "lbm_chan_multi.hip", "lbm_chan_march.hip",
-           "lbm_phase_multi.hip",
+           "lbm_phase_multi.hip", "lbm_phase_march.hip",
            "lbm_adjoint.hip", "lbm_d3q19.hip", "lbm_phase3d.hip"]
 
 

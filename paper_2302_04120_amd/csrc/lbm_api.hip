@@ -279,25 +279,6 @@ hipError_t step_once(lbm_ctx* c) {
     return launch_phase_step<S>(c->pk, a, b, c->desc.prec == LBM_FP32_DEV_ARITH64, c->stream);
 }
 
-// Whether the next two two-phase steps go through the two-step kernel (mode 2
-// takes it where the kernel covers the configuration).  Automatic mode takes it
-// when its workgroups (one per row segment, x-tile and replica; two are resident
-// per CU) fill the 256 CUs and, for rows in x-tiles, at least 90 % of the
-// launched lanes hold stored columns; smaller or narrow grids keep the
-// single-step kernel, whose tiles spread over more CUs.
-bool use_tb2(const lbm_ctx* c) {
-    if (c->desc.lattice != LBM_D2Q9_PHASE || c->fusion == 1 || c->tb2_seg < 1) return false;
-    if (c->fusion == 2) return true;
-    return phase_tb2_workgroups(c->pk, c->tb2_seg) >= 512 && phase_tb2_lane_use(c->pk) >= 0.9;
-}
-
-// Whether channel steps go through the marching kernel: mode 2 wherever it covers
-// the configuration, automatic mode where its plan expects it to be fastest.
-bool use_march(const lbm_ctx* c) {
-    if (c->desc.lattice != LBM_D2Q9_D2Q5 || c->cmarch.steps < 2) return false;
-    return c->fusion == 2 || (c->fusion == 0 && c->cmarch.fast);
-}
-
 // The many-steps kernel needs the grid split into at most kPersistMaxTiles
 // tiles (of 512, 256 or 128 nodes) over all replicas, all resident at once.
 bool phase_persist_fits_desc(const lbm_desc& d) {
@@ -367,6 +348,67 @@ bool caller_captures(const lbm_ctx* c) {
     return hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
 }
 
+// Whether steps go through the marching kernel of the 2D lattices: mode 2 wherever
+// it covers the configuration, automatic mode where its plan expects it to be
+// fastest and, for steps that the caller captures, by capture_in_pairs.
+const MarchPlan& march_plan(const lbm_ctx* c) {
+    return c->desc.lattice == LBM_D2Q9_PHASE ? c->pmarch : c->cmarch;
+}
+bool use_march(const lbm_ctx* c) {
+    if (march_plan(c).steps < 2) return false;
+    if (c->fusion != 0) return c->fusion == 2;
+    return caller_captures(c) ? c->capture_pairs : march_plan(c).fast;
+}
+
+// Whether steps that the caller captures in automatic mode go in pairs, one buffer
+// swap each, instead of singly.  A replay starts from the buffer its capture
+// started in, so the number of swaps decides which runs of captured steps can be
+// replayed, and it is fixed by this rule on the grid whatever the plans say: pairs
+// where whole-row workgroups (x-tiles of 250 or 252 columns, with at least 90 % of
+// the 256 lanes stored; segments of the length that takes the fewest row steps in
+// rounds of the workgroups two steps in 225, 150 or, in FP64, twice as many
+// registers leave room for) number at least 512.
+bool capture_in_pairs(const lbm_desc& d, const PhaseK& pk, const ChanK& ck) {
+    const bool f64 = d.prec == LBM_FP64;
+    const int nx = d.nx, ny = d.ny;
+    int lanes = 256, out, per_cu, lag, least;
+    if (d.lattice == LBM_D2Q9_PHASE) {
+        if (d.prec == LBM_FP32_DEV_ARITH64 || !phase_march_fits(pk)) return false;
+        const bool whole = nx % 64 == 0 && nx <= 256;
+        if (whole) lanes = nx;
+        out = whole ? nx : 250;
+        per_cu = (f64 ? 4 : 8) / (lanes / 64);
+        lag = 5;
+        least = ny < 128 ? ny : 64;
+    } else {
+        if (!chan_march_fits(ck)) return false;
+        const bool split = nx % kBlk != 0 || (long long)nx * ck.npl * (f64 ? 8 : 4) >= (1LL << 31);
+        const bool plain = split && ck.bcx != 2 && ck.bcy != 2;
+        out = 252;
+        per_cu = ck.tq == 5 ? (f64 ? 2 : 3) : f64 ? 1 : plain ? 3 : 2;
+        lag = 2;
+        least = std::min(ny, 32);
+    }
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) == hipSuccess)
+        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int ntx = (nx + out - 1) / out;
+    const long long columns = (long long)d.batch * ntx, slots = (long long)cus * per_cu;
+    if (nx < 0.9 * double(ntx) * lanes) return false;
+    long long wgs = columns, fewest = -1;
+    for (int seg = ny; seg >= least; --seg) {
+        const long long nseg = (ny + seg - 1) / seg;
+        if (seg < ny && seg - 1 >= least && (ny + seg - 2) / std::max(seg - 1, 1) == nseg)
+            continue;  // the shortest segment of a count
+        const long long rows = (columns * nseg + slots - 1) / slots * (seg + lag);
+        if (fewest < 0 || rows < fewest) {
+            fewest = rows;
+            wgs = columns * nseg;
+        }
+    }
+    return wgs >= 512;
+}
+
 // Whether runs of steps go through the many-steps channel kernel: automatic
 // mode, where the plan made with the parameters expects it to be faster.  Not
 // under the caller's stream capture: the number of buffer swaps of a captured
@@ -407,7 +449,7 @@ hipError_t step_chan_multi(lbm_ctx* c, int left) {
 // channel.
 bool use_phase_multi(const lbm_ctx* c) {
     return c->desc.lattice == LBM_D2Q9_PHASE && c->fusion == 0 && c->pmulti.steps >= 1 &&
-           !use_tb2(c) && !caller_captures(c);
+           !caller_captures(c);
 }
 
 template <typename S>
@@ -437,8 +479,8 @@ bool use_d3_tb2(const lbm_ctx* c) {
 
 // Enqueue the next launch of a run of `left` steps, advancing the buffer parity
 // and the step count; *done receives its steps and *swaps the number of buffer
-// swaps made.  While the caller captures the stream, a marching channel launch
-// takes two steps.
+// swaps made.  While the caller captures the stream, a marching launch takes two
+// steps.
 template <typename S>
 hipError_t advance(lbm_ctx* c, int left, int* done, int* swaps) {
     hipError_t e;
@@ -447,15 +489,17 @@ hipError_t advance(lbm_ctx* c, int left, int* done, int* swaps) {
         *done = 2;
         e = launch_d3_tb2<S>(c->d3k, c->d3tb2, (const S*)bufA(c), (S*)bufB(c), c->stream);
     } else if (left >= 2 && use_march(c)) {
-        const int m = caller_captures(c) ? 2 : even_share(left, c->cmarch.steps);
-        double mods[4];
-        for (int i = 0; i < m; ++i) mods[i] = flux_mod_at(c, c->t + i);
+        const MarchPlan& plan = march_plan(c);
+        const int m = caller_captures(c) ? 2 : even_share(left, plan.steps);
         *done = m;
-        e = launch_chan_march<S>(c->ck, m, (const S*)bufA(c), (S*)bufB(c), aux_qw<S>(c),
-                                 aux_uin<S>(c), aux_tin<S>(c), mods, c->cmarch.nseg, c->stream);
-    } else if (left >= 2 && use_tb2(c)) {
-        *done = 2;
-        e = launch_phase_tb2<S>(c->pk, (const S*)bufA(c), (S*)bufB(c), c->tb2_seg, c->stream);
+        if (c->desc.lattice == LBM_D2Q9_PHASE) {
+            e = launch_phase_march<S>(c->pk, m, plan.nseg, (const S*)bufA(c), (S*)bufB(c), c->stream);
+        } else {
+            double mods[4];
+            for (int i = 0; i < m; ++i) mods[i] = flux_mod_at(c, c->t + i);
+            e = launch_chan_march<S>(c->ck, m, (const S*)bufA(c), (S*)bufB(c), aux_qw<S>(c),
+                                     aux_uin<S>(c), aux_tin<S>(c), mods, plan.nseg, c->stream);
+        }
     } else {
         *done = 1;
         e = step_once<S>(c);
@@ -637,10 +681,10 @@ lbm_status lbm_set_step_fusion(lbm_ctx* c, int mode) {
         return set_err(c, LBM_E_UNSUPPORTED,
                        "many-steps kernel needs at most 16 tiles of 512 nodes over all replicas");
     if (mode == 2 && c->desc.lattice == LBM_D2Q9_PHASE && c->desc.prec == LBM_FP32_DEV_ARITH64)
-        return set_err(c, LBM_E_UNSUPPORTED, "two-step kernel: not with FP64 arithmetic on FP32 storage");
+        return set_err(c, LBM_E_UNSUPPORTED, "marching kernel: not with FP64 arithmetic on FP32 storage");
     if (mode == 2 && c->desc.lattice == LBM_D2Q9_D2Q5 && c->has_params && !chan_march_fits(c->ck))
         return set_err(c, LBM_E_UNSUPPORTED,
-                       "two-step channel kernel: needs both flow and temperature");
+                       "marching channel kernel: needs both flow and temperature");
     if (mode != c->fusion) {
         DeviceGuard g(c->device);
         drop_graphs(c);
@@ -859,19 +903,18 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
     }
     c->ck = ck;
     c->pk = pk;
-    c->tb2_seg = 0;
-    if (d.lattice == LBM_D2Q9_PHASE && phase_tb2_fits(pk)) {
+    if (d.lattice == LBM_D2Q9_PHASE && !c->pplans_made) {  // depend on the grid and its boundaries only
         DeviceGuard g(c->device);
-        c->tb2_seg = d.prec == LBM_FP64                ? phase_tb2_seg<double>(pk)
-                     : d.prec == LBM_FP32_DEV_ARITH64 ? 0  // the two-step kernel computes in S
-                                                       : phase_tb2_seg<float>(pk);
-    }
-    if (d.lattice == LBM_D2Q9_PHASE) {
-        DeviceGuard g(c->device);
-        if (!c->pmulti_made)  // depends on the grid and its boundaries only
-            c->pmulti = d.prec == LBM_FP64 ? phase_multi_plan<double>(pk, false)
-                                           : phase_multi_plan<float>(pk, d.prec == LBM_FP32_DEV_ARITH64);
-        c->pmulti_made = true;
+        const bool f64 = d.prec == LBM_FP64, a64 = d.prec == LBM_FP32_DEV_ARITH64;
+        c->pmulti = f64 ? phase_multi_plan<double>(pk, false) : phase_multi_plan<float>(pk, a64);
+        if (!a64)  // the marching kernel computes in the state's type
+            c->pmarch = f64 ? phase_march_plan<double>(pk) : phase_march_plan<float>(pk);
+        const double single = phase_single_cost(2.0 * c->N * (f64 ? 20 * 8 : 21 * 4), f64);
+        // the marching model is up to 15 % optimistic
+        c->pmarch.fast = c->pmarch.steps > 0 &&
+                         1.1 * c->pmarch.cost < (c->pmulti.steps > 0 ? c->pmulti.cost : single);
+        c->capture_pairs = capture_in_pairs(d, pk, ck);
+        c->pplans_made = true;
     }
     if (d.lattice == LBM_D2Q9_D2Q5 && !c->cplans_made) {  // depend on the grid and its boundaries only
         DeviceGuard g(c->device);
@@ -882,6 +925,7 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
         // the marching model is up to 15 % optimistic
         c->cmarch.fast = c->cmarch.steps > 0 &&
                          1.1 * c->cmarch.cost < (c->cmulti.steps > 0 ? c->cmulti.cost : 0.95 * single);
+        c->capture_pairs = capture_in_pairs(d, pk, ck);
         c->cplans_made = true;
     }
     if (d.lattice == LBM_D3Q19_PHASE) {
@@ -1071,7 +1115,7 @@ lbm_status step_run(lbm_ctx* c, int n) {
         hipError_t e = f64 ? step_chan_multi<double>(c, n) : step_chan_multi<float>(c, n);
         return e == hipSuccess ? LBM_OK : hip_fail(c, e, "step kernel");
     }
-    if (n > 1 && use_phase_multi(c)) {
+    if (n > 1 && !use_march(c) && use_phase_multi(c)) {
         hipError_t e = f64 ? step_phase_multi<double>(c, n) : step_phase_multi<float>(c, n);
         return e == hipSuccess ? LBM_OK : hip_fail(c, e, "step kernel");
     }

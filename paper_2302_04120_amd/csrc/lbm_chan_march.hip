@@ -342,8 +342,8 @@ bool chan_march_fits(const ChanK& k) {
 // -> 152, FP64 with the D2Q9 set 427 -> 278; 4000 x 500 FP32 45 -> 21; 1003 x
 // 701 FP64 29 -> 20.  Smaller grids go through the many-steps kernel.
 template <typename S>
-ChanMarchPlan chan_march_plan(const ChanK& k) {
-    ChanMarchPlan best{};
+MarchPlan chan_march_plan(const ChanK& k) {
+    MarchPlan best{};
     int dev = 0, cus = 0;
     if (!chan_march_fits(k) || hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
@@ -372,7 +372,7 @@ ChanMarchPlan chan_march_plan(const ChanK& k) {
             };
             const double cost = (0.5 + (seg + 2 * K) * (double(wgs / cap) * row(cap) +
                                                         (wgs % cap ? row(wgs % cap) : 0.0))) / K;
-            if (best.steps == 0 || cost < best.cost) best = ChanMarchPlan{K, nseg, cost};
+            if (best.steps == 0 || cost < best.cost) best = MarchPlan{K, nseg, cost};
         }
     }
     return best;
@@ -390,7 +390,7 @@ hipError_t launch_chan_march(const ChanK& k, int K, const S* a, S* b, const S* q
 }
 
 #define LBM_MARCH_INST(S)                                                                          \
-    template ChanMarchPlan chan_march_plan<S>(const ChanK&);                                       \
+    template MarchPlan chan_march_plan<S>(const ChanK&);                                       \
     template hipError_t launch_chan_march<S>(const ChanK&, int, const S*, S*, const S*, const S*,  \
                                              const S*, const double*, int, hipStream_t);
 LBM_MARCH_INST(float)

@@ -136,6 +136,12 @@ struct MacroOut {
 // in FP32).
 inline double chan_single_cost(double bytes) { return 4.6 + bytes / 5.6e6; }
 
+// The same of a single two-phase D2Q9 step (measured: FP32 10.7 us on 4 x 256^2, 22 us
+// on 1003 x 701, 260 us on 128 x 256^2; beyond the memory-side cache at the rate of HBM).
+inline double phase_single_cost(double bytes, bool f64) {
+    return (f64 ? 6.2 : 4.8) + bytes / (bytes < 3e8 ? (f64 ? 7.4e6 : 7.0e6) : 4.9e6);
+}
+
 // Tiles and steps per launch of the many-steps channel kernel (lbm_chan_multi.hip);
 // steps 0: not used.
 constexpr int kChanMultiMax = 16;
@@ -144,11 +150,20 @@ struct ChanMultiPlan {
     double cost = 0.0;  // expected time of a step (us)
 };
 
+// Steps per launch (2 to 4) and row segments per replica of a marching 2D kernel,
+// with the expected time of a step (us); steps 0: not usable.
+struct MarchPlan {
+    int steps = 0, nseg = 0;
+    double cost = 0.0;
+    bool fast = false;  // expected to beat the other kernels (automatic mode takes it)
+};
+
 // Tiles and steps per launch of the many-steps two-phase kernel
 // (lbm_phase_multi.hip); steps 0: not used.
 constexpr int kPhaseMultiMax = 8;
 struct PhaseMultiPlan {
     int steps = 0, ntx = 0, nty = 0;
+    double cost = 0.0;
 };
 
 // Tiles per plane and z segments per replica of the 3D two-phase step that
@@ -162,14 +177,6 @@ struct P3MarchPlan {
 struct D3Tb2Plan {
     int ntx = 0, nty = 0, nseg = 0;
     bool fast = false;  // expected to beat single steps (automatic mode takes it)
-};
-
-// Steps per launch (2 to 4) and row segments per replica of the marching channel
-// kernel, with the expected time of a step (us); steps 0: not usable.
-struct ChanMarchPlan {
-    int steps = 0, nseg = 0;
-    double cost = 0.0;
-    bool fast = false;  // expected to beat the other kernels (automatic mode takes it)
 };
 
 struct D1K {
@@ -232,18 +239,19 @@ struct lbm_ctx {
     bool own_capture = false;  // while step graphs are being captured
     hipGraphExec_t step_graph[2] = {nullptr, nullptr};
     int graph_swaps[2] = {0, 0};  // buffer swaps made by each captured graph
-    // two-phase steps: 0 automatic, 1 single-step kernel only, 2 two-step
-    // kernel whenever the grid allows it, 3 many steps per cooperative launch
+    // steps: 0 automatic, 1 single-step kernel only, 2 marching or two-step
+    // kernels wherever they apply, 3 many steps per cooperative launch
     int fusion = 0;
-    lbm::ChanMarchPlan cmarch;          // channel: several steps per marching launch
+    lbm::MarchPlan cmarch;          // channel: several steps per marching launch
     lbm::ChanMultiPlan cmulti;          // channel: many steps per launch (automatic mode)
     bool cplans_made = false;
     lbm::PhaseMultiPlan pmulti;         // two-phase D2Q9: many steps per launch (automatic mode)
-    bool pmulti_made = false;
+    bool pplans_made = false;
     lbm::P3MarchPlan p3march;           // 3D two-phase: one marching launch per step
     bool p3march_made = false;
     lbm::D3Tb2Plan d3tb2;               // D3Q19: two steps per launch (automatic mode)
-    int tb2_seg = 0;                    // two-phase: rows per two-step workgroup (0: not usable)
+    lbm::MarchPlan pmarch;              // two-phase D2Q9: several steps per marching launch
+    bool capture_pairs = false;         // steps the caller captures go in pairs (automatic mode)
     unsigned* persist_flags = nullptr;  // kPersistMaxTiles step counters, then the error word
     unsigned persist_epoch = 0;         // steps taken by persistent launches since the reset
 };
@@ -274,7 +282,7 @@ hipError_t launch_chan_step(const ChanK& k, const S* a, S* b, const S* qw, const
 // segments per replica (chan_march_plan, made with the parameters)
 bool chan_march_fits(const ChanK& k);
 template <typename S>
-ChanMarchPlan chan_march_plan(const ChanK& k);
+MarchPlan chan_march_plan(const ChanK& k);
 template <typename S>
 hipError_t launch_chan_march(const ChanK& k, int K, const S* a, S* b, const S* qw, const S* uin,
                              const S* tin, const double* mods, int nseg, hipStream_t s);
@@ -305,19 +313,12 @@ PhaseMultiPlan phase_multi_plan(const PhaseK& k, bool arith64);
 template <typename S>
 hipError_t launch_phase_multi(const PhaseK& k, const PhaseMultiPlan& plan, const S* a, S* b,
                               bool arith64, int nsteps, hipStream_t s);
-// two steps in one launch; the whole state (populations and (phi u)) moves
-// from buffer a to buffer b; needs phase_tb2_fits.  seg: rows per workgroup
-// (phase_tb2_seg, fixed when the parameters are set)
-bool phase_tb2_fits(const PhaseK& k);
-// whether rows go in x-tiles (nx not a multiple of 64 up to 256), and the
-// share of the launched lanes whose columns are stored
-bool phase_tb2_tiled(const PhaseK& k);
-double phase_tb2_lane_use(const PhaseK& k);
+// several steps in one launch (plan.steps, in FP64 two): a to b
+bool phase_march_fits(const PhaseK& k);
 template <typename S>
-int phase_tb2_seg(const PhaseK& k);
-long long phase_tb2_workgroups(const PhaseK& k, int seg);
+MarchPlan phase_march_plan(const PhaseK& k);
 template <typename S>
-hipError_t launch_phase_tb2(const PhaseK& k, const S* a, S* b, int seg, hipStream_t s);
+hipError_t launch_phase_march(const PhaseK& k, int K, int nseg, const S* a, S* b, hipStream_t s);
 // *first = min(*first, t) if any node value of the nplanes planes is not
 // finite (plane stride P, or the node-block layout when blocked)
 template <typename S>

@@ -393,318 +393,6 @@ __global__ __launch_bounds__(TX * TY) void k_phase_persist(PhaseK k, S* __restri
 }
 
 // ---------------------------------------------------------------------------
-// Two steps per launch (temporal blocking).  A workgroup of nx threads (one
-// per column, nx a multiple of 64 up to 256) marches up the rows of one
-// segment [a, e) of one replica (rows per segment: phase_tb2_seg).  At row
-// v it collides step n at row v and
-// step n + 1 at row v - 3:
-//   - the post-collision values of step n are exchanged in x through LDS and
-//     accumulated, per column, into the step-(n + 1) state of rows v - 1, v
-//     and v + 1, which stays in registers (a row's state is complete once
-//     the row above it has collided);
-//   - step n + 1 at row r needs phi_{n+1} of rows r - 1 .. r + 1, i.e. the
-//     step-n collisions of rows r - 2 .. r + 2, hence the lag;
-//   - phi of both steps lives in LDS rings of four rows.
-// Only the state at n and at n + 2 touches memory: half the traffic of two
-// single steps.  Periodic y: step n also collides the two rows on each side
-// of the segment (their outputs feed only this workgroup's registers), so
-// every segment is independent.  Walls: rows outside [0, ny) do not exist
-// and the bounce-back of the single step applies at both walls.  The
-// arithmetic per node is phase_local + phase_collide, as in k_phase.
-//
-// TILED: the same march for rows of any width, in x-tiles of 256 lanes that
-// overlap by 3 columns on each side (the segment overlap of y applied in
-// x).  Lane l of tile t holds column x0 - 3 + l (mod nx), x0 = 250 t; x
-// neighbours in LDS are lanes l -+ 1, so step n is exact on lanes 1..254
-// (phi_n of both neighbours), the step-(n + 1) state on lanes 2..253 (pushes
-// from both neighbours), and step n + 1 on lanes 3..252 (phi_{n+1} of both
-// neighbours): those 250 columns are stored, the edge lanes' values are
-// never used.  The stored columns of neighbouring tiles are disjoint, and
-// every destination slot is still written by exactly one source node.
-//
-// ALIGNED (nx a multiple of 64, a row's node blocks under 2 GiB:
-// phase_tb2_aligned): every row starts on a node-block boundary, so value i of
-// column c in row v lies at the row's block base (uniform over the workgroup:
-// scalar registers) plus the column's byte offset within the row's blocks
-// (per lane, 32 bits, fixed for x, x - 1 and x + 1) plus i blocks of 64
-// values, and no access needs per-lane 64-bit index arithmetic.  Other rows
-// take the general node-block index.
-// ---------------------------------------------------------------------------
-constexpr int kTbMaxNx = 256;
-constexpr int kTbHalo = 3;                          // overlap columns per side (TILED)
-constexpr int kTbTileOut = kTbMaxNx - 2 * kTbHalo;  // stored columns per tile
-#ifndef LBM_TB_SEG
-#define LBM_TB_SEG 128
-#endif
-constexpr int kTbSeg = LBM_TB_SEG;  // rows per segment
-
-// register state of one row of one column: h 0-8, low part of h_0, z 0-8, (phi u)
-constexpr int kH = 0, kLO = 9, kZ = 10, kPU = 19, kNS = 21;
-
-template <typename S, bool TILED, bool ALIGNED>
-__global__ __launch_bounds__(kTbMaxNx) void k_phase_tb2(PhaseK k, const S* __restrict__ A,
-                                                        S* __restrict__ B, int seg) {
-    static_assert(TILED || ALIGNED, "whole rows are 64, 128, 192 or 256 columns");
-    using C = S;
-    constexpr bool RMASS = std::is_same<S, float>::value;
-    using PL = PhasePlanes<S>;
-    const int nx = k.nx, ny = k.ny;
-    const int nseg = (ny + seg - 1) / seg;
-    const int ntx = TILED ? (nx + kTbTileOut - 1) / kTbTileOut : 1;
-    int w;
-    if (!xcd_tile(ntx * nseg * k.batch, w)) return;  // whole workgroup, before any barrier
-    const int tx = w % ntx;  // x-tile (TILED), x fastest
-    w /= ntx;
-    const int b = w / nseg;
-    const int a = (w - b * nseg) * seg;
-    const int e = min(a + seg, ny);
-    const bool walls = k.bcy != 0;
-    const int s1 = walls ? max(a - 2, 0) : a - 2;   // first row of step n
-    const int e1 = walls ? min(e + 2, ny) : e + 2;  // end of step-n rows
-    const int lastload = walls ? min(e1, ny - 1) : e1;
-    const long long base = (long long)b * ny * nx;
-    // x, xm, xp: the lane's column and its periodic neighbours in memory; lx,
-    // lxm, lxp: the lane and its neighbour lanes in LDS (the same unless
-    // TILED).
-    const unsigned lx = threadIdx.x;
-    unsigned x = lx;
-    bool out = true;  // this lane stores its step-(n + 1) result
-    if constexpr (TILED) {
-        const int c = tx * kTbTileOut - kTbHalo + int(lx);
-        x = unsigned(((c % nx) + nx) % nx);
-        out = int(lx) >= kTbHalo && int(lx) < kTbMaxNx - kTbHalo && c < nx;
-    }
-    const unsigned xm = x == 0 ? nx - 1 : x - 1;
-    const unsigned xp = x == unsigned(nx - 1) ? 0u : x + 1;
-    const unsigned lxm = TILED ? (lx == 0 ? 0u : lx - 1) : xm;
-    const unsigned lxp = TILED ? (lx == kTbMaxNx - 1 ? lx : lx + 1) : xp;
-
-    __shared__ C phN[4][kTbMaxNx];   // phi_n, rows v mod 4
-    __shared__ C phN1[4][kTbMaxNx];  // phi_{n+1}
-    __shared__ C xch[12][kTbMaxNx];  // x-moving post-collision values of step n
-
-    // memory row of virtual row v: virtual rows of a periodic segment lie in
-    // [-3, ny + 2] and ny >= 4, so one correction wraps them
-    auto rowoff = [&](int v) {
-        const int r = v < 0 ? v + ny : (v >= ny ? v - ny : v);
-        return base + (long long)r * nx;
-    };
-    // value i of the node in column slot c (0: x, 1: x - 1, 2: x + 1) of row v
-    const unsigned xcol[3] = {x, xm, xp};
-    unsigned boff[3];  // ALIGNED: byte offset of value 0 of those columns within a row
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-        boff[c] = unsigned(((xcol[c] >> 6) * PL::NPL * kBlk + (xcol[c] & (kBlk - 1))) * sizeof(S));
-    auto at = [&](auto* P, int v, int c, int i) {
-        if constexpr (ALIGNED) {
-            using B8 = std::conditional_t<std::is_const_v<std::remove_pointer_t<decltype(P)>>,
-                                          const char, char>;
-            auto* row = (B8*)P + (rowoff(v) >> 6) * (long long)(PL::NPL * kBlk * sizeof(S));
-            return (decltype(P))(row + boff[c]) + i * kBlk;
-        } else {
-            return P + pidx<S>(i, rowoff(v) + xcol[c]);
-        }
-    };
-    auto load_row = [&](int v, C (&s)[kNS]) {
-#pragma unroll
-        for (int i = 0; i < 9; ++i) s[kH + i] = C(*at(A, v, 0, PL::H + i));
-#pragma unroll
-        for (int i = 0; i < 9; ++i) s[kZ + i] = C(*at(A, v, 0, PL::Z + i));
-        s[kLO] = RMASS ? C(*at(A, v, 0, PL::LO)) : C(0);
-        s[kPU] = C(*at(A, v, 0, PL::PU));
-        s[kPU + 1] = C(*at(A, v, 0, PL::PU + 1));
-    };
-    auto phi_of = [&](const C (&s)[kNS]) {
-        const C hh[9] = {s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8]};
-        return phi_sum(hh, s[kLO]);
-    };
-    // phi of row v into a ring, with the wall ghost rows (copies of the
-    // first and last rows: zero normal gradient)
-    auto put_phi = [&](C (&ring)[4][kTbMaxNx], int v, C ph) {
-        ring[v & 3][lx] = ph;
-        if (walls && v == 0) ring[3][lx] = ph;                // row -1
-        if (walls && v == ny - 1) ring[ny & 3][lx] = ph;      // row ny
-    };
-    auto gather = [&](C (&ring)[4][kTbMaxNx], int v, C (&pn)[9]) {
-        const C* rm = ring[(v - 1) & 3];
-        const C* r0 = ring[v & 3];
-        const C* rp = ring[(v + 1) & 3];
-        pn[0] = r0[lx];
-        pn[1] = r0[lxp];
-        pn[2] = rp[lx];
-        pn[3] = r0[lxm];
-        pn[4] = rm[lx];
-        pn[5] = rp[lxp];
-        pn[6] = rp[lxm];
-        pn[7] = rm[lxm];
-        pn[8] = rm[lxp];
-    };
-
-    // Register slots: slot (u - s1) mod 5 holds row u of
-    //   Ld: the stored state (rows v and v + 1 are live),
-    //   Ac: the accumulated step-(n+1) state (rows v - 3 .. v + 1).
-    // The row loop is unrolled five times, so every slot index is a
-    // compile-time constant and no row is copied between registers.
-    C Ld[5][kNS], Ac[5][kNS];
-#pragma unroll
-    for (int j = 0; j < 5; ++j)
-#pragma unroll
-        for (int q = 0; q < kNS; ++q) Ld[j][q] = Ac[j][q] = C(0);
-    // prologue: phi_n of rows s1 - 1 and s1, state of row s1 (slot 0)
-    if (!walls || s1 > 0) {
-        load_row(s1 - 1, Ld[4]);
-        put_phi(phN, s1 - 1, phi_of(Ld[4]));
-    }
-    load_row(s1, Ld[0]);
-    put_phi(phN, s1, phi_of(Ld[0]));
-    // (the first barrier of the row step orders these LDS writes)
-
-    // one row step at row v, v - s1 = J (mod 5)
-    auto row_step = [&](int v, auto Jc) {
-        constexpr int J = decltype(Jc)::value;
-        constexpr int s0 = J % 5, sn = (J + 1) % 5;          // rows v, v + 1
-        constexpr int sm1 = (J + 4) % 5, sm3 = (J + 2) % 5;  // rows v - 1, v - 3
-        const bool do_n = v < e1;
-        const bool do_load = v + 1 <= lastload;
-        const int r = v - 3;
-        // the load is unconditional (the last rows re-read an in-bounds row),
-        // so the compiler can see that every slot is overwritten before it
-        // is read and keeps only the live rows in registers
-        load_row(do_load ? v + 1 : lastload, Ld[sn]);
-        __syncthreads();  // phi_{n+1} of row v - 2 and the previous exchange reads are done
-        // ---- step n + 1 at row r = v - 3, straight to memory
-        if (r >= a && r < e && out) {
-            C pn[9], h[9], z[9], hs[9], zst[9], pux, puy;
-            S h0hi, h0lo;
-            gather(phN1, r, pn);
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                h[i] = Ac[sm3][kH + i];
-                z[i] = Ac[sm3][kZ + i];
-            }
-            const PhaseLocal<C> L = phase_local<C>(k, pn, z);
-            phase_collide<S, C>(k, L, h, Ac[sm3][kLO], z, Ac[sm3][kPU], Ac[sm3][kPU + 1], hs, h0hi,
-                                h0lo, zst, pux, puy);
-            st(at(B, r, 0, PL::PU), S(pux));
-            st(at(B, r, 0, PL::PU + 1), S(puy));
-            st(at(B, r, 0, PL::H), h0hi);
-            if constexpr (RMASS) st(at(B, r, 0, PL::LO), h0lo);
-            st(at(B, r, 0, PL::Z), S(zst[0]));
-#pragma unroll
-            for (int i = 1; i < 9; ++i) {
-                const int ryd = r + EY[i];
-                if (walls && (ryd < 0 || ryd >= ny)) {
-                    st(at(B, r, 0, PL::H + OPP[i]), S(hs[i]));
-                    st(at(B, r, 0, PL::Z + OPP[i]), S(zst[i]));
-                } else {
-                    const int c = EX[i] == 0 ? 0 : (EX[i] > 0 ? 2 : 1);
-                    st(at(B, ryd, c, PL::H + i), S(hs[i]));
-                    st(at(B, ryd, c, PL::Z + i), S(zst[i]));
-                }
-            }
-        }
-        // ---- phi_n of row v + 1
-        if (do_load) put_phi(phN, v + 1, phi_of(Ld[sn]));
-        __syncthreads();
-        // ---- step n at row v
-        C hs[9], zst[9], pux = C(0), puy = C(0);
-        S h0hi = S(0), h0lo = S(0);
-        if (do_n) {
-            C pn[9], h[9], z[9];
-            gather(phN, v, pn);
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                h[i] = Ld[s0][kH + i];
-                z[i] = Ld[s0][kZ + i];
-            }
-            const PhaseLocal<C> L = phase_local<C>(k, pn, z);
-            phase_collide<S, C>(k, L, h, Ld[s0][kLO], z, Ld[s0][kPU], Ld[s0][kPU + 1], hs, h0hi,
-                                h0lo, zst, pux, puy);
-            xch[0][lx] = hs[1];
-            xch[1][lx] = hs[3];
-            xch[2][lx] = hs[5];
-            xch[3][lx] = hs[6];
-            xch[4][lx] = hs[7];
-            xch[5][lx] = hs[8];
-            xch[6][lx] = zst[1];
-            xch[7][lx] = zst[3];
-            xch[8][lx] = zst[5];
-            xch[9][lx] = zst[6];
-            xch[10][lx] = zst[7];
-            xch[11][lx] = zst[8];
-        }
-        __syncthreads();
-        if (do_n) {
-            // pushes of row v: +y movers to row v + 1, rest and x movers to
-            // row v, -y movers to row v - 1 (x movers come from x -+ 1)
-            C(&A0)[kNS] = Ac[s0];
-            C(&Ap)[kNS] = Ac[sn];
-            C(&A1)[kNS] = Ac[sm1];
-            A0[kH + 0] = C(h0hi);
-            A0[kLO] = C(h0lo);
-            A0[kZ + 0] = zst[0];
-            A0[kPU] = pux;
-            A0[kPU + 1] = puy;
-            A0[kH + 1] = xch[0][lxm];
-            A0[kH + 3] = xch[1][lxp];
-            A0[kZ + 1] = xch[6][lxm];
-            A0[kZ + 3] = xch[7][lxp];
-            // +y movers to row v + 1, -y movers to row v - 1.  Written
-            // unconditionally (branch-free, so every slot stays in registers):
-            // at a wall the row beyond it does not exist and its slot is
-            // overwritten before it is read again.
-            Ap[kH + 2] = hs[2];
-            Ap[kH + 5] = xch[2][lxm];
-            Ap[kH + 6] = xch[3][lxp];
-            Ap[kZ + 2] = zst[2];
-            Ap[kZ + 5] = xch[8][lxm];
-            Ap[kZ + 6] = xch[9][lxp];
-            A1[kH + 4] = hs[4];
-            A1[kH + 7] = xch[4][lxp];
-            A1[kH + 8] = xch[5][lxm];
-            A1[kZ + 4] = zst[4];
-            A1[kZ + 7] = xch[10][lxp];
-            A1[kZ + 8] = xch[11][lxm];
-            // top wall: the +y movers come back reversed into the node's -y
-            // slots (below the top row, the next row's pushes overwrite them)
-            A0[kH + 4] = hs[2];
-            A0[kH + 7] = hs[5];
-            A0[kH + 8] = hs[6];
-            A0[kZ + 4] = zst[2];
-            A0[kZ + 7] = zst[5];
-            A0[kZ + 8] = zst[6];
-            // bottom wall: the -y movers come back reversed into the +y slots
-            // (elsewhere those hold the pushes of the row below)
-            const bool bottom = walls && v == 0;
-            A0[kH + 2] = bottom ? hs[4] : A0[kH + 2];
-            A0[kH + 5] = bottom ? hs[7] : A0[kH + 5];
-            A0[kH + 6] = bottom ? hs[8] : A0[kH + 6];
-            A0[kZ + 2] = bottom ? zst[4] : A0[kZ + 2];
-            A0[kZ + 5] = bottom ? zst[7] : A0[kZ + 5];
-            A0[kZ + 6] = bottom ? zst[8] : A0[kZ + 6];
-        }
-        // ---- phi_{n+1} of row v - 1, whose state is complete now
-        {
-            const int q = v - 1;
-            const bool need = q >= a - 1 && q <= e && (!walls || (q >= 0 && q < ny));
-            if (need) put_phi(phN1, q, phi_of(Ac[sm1]));
-        }
-    };
-    const int vend = e + 3;
-    for (int v = s1; v < vend; v += 5) {
-        row_step(v, std::integral_constant<int, 0>{});
-        if (v + 1 >= vend) break;
-        row_step(v + 1, std::integral_constant<int, 1>{});
-        if (v + 2 >= vend) break;
-        row_step(v + 2, std::integral_constant<int, 2>{});
-        if (v + 3 >= vend) break;
-        row_step(v + 3, std::integral_constant<int, 3>{});
-        if (v + 4 >= vend) break;
-        row_step(v + 4, std::integral_constant<int, 4>{});
-    }
-}
-
-// ---------------------------------------------------------------------------
 // 1D thermal BGK, whole run in one workgroup of WAVES waves (n <= 64 WAVES M).
 // A step is a serial chain of a few FP64 operations, so what it pays for is
 // latency: a lane keeps M consecutive nodes in registers, its neighbours'
@@ -1225,91 +913,6 @@ hipError_t launch_phase_step(const PhaseK& k, const S* a, S* b, bool arith64, hi
     return launch_phase_kernel<S, S, false>(k, a, b, MacroOut{}, lds, s);
 }
 
-// The two-step kernel takes a whole row per workgroup when nx is a multiple
-// of 64 up to 256, and x-tiles of kTbTileOut stored columns otherwise; y
-// needs at least 4 rows (virtual rows wrap with one correction).
-bool phase_tb2_fits(const PhaseK& k) { return k.ny >= 4 && k.nx >= 1; }
-bool phase_tb2_tiled(const PhaseK& k) { return !(k.nx % 64 == 0 && k.nx <= kTbMaxNx); }
-int phase_tb2_ntx(const PhaseK& k) {
-    return phase_tb2_tiled(k) ? (k.nx + kTbTileOut - 1) / kTbTileOut : 1;
-}
-// Share of the launched lanes whose columns are stored (1 for whole rows).
-double phase_tb2_lane_use(const PhaseK& k) {
-    return phase_tb2_tiled(k) ? double(k.nx) / (double(phase_tb2_ntx(k)) * kTbMaxNx) : 1.0;
-}
-
-// Whether the two-step kernel addresses rows through a scalar block base and
-// 32-bit lane offsets: nx a multiple of 64, and the byte offset of the last
-// column within a row's node blocks (nx values per state value) below 2^31.
-template <typename S>
-bool phase_tb2_aligned(const PhaseK& k) {
-    return k.nx % kBlk == 0 &&
-           (long long)k.nx * PhasePlanes<S>::NPL * (long long)sizeof(S) < (1LL << 31);
-}
-
-// Rows per segment.  Every workgroup marches seg + 5 rows (its segment, two
-// rows of overlap below and three of lag above), all workgroups take the
-// same time, and the GPU holds `slots` of them at once, so a launch costs
-// about ceil(workgroups / slots) (seg + 5) row steps.  The segment length
-// (at least 64 rows, or the whole replica) minimises that, preferring longer
-// segments on ties: 1024 replicas of 256^2 in FP32 (512 slots) keep whole
-// replicas (two full rounds); the 8192^2 domain in 33 x-tiles takes 265-row
-// segments (1023 workgroups, two rounds) instead of 128-row ones (2112
-// workgroups: a fifth, nearly empty round).
-template <typename S>
-int phase_tb2_seg(const PhaseK& k) {
-    const int ny = k.ny;
-    int dev = 0, cus = 0, per_cu = 0;
-    const bool tiled = phase_tb2_tiled(k);
-    long long slots = 512;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        (tiled ? (phase_tb2_aligned<S>(k)
-                      ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                            &per_cu, k_phase_tb2<S, true, true>, kTbMaxNx, 0)
-                      : hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                            &per_cu, k_phase_tb2<S, true, false>, kTbMaxNx, 0))
-               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_phase_tb2<S, false, true>,
-                                                              k.nx, 0)) == hipSuccess &&
-        cus > 0 && per_cu > 0)
-        slots = (long long)cus * per_cu;
-    const long long units = (long long)k.batch * phase_tb2_ntx(k);
-    const int lo = ny < kTbSeg ? ny : kTbSeg / 2;
-    int best = ny;
-    long long best_cost = -1;
-    for (int seg = ny; seg >= lo; --seg) {
-        const long long nseg = (ny + seg - 1) / seg;
-        if (seg < ny && (ny + seg - 2) / (seg - 1 > 0 ? seg - 1 : 1) == nseg && seg - 1 >= lo)
-            continue;  // a shorter segment gives the same count: take the shortest of them
-        const long long rounds = (units * nseg + slots - 1) / slots;
-        const long long cost = rounds * (seg + 5);
-        if (best_cost < 0 || cost < best_cost) {
-            best_cost = cost;
-            best = seg;
-        }
-    }
-    return best;
-}
-
-long long phase_tb2_workgroups(const PhaseK& k, int seg) {
-    return (long long)((k.ny + seg - 1) / seg) * k.batch * phase_tb2_ntx(k);
-}
-
-template <typename S>
-hipError_t launch_phase_tb2(const PhaseK& k, const S* a, S* b, int seg, hipStream_t s) {
-    if (!phase_tb2_fits(k) || seg < 1) return hipErrorInvalidValue;
-    const long long wgs = phase_tb2_workgroups(k, seg);
-    if ((wgs + kXCD - 1) / kXCD * kXCD > 0x7fffffffLL) return hipErrorInvalidValue;
-    dim3 grd(unsigned((wgs + kXCD - 1) / kXCD * kXCD));
-    if (!phase_tb2_tiled(k))
-        hipLaunchKernelGGL((k_phase_tb2<S, false, true>), grd, dim3(k.nx), 0, s, k, a, b, seg);
-    else if (phase_tb2_aligned<S>(k))
-        hipLaunchKernelGGL((k_phase_tb2<S, true, true>), grd, dim3(kTbMaxNx), 0, s, k, a, b, seg);
-    else
-        hipLaunchKernelGGL((k_phase_tb2<S, true, false>), grd, dim3(kTbMaxNx), 0, s, k, a, b, seg);
-    return hipGetLastError();
-}
-
 // One wave of 1, 2 or 4 nodes a lane up to 256 nodes, then four waves.
 hipError_t launch_d1(const D1K& k, double* g, int nsteps, hipStream_t s) {
     if (k.n < 3 || k.n > 1024) return hipErrorInvalidValue;
@@ -1408,8 +1011,6 @@ hipError_t launch_nusselt(const ChanK& k, const S* a, const S* qw, double qsi, d
     template hipError_t launch_chan_step<S>(const ChanK&, const S*, S*, const S*, const S*,     \
                                             const S*, double, hipStream_t);                       \
     template hipError_t launch_phase_step<S>(const PhaseK&, const S*, S*, bool, hipStream_t);    \
-    template hipError_t launch_phase_tb2<S>(const PhaseK&, const S*, S*, int, hipStream_t);      \
-    template int phase_tb2_seg<S>(const PhaseK&);                                                \
     template hipError_t launch_phase_persist<S>(const PhaseK&, S*, S*, int, unsigned, unsigned*,  \
                                                 unsigned*, bool, hipStream_t);                    \
     template hipError_t launch_chan_init<S>(const ChanK&, const double*, S*, hipStream_t);       \

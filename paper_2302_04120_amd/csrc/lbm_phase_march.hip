@@ -1,0 +1,390 @@
+// Several two-phase D2Q9 steps per launch on grids that fill the GPU (temporal
+// blocking): the state crosses HBM once per K steps.
+//
+// A workgroup takes one x-tile of one row segment [a, e) of one replica.  Rows of
+// up to 256 columns are one tile, a lane per column, that wraps in x (WHOLE);
+// longer ones go in tiles of 256 lanes that store 256 - 4 K columns.  It marches up
+// the rows; at row step v, stage s (0 .. K - 1) collides step n + s at row v - 2 s:
+//   - phi of the rows around it comes from the stage's ring of four rows in LDS;
+//   - the x-moving values go to the neighbour lanes through LDS;
+//   - each lane pulls the state of step n + s + 1: the values that move down
+//     complete row v - 2 s - 1, whose phi goes into the next stage's ring and which
+//     that stage collides a row step later (kept in LDS until then); the values that
+//     stay in row v - 2 s start it (W), those that move up wait for the next row (U).
+// The last stage's completed row is stored.  A step reaches two nodes (phi of the
+// neighbours' populations), so stage s is exact on lanes 2 s + 1 .. 254 - 2 s of a
+// tile and runs on rows a - 2 (K - s) + 1 .. e + 2 (K - s) - 2 (between walls those
+// that exist): tiles and segments are independent.  The arithmetic per node is that
+// of the single-step kernel (phi_sum, phase_local, phase_collide): K steps here
+// equal K single steps bit for bit.
+//
+// The stages share one exchange buffer: the first barrier of the next stage lies
+// between a stage's reads and the next writes.  Two row steps per loop iteration let
+// the loop-carried rows change registers without copies (6 % of the instructions).
+// The prefetched row is waited for before the stores of a row step, since a wait
+// after them would wait for the stores too.
+//
+// Bound: at K = 3 in FP32 the vector ALU (1180 instructions a row step, two waves
+// per SIMD at 197 to 220 registers, 85 % of its cycles issue); 2048 x 2048 moves the
+// launch's bytes at 3.7 TB/s.  Four stages would need 91 KB of LDS a workgroup, one
+// per CU.  FP64 takes two steps: 310 registers, one wave per SIMD (held to 256
+// registers it spills and takes 1.9 times as long).  The scheme this replaces
+// accumulated three rows of the next state in registers (225) for two steps.
+//
+// ALIGNED: nx a multiple of 64 and a row's node blocks under 2 GiB, so every row
+// starts on a node block and an access is the row's block base (uniform) plus a
+// 32-bit lane offset.
+#include "lbm_phase.h"
+
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+namespace lbm {
+namespace {
+
+constexpr int kPmLanes = 256;
+
+template <typename C>
+struct PhaseMarchArgs {
+    PhaseKT<C> k;
+    int ntx, nseg, wy, ey;  // tiles per row; segment i spans wy rows, one more for i < ey
+};
+
+// The state of a node: h 0-8, z 0-8, (phi u), the low part of h_0 (FP32).
+constexpr int mH = 0, mZ = 9, mPU = 18, mLO = 20, mNS = 21;
+
+template <typename S, bool WHOLE, bool ALIGNED, int K>
+__global__ __launch_bounds__(kPmLanes) void k_phase_march(const PhaseMarchArgs<S> p,
+                                                          const S* __restrict__ A,
+                                                          S* __restrict__ B) {
+    using C = S;
+    using PL = PhasePlanes<S>;
+    constexpr bool RMASS = std::is_same<S, float>::value;
+    constexpr int HALO = 2 * K, OUT = kPmLanes - 2 * HALO;
+    __shared__ C ring[K][4][kPmLanes];  // phi of each stage's state, rows mod 4
+    __shared__ C xb[12][kPmLanes];      // x-moving post-collision values
+    constexpr int NS = PL::NPL;         // LO last: FP64 has none
+    __shared__ C next[K > 1 ? K - 1 : 1][NS][kPmLanes];  // the row stages after the first collide next
+    const auto& k = p.k;
+    const int nx = k.nx, ny = k.ny;
+    int w, tx, sg, b;
+    if (!xcd_tile(p.ntx * p.nseg * k.batch, w)) return;  // whole workgroup, before any barrier
+    block_divide(w, p.ntx, w, tx);
+    block_divide(w, p.nseg, b, sg);
+    const int a = sg * p.wy + min(sg, p.ey), e = a + p.wy + (sg < p.ey);
+    const bool walls = k.bcy != 0;
+    const long long base = (long long)b * ny * nx;
+    const unsigned lx = threadIdx.x;
+    int xi;
+    bool own;
+    unsigned lxm, lxp;
+    if constexpr (WHOLE) {  // the row wraps in LDS; lanes beyond it shadow the last column
+        xi = min(int(lx), nx - 1);
+        own = int(lx) < nx;
+        lxm = xi == 0 ? nx - 1 : xi - 1;
+        lxp = xi == nx - 1 ? 0 : xi + 1;
+    } else {
+        const int col = tx * OUT - HALO + int(lx);
+        xi = col;
+        while (xi < 0) xi += nx;
+        while (xi >= nx) xi -= nx;
+        own = int(lx) >= HALO && int(lx) < kPmLanes - HALO && col < nx;
+        lxm = lx == 0 ? 0u : lx - 1;
+        lxp = lx == kPmLanes - 1 ? lx : lx + 1;
+    }
+    const unsigned x = unsigned(xi);
+    auto rowof = [&](int v) {
+        while (v < 0) v += ny;
+        while (v >= ny) v -= ny;
+        return v;
+    };
+    const unsigned boff =
+        ALIGNED ? unsigned(((x >> 6) * PL::NPL * kBlk + (x & (kBlk - 1))) * sizeof(S)) : x;
+    auto at = [&](auto* P, int row, int i) {
+        const long long ro = base + (long long)row * nx;
+        if constexpr (ALIGNED) {
+            using B8 = std::conditional_t<std::is_const_v<std::remove_pointer_t<decltype(P)>>,
+                                          const char, char>;
+            auto* r = (B8*)P + (ro >> 6) * (long long)(PL::NPL * kBlk * sizeof(S));
+            return (decltype(P))(r + boff) + i * kBlk;
+        } else {
+            return P + pidx<S>(i, ro + boff);
+        }
+    };
+    auto load_h = [&](int row, C (&h)[9], C& lo) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) h[i] = C(*at(A, row, PL::H + i));
+        lo = RMASS ? C(*at(A, row, PL::LO)) : C(0);
+    };
+    auto load_rest = [&](int row, C (&s)[mNS]) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) s[mZ + i] = C(*at(A, row, PL::Z + i));
+        s[mPU] = C(*at(A, row, PL::PU));
+        s[mPU + 1] = C(*at(A, row, PL::PU + 1));
+    };
+    auto phi_of = [&](const C (&s)[mNS]) {
+        const C hh[9] = {s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8]};
+        return phi_sum(hh, s[mLO]);
+    };
+    // first row and end of the collisions of stage s
+    auto lo_of = [&](int s) { const int r = a - (2 * (K - s) - 1); return walls ? max(r, 0) : r; };
+    auto hi_of = [&](int s) { const int r = e + (2 * (K - s) - 1); return walls ? min(r, ny) : r; };
+
+    // H0: the row stage 0 collides next, N: h of the row after it (its phi is
+    // needed a row early); W[s], U[s]: of the state that stage s builds, the started
+    // row and the values that move up from it
+    C N[9], Nlo, H0[mNS], W[K][mNS], U[K][6];
+#pragma unroll
+    for (int s = 0; s < K; ++s) {
+#pragma unroll
+        for (int i = 0; i < mNS; ++i) W[s][i] = C(0);
+        if (s > 0) {
+#pragma unroll
+            for (int i = 0; i < NS; ++i) next[s > 0 ? s - 1 : 0][i][lx] = C(0);
+        }
+#pragma unroll
+        for (int i = 0; i < 6; ++i) U[s][i] = C(0);
+    }
+    const int rlo = walls ? 0 : -(1 << 30), rhi = walls ? ny - 1 : 1 << 30;  // phi across a wall: the wall row's
+    const int first = lo_of(0), lastrow = walls ? min(e + 2 * K, ny) - 1 : e + 2 * K - 1;
+    if (!walls || first > 0) {
+        load_h(rowof(first - 1), N, Nlo);
+        ring[0][(first - 1) & 3][lx] = phi_sum(N, Nlo);
+    }
+    load_h(rowof(first), N, Nlo);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) H0[mH + i] = N[i];
+    H0[mLO] = Nlo;
+    load_rest(rowof(first), H0);
+    ring[0][first & 3][lx] = phi_sum(N, Nlo);
+    int rn = rowof(min(first + 1, lastrow));  // the row of N
+    load_h(rn, N, Nlo);
+    ring[0][(first + 1) & 3][lx] = phi_sum(N, Nlo);
+
+    auto row_step = [&](const int v) __attribute__((always_inline)) {
+        C T[mNS];
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+            const int r = v - 2 * s;
+            const bool on = r >= lo_of(s) && r < hi_of(s);
+            __syncthreads();  // phi of row r + 1 is in this stage's ring
+            C hs[9], zst[9], pux = C(0), puy = C(0);
+            S h0hi = S(0), h0lo = S(0);
+            C hc[mNS];
+#pragma unroll
+            for (int i = 0; i < mNS; ++i) {
+                if (s == 0) {
+                    hc[i] = H0[i];
+                } else if (i < NS) {  // the row below, which stage s - 1 completed an iteration ago
+                    hc[i] = next[s > 0 ? s - 1 : 0][i][lx];
+                    next[s > 0 ? s - 1 : 0][i][lx] = T[i];
+                } else {
+                    hc[i] = C(0);
+                }
+            }
+            if (on) {
+                const C* rm = ring[s][max(r - 1, rlo) & 3];
+                const C* r0 = ring[s][r & 3];
+                const C* rp = ring[s][min(r + 1, rhi) & 3];
+                const unsigned lc = WHOLE ? unsigned(xi) : lx;
+                const C pn[9] = {r0[lc], r0[lxp], rp[lc], r0[lxm], rm[lc], rp[lxp], rp[lxm], rm[lxm], rm[lxp]};
+                C h[9], z[9];
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    h[i] = hc[mH + i];
+                    z[i] = hc[mZ + i];
+                }
+                const PhaseLocal<C> L = phase_local<C>(k, pn, z);
+                phase_collide<S, C>(k, L, h, hc[mLO], z, hc[mPU], hc[mPU + 1], hs, h0hi, h0lo, zst,
+                                    pux, puy);
+                const int xm[6] = {1, 3, 5, 6, 7, 8};
+#pragma unroll
+                for (int j = 0; j < 6; ++j) {
+                    xb[j][lx] = hs[xm[j]];
+                    xb[6 + j][lx] = zst[xm[j]];
+                }
+            }
+            if (s == 0) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) H0[mH + i] = N[i];
+                H0[mLO] = Nlo;
+                load_rest(rn, H0);
+                if (v + 2 <= lastrow) rn = rn + 1 == ny ? 0 : rn + 1;
+                load_h(rn, N, Nlo);
+            }
+            __syncthreads();
+            C(&Ws)[mNS] = W[s];
+            C(&Us)[6] = U[s];
+            if (on) {  // row r - 1 receives the values that move down
+                Ws[mH + 4] = hs[4];
+                Ws[mH + 7] = xb[4][lxp];
+                Ws[mH + 8] = xb[5][lxm];
+                Ws[mZ + 4] = zst[4];
+                Ws[mZ + 7] = xb[10][lxp];
+                Ws[mZ + 8] = xb[11][lxm];
+            }
+#pragma unroll
+            for (int i = 0; i < mNS; ++i) T[i] = Ws[i];
+            if (s + 1 < K) ring[s + 1 < K ? s + 1 : 0][(r - 1) & 3][lx] = phi_of(T);
+            if (!on) continue;
+            const bool bottom = walls && r == 0, top = walls && r == ny - 1;
+            Ws[mH] = h0hi;
+            Ws[mLO] = h0lo;
+            Ws[mZ] = zst[0];
+            Ws[mPU] = pux;
+            Ws[mPU + 1] = puy;
+            Ws[mH + 1] = xb[0][lxm];
+            Ws[mH + 3] = xb[1][lxp];
+            Ws[mZ + 1] = xb[6][lxm];
+            Ws[mZ + 3] = xb[7][lxp];
+            Ws[mH + 2] = bottom ? hs[4] : Us[0];
+            Ws[mH + 5] = bottom ? hs[7] : Us[1];
+            Ws[mH + 6] = bottom ? hs[8] : Us[2];
+            Ws[mZ + 2] = bottom ? zst[4] : Us[3];
+            Ws[mZ + 5] = bottom ? zst[7] : Us[4];
+            Ws[mZ + 6] = bottom ? zst[8] : Us[5];
+            Us[0] = hs[2];
+            Us[1] = xb[2][lxm];
+            Us[2] = xb[3][lxp];
+            Us[3] = zst[2];
+            Us[4] = xb[8][lxm];
+            Us[5] = xb[9][lxp];
+            if (top) {
+                Ws[mH + 4] = hs[2];
+                Ws[mH + 7] = hs[5];
+                Ws[mH + 8] = hs[6];
+                Ws[mZ + 4] = zst[2];
+                Ws[mZ + 7] = zst[5];
+                Ws[mZ + 8] = zst[6];
+            }
+        }
+        // the loads end here, so that they do not wait for the stores below
+#pragma unroll
+        for (int i = 0; i < 9; ++i) asm volatile("" : "+v"(N[i]), "+v"(H0[mZ + i]));
+        asm volatile("" : "+v"(Nlo), "+v"(H0[mPU]), "+v"(H0[mPU + 1]));
+        ring[0][(v + 2) & 3][lx] = phi_sum(N, Nlo);
+        const int r = v - 2 * (K - 1) - 1;
+        if (own && r >= a && r < e) {
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                st(at(B, r, PL::H + i), S(T[mH + i]));
+                st(at(B, r, PL::Z + i), S(T[mZ + i]));
+            }
+            if constexpr (RMASS) st(at(B, r, PL::LO), S(T[mLO]));
+            st(at(B, r, PL::PU), S(T[mPU]));
+            st(at(B, r, PL::PU + 1), S(T[mPU + 1]));
+        }
+    };
+    for (int v = first; v <= e + 2 * (K - 1); v += 2) {
+        row_step(v);
+        row_step(v + 1);
+    }
+}
+
+template <typename S>
+bool phase_march_aligned(const PhaseK& k) {
+    return k.nx % kBlk == 0 && (long long)k.nx * PhasePlanes<S>::NPL * (long long)sizeof(S) < (1LL << 31);
+}
+template <typename S, int K>
+auto phase_march_kernel(const PhaseK& k) {
+    if (k.nx <= kPmLanes)
+        return phase_march_aligned<S>(k) ? k_phase_march<S, true, true, K> : k_phase_march<S, true, false, K>;
+    return phase_march_aligned<S>(k) ? k_phase_march<S, false, true, K> : k_phase_march<S, false, false, K>;
+}
+int phase_march_tiles(const PhaseK& k, int K) {
+    return k.nx <= kPmLanes ? 1 : (k.nx + kPmLanes - 4 * K - 1) / (kPmLanes - 4 * K);
+}
+int phase_march_waves(const PhaseK& k) { return std::min((k.nx + 63) / 64, kPmLanes / 64); }
+
+template <typename S, int K>
+hipError_t phase_march_launch(const PhaseK& k, int nseg, const S* a, S* b, hipStream_t s) {
+    const int ntx = phase_march_tiles(k, K);
+    const long long wgs = (long long)ntx * nseg * k.batch;
+    if (nseg < 1 || nseg > k.ny || wgs >= (1 << 21)) return hipErrorInvalidValue;
+    PhaseMarchArgs<S> p{};
+    p.k = phase_kt<S>(k);
+    p.ntx = ntx;
+    p.nseg = nseg;
+    p.wy = k.ny / nseg;
+    p.ey = k.ny % nseg;
+    hipLaunchKernelGGL((phase_march_kernel<S, K>(k)), dim3(unsigned((wgs + kXCD - 1) / kXCD * kXCD)),
+                       dim3(unsigned(phase_march_waves(k) * 64)), 0, s, p, a, b);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool phase_march_fits(const PhaseK& k) { return k.ny >= 4 && k.nx >= 1; }
+
+// Steps per launch and segments by a cost model fitted to 500 plans on 22 grids of
+// 0.3 M to 12 M nodes (11 %; its choice is the best measured plan on 36 of the 43
+// grids and types, within 28 % on all).  All workgroups of a round march
+// seg + 4 K - 2 rows; a row step is the root sum square of
+//   the stages' time: row0 + K lam for one workgroup on a CU (the chain of a
+//   row), or K beta for every four waves of a CU (issue), and
+//   the bytes of the resident workgroups at 24 (FP64: 11) TB/s out of the caches,
+//   at 9.0 (8.1) TB/s where both buffers outgrow the 256 MB memory-side cache.
+// Measured per step, before (the faster of single steps, the two-step scheme above
+// and LDS tiles, as automatic mode took them) -> here: FP32 128 replicas of 256^2
+// 147 -> 112-115 us, 32 replicas 73 -> 36, 2048 x 2048 138 -> 64-68, 4096 x 3000
+// 386 -> 156, 4 x 1003 x 701 100 -> 55, 12 x 256^2 25.6 -> 19.8; FP64 64 replicas
+// of 256^2 255 -> 151, 2048 x 2048 262 -> 168, 450 x 460 x 6 90 -> 60.  A single
+// 1003 x 701 domain has too few rows per workgroup to gain (FP32 21.5 -> 21.1, FP64
+// 36.7 -> 36.7) and keeps single steps, as do rows far narrower than a wave.
+template <typename S>
+MarchPlan phase_march_plan(const PhaseK& k) {
+    MarchPlan best{};
+    int dev = 0, cus = 0;
+    if (!phase_march_fits(k) || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        return best;
+    constexpr bool F32 = sizeof(S) == 4;
+    const double lam = F32 ? 0.82 : 0.97, row0 = F32 ? 0.43 : 1.2, beta = F32 ? 0.515 : 1.17;
+    const double t0 = F32 ? 11.9 : 0.6;
+    const int waves = phase_march_waves(k);
+    const double plane = double(PhasePlanes<S>::NPL) * sizeof(S);
+    const double row_bytes = 2.0 * std::min(k.nx, kPmLanes) * plane;
+    const double state = double(k.nx) * k.ny * k.batch * plane;
+    const double bw = 2 * state < 3e8 ? (F32 ? 24e6 : 11e6) : (F32 ? 9e6 : 8.1e6);  // bytes per us
+    for (int K = 2; K <= (F32 ? 3 : 2); ++K) {
+        const int resident = resident_workgroups(
+            K == 2 ? (const void*)phase_march_kernel<S, 2>(k) : (const void*)phase_march_kernel<S, F32 ? 3 : 2>(k),
+            waves);
+        if (resident < 1) continue;
+        const long long column = (long long)phase_march_tiles(k, K) * k.batch, cap = (long long)cus * resident;
+        for (int seg = k.ny; seg >= 1; --seg) {
+            const int nseg = (k.ny + seg - 1) / seg;
+            if (seg > 1 && (k.ny + seg - 2) / (seg - 1) == nseg) continue;  // shorter, the same count
+            const long long wgs = column * nseg;
+            if (wgs >= (1 << 21)) break;
+            auto row = [&](long long n) {
+                const double t = std::max(row0 + K * lam, K * beta * double((n + cus - 1) / cus) * waves / 4);
+                return std::hypot(t, row_bytes * double(n) / bw);
+            };
+            const double cost = (t0 + (seg + 4 * K - 2) * (double(wgs / cap) * row(cap) +
+                                                           (wgs % cap ? row(wgs % cap) : 0.0))) / K;
+            if (best.steps == 0 || cost < best.cost) best = MarchPlan{K, nseg, cost};
+        }
+    }
+    return best;
+}
+
+// K steps in one launch; the whole state (populations and (phi u)) moves from
+// buffer a to buffer b.
+template <typename S>
+hipError_t launch_phase_march(const PhaseK& k, int K, int nseg, const S* a, S* b, hipStream_t s) {
+    if (!phase_march_fits(k)) return hipErrorInvalidValue;
+    if (K == 2) return phase_march_launch<S, 2>(k, nseg, a, b, s);
+    if constexpr (sizeof(S) == 4)
+        if (K == 3) return phase_march_launch<S, 3>(k, nseg, a, b, s);
+    return hipErrorInvalidValue;
+}
+
+#define LBM_PMARCH_INST(S)                                                                         \
+    template MarchPlan phase_march_plan<S>(const PhaseK&);                                         \
+    template hipError_t launch_phase_march<S>(const PhaseK&, int, int, const S*, S*, hipStream_t);
+LBM_PMARCH_INST(float)
+LBM_PMARCH_INST(double)
+
+}  // namespace lbm

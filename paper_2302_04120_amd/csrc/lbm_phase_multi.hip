@@ -217,6 +217,7 @@ PhaseMultiPlan pm_plan(const PhaseK& k) {
                 if (cost < least) {
                     least = cost;
                     best.steps = steps;
+                    best.cost = cost;
                     best.ntx = ntx;
                     best.nty = nty;
                 }

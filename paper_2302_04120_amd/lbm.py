@@ -336,7 +336,7 @@ class Lattice:
         return int(s.value)
 
     def set_step_fusion(self, mode):
-        """Step kernel choice: 0 automatic, 1 single-step, 2 two-step, 3 (two-phase
+        """Step kernel choice: 0 automatic, 1 single-step, 2 marching or two-step kernels, 3 (two-phase
         D2Q9) many steps per cooperative launch, grids of at most 16 tiles."""
         self._check(lib().lbm_set_step_fusion(self.ctx, int(mode)))
 
