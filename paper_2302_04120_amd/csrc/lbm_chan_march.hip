@@ -117,13 +117,27 @@ __global__ __launch_bounds__(kMarchLanes) void k_chan_march(const ChanMarchArgs<
     }
     const int first = walls ? max(a - K, 0) : a - K, last = walls ? min(e + K, ny) : e + K;
 
+    C N[NV];  // the next row
+    int rn = rowof(first);
+    auto load_next = [&] {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) N[i] = C(*at(A, rn, i));
+    };
+    // The next row is loaded a row step ahead where that was measured to pay: 8192 x
+    // 1024 FP32 K = 4 67.6 -> 65.1 us a step (D2Q9 set 106 -> 96), FP64 D2Q9 K = 3 296
+    // -> 259.  At K = 2 the launch runs at HBM's rate either way (FP32 109 -> 112, D2Q9
+    // set 137 -> 147), and two K = 3 instances would lose a wave per SIMD to the
+    // registers.
+    constexpr bool AHEAD = sizeof(S) == 4 ? K == 4 || (K == 3 && QT == 5) : QT == 9;
+    if constexpr (AHEAD) load_next();
+
     for (int v = first; v < e + K; ++v) {
         C T[NV];  // the row the next stage collides
-        {
-            const int row = rowof(min(v, last - 1));  // the last row steps re-read an existing row
+        if constexpr (!AHEAD) load_next();
 #pragma unroll
-            for (int i = 0; i < NV; ++i) T[i] = C(*at(A, row, i));
-        }
+        for (int i = 0; i < NV; ++i) T[i] = N[i];
+        if (v + 1 < last) rn = rn + 1 == ny ? 0 : rn + 1;  // else re-reads the last row
+        if constexpr (AHEAD) load_next();
 #pragma unroll
         for (int s = 0; s < K; ++s) {
             const int r = v - s;
@@ -270,6 +284,9 @@ __global__ __launch_bounds__(kMarchLanes) void k_chan_march(const ChanMarchArgs<
                 }
             }
         }
+        // the loads end here, so that they do not wait for the stores below
+#pragma unroll
+        for (int i = 0; AHEAD && i < NV; ++i) asm volatile("" : "+v"(N[i]));
         const int r = v - K;
         if (own && r >= a) {  // complete: r < e by the loop's end
 #pragma unroll
@@ -336,10 +353,10 @@ bool chan_march_fits(const ChanK& k) {
 //   row), or K beta for each of the w workgroups of a CU (issue), and
 //   the bytes of the resident workgroups at 12 TB/s out of the caches, or 5.7
 //   to 6.7 TB/s where both buffers outgrow the 256 MB memory-side cache.
-// Measured per step, single step -> K of the plan: 8192 x 1024 FP32 182 -> 68 us
+// Measured per step, single step -> K of the plan: 8192 x 1024 FP32 182 -> 65 us
 // (K = 4; two steps in the scheme this replaces, which accumulated three rows
-// of the next state in registers: 112), with the D2Q9 set 238 -> 107, FP64 325
-// -> 152, FP64 with the D2Q9 set 427 -> 278; 4000 x 500 FP32 45 -> 21; 1003 x
+// of the next state in registers: 112), with the D2Q9 set 238 -> 97, FP64 325
+// -> 145, FP64 with the D2Q9 set 427 -> 259; 4000 x 500 FP32 45 -> 21; 1003 x
 // 701 FP64 29 -> 20.  Smaller grids go through the many-steps kernel.
 template <typename S>
 MarchPlan chan_march_plan(const ChanK& k) {
