@@ -466,14 +466,16 @@ auto d3_tb2_kernel(bool aligned, int threads) {
 
 }  // namespace
 
-// Tiles and segments by a cost model fitted to 600 plans on 16 boxes of 0.1 M
-// to 8 M nodes (it predicts them to 15 %, its choice runs within 12 % of the
-// best measured plan in 14 of the 16).  A workgroup takes planes + 2 plane
-// steps, each the longer (cubic mean) of
+// Tiles and segments by a cost model fitted to 1200 plans on 30 boxes of 0.1 M
+// to 17 M nodes (10 %; its choice runs 3 to 4 % behind the best measured plan on
+// average, 12 % at most).  A workgroup takes planes + 2 plane steps, each a
+// mean of power 2.7 of
 //   l0 + l1 waves   the chain of a plane step: load, two collisions, barrier;
-//   the bytes all resident workgroups move in it at 6.6 TB/s, with lost
-//   columns (pad) where tiles cut the rows and a share more where rows start
-//   inside node blocks,
+//   the bytes all resident workgroups move in it at 6.8 (FP64: 6.6) TB/s, with
+//   lost columns (pad) where tiles cut the rows, a share more (cut) where they
+//   cut them inside node blocks, and another (uneven) where tiles differ in
+//   height, their workgroups then drifting apart (256 x 256 x 128: tiles of 128 x 4
+//   129 us a step, of 64 x 12 and 64 x 13 142),
 // in rounds of one workgroup per CU.  Measured per step, single -> two-step:
 // FP32 256 x 256 x 128 247 -> 128-133 us (4.98 TB/s of the launch's bytes, the
 // rate of a copy), 192^3 227 -> 117, 128^3 73 -> 39, 64^3 13.6 -> 7.0; FP64
@@ -491,8 +493,9 @@ D3Tb2Plan d3_tb2_plan(const D3K& k) {
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         return best;
     constexpr bool F32 = sizeof(S) == 4;
-    const double l0 = F32 ? 1.46 : 1.12, l1 = F32 ? 0.15 : 0.38, pad = F32 ? 18 : 8;
-    const double share = k.nx % kBlk ? 0.12 : 0.0, cut = 0.12, bw = 6.6e6;  // bytes per us
+    const double l0 = F32 ? 1.41 : 1.0, l1 = F32 ? 0.15 : 0.38, pad = F32 ? 25 : 8.7;
+    const double cut = F32 ? 0.17 : 0.19, uneven = F32 ? 0.10 : 0.05, power = 2.7;
+    const double bw = F32 ? 6.8e6 : 6.6e6;  // bytes per us
     const double nodes = double(k.nx) * k.ny * k.nz * k.batch;
     const double single = 7.5 + nodes * 38 * sizeof(S) / 5.2e6;
     double least = 1e300;
@@ -504,16 +507,21 @@ D3Tb2Plan d3_tb2_plan(const D3K& k) {
             p.nty = (k.ny + h - 1) / h;
             if (h > 1 && (k.ny + h - 2) / (h - 1) == p.nty) continue;  // a lower tile of the same count
             const double lat = l0 + l1 * ((across * (h + 2) + 63) / 64);
-            const double bytes = 19.0 * sizeof(S) * (2.0 * w + (p.ntx > 1 ? pad : 0)) * h *
-                                 (1 + std::max(share, w % kBlk && p.ntx > 1 ? cut : 0.0));
+            const double bytes = 19.0 * sizeof(S) * (2.0 * w + (p.ntx > 1 ? pad : 0)) * k.ny / p.nty *
+                                 (1 + (w % kBlk && p.ntx > 1 ? cut : 0.0) + (k.ny % p.nty ? uneven : 0.0));
             const long long column = (long long)p.ntx * p.nty * k.batch;
+            const double chain = std::pow(lat, power);
+            auto plane = [&](long long n) {
+                return std::pow(chain + std::pow(bytes * n / bw, power), 1 / power);
+            };
+            const double full = plane(cus);
             for (int seg = k.nz; seg >= 1; --seg) {
                 p.nseg = (k.nz + seg - 1) / seg;
                 if (seg > 1 && (k.nz + seg - 2) / (seg - 1) == p.nseg) continue;
                 const long long wgs = column * p.nseg;
                 if (wgs >= (1 << 21)) break;
-                auto plane = [&](long long n) { return std::cbrt(lat * lat * lat + std::pow(bytes * n / bw, 3)); };
-                const double cost = (seg + 2) * (double(wgs / cus) * plane(cus) +
+                const double planes = F32 ? double(k.nz) / p.nseg : seg;
+                const double cost = (planes + 2) * (double(wgs / cus) * full +
                                                  (wgs % cus ? plane(wgs % cus) : 0.0)) / 2;
                 if (cost < least) {
                     least = cost;
