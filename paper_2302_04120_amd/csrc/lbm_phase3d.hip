@@ -463,9 +463,9 @@ __global__ __launch_bounds__(NT) void k_p3_march(const P3MarchArgs<S> p, const S
 #pragma unroll
         for (int i = 0; i < 19; ++i) Z[i] = C(*at(A, z, 4, 19 + i));
     };
-    auto load_pu = [&](int z) {
+    auto load_pu = [&](int z, C (&q)[3]) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) pu[c] = C(*at(A, z, 4, PU + c));
+        for (int c = 0; c < 3; ++c) q[c] = C(*at(A, z, 4, PU + c));
     };
     // phi of plane v from the loaded h, which the tile's own lanes keep
     auto take_h = [&](int v) {
@@ -476,6 +476,16 @@ __global__ __launch_bounds__(NT) void k_p3_march(const P3MarchArgs<S> p, const S
             if constexpr (RMASS) hb[v & 1][19][own_at] = hnlo;
         }
     };
+    // In FP64 the loads of a plane step end here, on every path and before its stores: a
+    // wait for them after the stores, which only some lanes make, would wait for those
+    // too, and without it the kernel spilled (108 B; 128^3 299 -> 270 us, 64^3 41 -> 36).
+    // FP32 gains nothing by it (192^3 496 us either way).
+    auto landed = [&] {
+        if constexpr (!RMASS) {
+#pragma unroll
+            for (int i = 0; i < 19; ++i) asm volatile("" : "+v"(Hn[i]), "+v"(Z[i]));
+        }
+    };
     auto above = [&](int v) { return k.bcz && v + 1 >= nz ? v : zof(v + 1); };
     if (!(k.bcz && a == 0)) {
         load_h(zof(a - 1));
@@ -483,7 +493,7 @@ __global__ __launch_bounds__(NT) void k_p3_march(const P3MarchArgs<S> p, const S
     }
     load_h(a);
     load_z(a);
-    load_pu(a);
+    load_pu(a, pu);
     take_h(a);
     load_h(above(a));
 
@@ -505,13 +515,20 @@ __global__ __launch_bounds__(NT) void k_p3_march(const P3MarchArgs<S> p, const S
                 }
                 L = p3_local<C>(k, pn, Z);
             }
+            C nextpu[3];
             load_z(vn);
+            load_pu(vn, nextpu);
             C H[19], hs[19], zs[19], pn3[3];
             S h0hi, h0lo;
 #pragma unroll
             for (int i = 0; i < 19; ++i) H[i] = hb[v & 1][i][own_at];
             p3_collide<S>(k, L, H, RMASS ? hb[v & 1][NH - 1][own_at] : C(0), pu, hs, h0hi, h0lo, zs, pn3);
-            load_pu(vn);
+            landed();
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                if constexpr (!RMASS) asm volatile("" : "+v"(nextpu[c]));
+                pu[c] = nextpu[c];
+            }
             const int zm = zof(v - 1), zp = zof(v + 1);
 #pragma unroll
             for (int c = 0; c < 3; ++c) st(at(B, v, 4, PU + c), S(pn3[c]));
@@ -539,6 +556,8 @@ __global__ __launch_bounds__(NT) void k_p3_march(const P3MarchArgs<S> p, const S
                     }
                 }
             }
+        } else {
+            landed();
         }
     }
 }
@@ -638,8 +657,7 @@ constexpr int p3_max_core() {
 //   where tiles cut the rows (pad) and more where rows start inside node blocks.
 // Measured per step, phi pass + step -> march: FP32 192^3 600 -> 493-515 us
 // (4.8 TB/s of 336 B per update), 128^3 179 -> 145, 100 x 120 x 130 162 -> 123,
-// 64^3 29 -> 19, 48^3 21.6 -> 13.3; FP64 192 x 192 x 96 607 -> 542 us, 128^3
-// 356 -> 299.  1024-thread workgroups (128 registers, 144 B of spills) took
+// 64^3 29 -> 19, 48^3 21.6 -> 13.3; FP64 128^3 356 -> 270 us.  1024-thread workgroups (128 registers, 144 B of spills) took
 // 613-740 us on 192^3; keeping the next plane's h in registers instead of LDS
 // took 201 registers.
 template <typename S>
