@@ -275,7 +275,7 @@ LBM_API lbm_status lbm_set_graph_steps(lbm_ctx* ctx, int steps);
  *           LBM_D2Q9_D2Q5 two to four (FP64 two or three), chosen by a cost
  *           model when the parameters are first set.
  *           LBM_D2Q9_PHASE: a whole row per workgroup up to 256 columns,
- *           otherwise x-tiles of 256 lanes that overlap their neighbours by
+ *           otherwise x-tiles of 128 or 256 lanes that overlap their neighbours by
  *           two columns per step and side; LBM_E_UNSUPPORTED with
  *           LBM_FP32_DEV_ARITH64; ny < 4 uses the single-step kernel.
  *           LBM_D2Q9_D2Q5: x-tiles of 256 lanes that overlap by one column

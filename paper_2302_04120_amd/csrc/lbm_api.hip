@@ -493,7 +493,8 @@ hipError_t advance(lbm_ctx* c, int left, int* done, int* swaps) {
         const int m = caller_captures(c) ? 2 : even_share(left, plan.steps);
         *done = m;
         if (c->desc.lattice == LBM_D2Q9_PHASE) {
-            e = launch_phase_march<S>(c->pk, m, plan.nseg, (const S*)bufA(c), (S*)bufB(c), c->stream);
+            e = launch_phase_march<S>(c->pk, m, plan.lanes, plan.nseg, (const S*)bufA(c), (S*)bufB(c),
+                                      c->stream);
         } else {
             double mods[4];
             for (int i = 0; i < m; ++i) mods[i] = flux_mod_at(c, c->t + i);
@@ -910,9 +911,8 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
         if (!a64)  // the marching kernel computes in the state's type
             c->pmarch = f64 ? phase_march_plan<double>(pk) : phase_march_plan<float>(pk);
         const double single = phase_single_cost(2.0 * c->N * (f64 ? 20 * 8 : 21 * 4), f64);
-        // the marching model is up to 15 % optimistic
         c->pmarch.fast = c->pmarch.steps > 0 &&
-                         1.1 * c->pmarch.cost < (c->pmulti.steps > 0 ? c->pmulti.cost : single);
+                         1.05 * c->pmarch.cost < (c->pmulti.steps > 0 ? c->pmulti.cost : single);
         c->capture_pairs = capture_in_pairs(d, pk, ck);
         c->pplans_made = true;
     }

@@ -136,10 +136,12 @@ struct MacroOut {
 // in FP32).
 inline double chan_single_cost(double bytes) { return 4.6 + bytes / 5.6e6; }
 
-// The same of a single two-phase D2Q9 step (measured: FP32 10.7 us on 4 x 256^2, 22 us
-// on 1003 x 701, 260 us on 128 x 256^2; beyond the memory-side cache at the rate of HBM).
+// The same of a single two-phase D2Q9 step (measured: FP32 10.6 us on 4 x 256^2, 22 us
+// on 1003 x 701, 260 us on 128 x 256^2; FP64 14.5, 36.5 and 490 us; beyond the
+// memory-side cache at the rate of HBM, in FP64 below 100 MB at the caches' 9 TB/s).
 inline double phase_single_cost(double bytes, bool f64) {
-    return (f64 ? 6.2 : 4.8) + bytes / (bytes < 3e8 ? (f64 ? 7.4e6 : 7.0e6) : 4.9e6);
+    const double near = f64 ? (bytes < 1e8 ? 9.0e6 : 7.4e6) : 7.0e6;
+    return (f64 ? 6.2 : 4.8) + bytes / (bytes < 3e8 ? near : 4.9e6);
 }
 
 // Tiles and steps per launch of the many-steps channel kernel (lbm_chan_multi.hip);
@@ -156,6 +158,7 @@ struct MarchPlan {
     int steps = 0, nseg = 0;
     double cost = 0.0;
     bool fast = false;  // expected to beat the other kernels (automatic mode takes it)
+    int lanes = 256;    // per workgroup
 };
 
 // Tiles and steps per launch of the many-steps two-phase kernel
@@ -318,7 +321,8 @@ bool phase_march_fits(const PhaseK& k);
 template <typename S>
 MarchPlan phase_march_plan(const PhaseK& k);
 template <typename S>
-hipError_t launch_phase_march(const PhaseK& k, int K, int nseg, const S* a, S* b, hipStream_t s);
+hipError_t launch_phase_march(const PhaseK& k, int K, int lanes, int nseg, const S* a, S* b,
+                              hipStream_t s);
 // *first = min(*first, t) if any node value of the nplanes planes is not
 // finite (plane stride P, or the node-block layout when blocked)
 template <typename S>

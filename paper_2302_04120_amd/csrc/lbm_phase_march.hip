@@ -3,7 +3,7 @@
 //
 // A workgroup takes one x-tile of one row segment [a, e) of one replica.  Rows of
 // up to 256 columns are one tile, a lane per column, that wraps in x (WHOLE);
-// longer ones go in tiles of 256 lanes that store 256 - 4 K columns.  It marches up
+// longer ones go in tiles of 128 or 256 lanes that store 4 K columns less.  It marches up
 // the rows; at row step v, stage s (0 .. K - 1) collides step n + s at row v - 2 s:
 //   - phi of the rows around it comes from the stage's ring of four rows in LDS;
 //   - the x-moving values go to the neighbour lanes through LDS;
@@ -12,7 +12,7 @@
 //     that stage collides a row step later (kept in LDS until then); the values that
 //     stay in row v - 2 s start it (W), those that move up wait for the next row (U).
 // The last stage's completed row is stored.  A step reaches two nodes (phi of the
-// neighbours' populations), so stage s is exact on lanes 2 s + 1 .. 254 - 2 s of a
+// neighbours' populations), so stage s is exact on lanes 2 s + 1 .. LANES - 2 - 2 s of a
 // tile and runs on rows a - 2 (K - s) + 1 .. e + 2 (K - s) - 2 (between walls those
 // that exist): tiles and segments are independent.  The arithmetic per node is that
 // of the single-step kernel (phi_sum, phase_local, phase_collide): K steps here
@@ -43,8 +43,6 @@
 namespace lbm {
 namespace {
 
-constexpr int kPmLanes = 256;
-
 template <typename C>
 struct PhaseMarchArgs {
     PhaseKT<C> k;
@@ -54,18 +52,18 @@ struct PhaseMarchArgs {
 // The state of a node: h 0-8, z 0-8, (phi u), the low part of h_0 (FP32).
 constexpr int mH = 0, mZ = 9, mPU = 18, mLO = 20, mNS = 21;
 
-template <typename S, bool WHOLE, bool ALIGNED, int K>
-__global__ __launch_bounds__(kPmLanes) void k_phase_march(const PhaseMarchArgs<S> p,
+template <typename S, bool WHOLE, bool ALIGNED, int LANES, int K>
+__global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<S> p,
                                                           const S* __restrict__ A,
                                                           S* __restrict__ B) {
     using C = S;
     using PL = PhasePlanes<S>;
     constexpr bool RMASS = std::is_same<S, float>::value;
-    constexpr int HALO = 2 * K, OUT = kPmLanes - 2 * HALO;
-    __shared__ C ring[K][4][kPmLanes];  // phi of each stage's state, rows mod 4
-    __shared__ C xb[12][kPmLanes];      // x-moving post-collision values
+    constexpr int HALO = 2 * K, OUT = LANES - 2 * HALO;
+    __shared__ C ring[K][4][LANES];  // phi of each stage's state, rows mod 4
+    __shared__ C xb[12][LANES];      // x-moving post-collision values
     constexpr int NS = PL::NPL;         // LO last: FP64 has none
-    __shared__ C next[K > 1 ? K - 1 : 1][NS][kPmLanes];  // the row stages after the first collide next
+    __shared__ C next[K > 1 ? K - 1 : 1][NS][LANES];  // the row stages after the first collide next
     const auto& k = p.k;
     const int nx = k.nx, ny = k.ny;
     int w, tx, sg, b;
@@ -89,9 +87,9 @@ __global__ __launch_bounds__(kPmLanes) void k_phase_march(const PhaseMarchArgs<S
         xi = col;
         while (xi < 0) xi += nx;
         while (xi >= nx) xi -= nx;
-        own = int(lx) >= HALO && int(lx) < kPmLanes - HALO && col < nx;
+        own = int(lx) >= HALO && int(lx) < LANES - HALO && col < nx;
         lxm = lx == 0 ? 0u : lx - 1;
-        lxp = lx == kPmLanes - 1 ? lx : lx + 1;
+        lxp = lx == LANES - 1 ? lx : lx + 1;
     }
     const unsigned x = unsigned(xi);
     auto rowof = [&](int v) {
@@ -286,30 +284,46 @@ template <typename S>
 bool phase_march_aligned(const PhaseK& k) {
     return k.nx % kBlk == 0 && (long long)k.nx * PhasePlanes<S>::NPL * (long long)sizeof(S) < (1LL << 31);
 }
-template <typename S, int K>
+template <typename S, int LANES, int K>
 auto phase_march_kernel(const PhaseK& k) {
-    if (k.nx <= kPmLanes)
-        return phase_march_aligned<S>(k) ? k_phase_march<S, true, true, K> : k_phase_march<S, true, false, K>;
-    return phase_march_aligned<S>(k) ? k_phase_march<S, false, true, K> : k_phase_march<S, false, false, K>;
+    if (k.nx <= LANES)
+        return phase_march_aligned<S>(k) ? k_phase_march<S, true, true, LANES, K>
+                                         : k_phase_march<S, true, false, LANES, K>;
+    if constexpr (LANES == 64)  // longer rows go in wider tiles
+        return k_phase_march<S, true, false, LANES, K>;
+    else
+        return phase_march_aligned<S>(k) ? k_phase_march<S, false, true, LANES, K>
+                                         : k_phase_march<S, false, false, LANES, K>;
 }
-int phase_march_tiles(const PhaseK& k, int K) {
-    return k.nx <= kPmLanes ? 1 : (k.nx + kPmLanes - 4 * K - 1) / (kPmLanes - 4 * K);
+template <typename S, int K>
+auto phase_march_kernel(const PhaseK& k, int lanes) {
+    using Kernel = decltype(phase_march_kernel<S, 64, K>(k));
+    return lanes == 64    ? (Kernel)phase_march_kernel<S, 64, K>(k)
+           : lanes == 128 ? (Kernel)phase_march_kernel<S, 128, K>(k)
+                          : (Kernel)phase_march_kernel<S, 256, K>(k);
 }
-int phase_march_waves(const PhaseK& k) { return std::min((k.nx + 63) / 64, kPmLanes / 64); }
+int phase_march_tiles(const PhaseK& k, int lanes, int K) {
+    return k.nx <= lanes ? 1 : (k.nx + lanes - 4 * K - 1) / (lanes - 4 * K);
+}
+// waves of a workgroup: those of the row's columns, or all of a tile's lanes
+int phase_march_waves(const PhaseK& k, int lanes) { return std::min((k.nx + 63) / 64, lanes / 64); }
 
 template <typename S, int K>
-hipError_t phase_march_launch(const PhaseK& k, int nseg, const S* a, S* b, hipStream_t s) {
-    const int ntx = phase_march_tiles(k, K);
+hipError_t phase_march_launch(const PhaseK& k, int lanes, int nseg, const S* a, S* b, hipStream_t s) {
+    if ((lanes != 64 && lanes != 128 && lanes != 256) || (lanes == 64 && k.nx > 64) || nseg < 1 ||
+        nseg > k.ny)
+        return hipErrorInvalidValue;
+    const int ntx = phase_march_tiles(k, lanes, K);
     const long long wgs = (long long)ntx * nseg * k.batch;
-    if (nseg < 1 || nseg > k.ny || wgs >= (1 << 21)) return hipErrorInvalidValue;
+    if (wgs >= (1 << 21)) return hipErrorInvalidValue;
     PhaseMarchArgs<S> p{};
     p.k = phase_kt<S>(k);
     p.ntx = ntx;
     p.nseg = nseg;
     p.wy = k.ny / nseg;
     p.ey = k.ny % nseg;
-    hipLaunchKernelGGL((phase_march_kernel<S, K>(k)), dim3(unsigned((wgs + kXCD - 1) / kXCD * kXCD)),
-                       dim3(unsigned(phase_march_waves(k) * 64)), 0, s, p, a, b);
+    hipLaunchKernelGGL((phase_march_kernel<S, K>(k, lanes)), dim3(unsigned((wgs + kXCD - 1) / kXCD * kXCD)),
+                       dim3(unsigned(phase_march_waves(k, lanes) * 64)), 0, s, p, a, b);
     return hipGetLastError();
 }
 
@@ -317,21 +331,25 @@ hipError_t phase_march_launch(const PhaseK& k, int nseg, const S* a, S* b, hipSt
 
 bool phase_march_fits(const PhaseK& k) { return k.ny >= 4 && k.nx >= 1; }
 
-// Steps per launch and segments by a cost model fitted to 500 plans on 22 grids of
-// 0.3 M to 12 M nodes (11 %; its choice is the best measured plan on 36 of the 43
-// grids and types, within 28 % on all).  All workgroups of a round march
+// Lanes per workgroup, steps per launch and segments by a cost model fitted to 1900
+// plans on 60 grids of 0.2 M to 12 M nodes (5 %; its choice runs within 4 % of the
+// best measured plan on all but the narrowest).  All workgroups of a round march
 // seg + 4 K - 2 rows; a row step is the root sum square of
-//   the stages' time: row0 + K lam for one workgroup on a CU (the chain of a
-//   row), or K beta for every four waves of a CU (issue), and
-//   the bytes of the resident workgroups at 24 (FP64: 11) TB/s out of the caches,
-//   at 9.0 (8.1) TB/s where both buffers outgrow the 256 MB memory-side cache.
+//   the stages' time, the cubic mean of row0 + K lam (the chain of a row: more
+//   where four waves meet at the barriers, less in one) and K beta for every four
+//   waves of a CU (issue), and
+//   the bytes of the resident workgroups at 19.6 (FP64: 14.3) TB/s out of the
+//   caches, at 9.2 (9.7) TB/s where both buffers outgrow the 256 MB memory-side
+//   cache.
 // Measured per step, before (the faster of single steps, the two-step scheme above
 // and LDS tiles, as automatic mode took them) -> here: FP32 128 replicas of 256^2
-// 147 -> 112-115 us, 32 replicas 73 -> 36, 2048 x 2048 138 -> 64-68, 4096 x 3000
-// 386 -> 156, 4 x 1003 x 701 100 -> 55, 12 x 256^2 25.6 -> 19.8; FP64 64 replicas
-// of 256^2 255 -> 151, 2048 x 2048 262 -> 168, 450 x 460 x 6 90 -> 60.  A single
-// 1003 x 701 domain has too few rows per workgroup to gain (FP32 21.5 -> 21.1, FP64
-// 36.7 -> 36.7) and keeps single steps, as do rows far narrower than a wave.
+// 147 -> 112 us, 32 replicas 73 -> 36, 2048 x 2048 138 -> 66, 4096 x 3000 386 -> 157,
+// 4 x 1003 x 701 100 -> 48, 40 x 300 x 280 117 -> 61, 128 x 128^2 73 -> 34, 256 x 64^2
+// 32 -> 21; FP64 64 replicas of 256^2 255 -> 151, 2048 x 2048 262 -> 143, 450 x 460 x
+// 6 90 -> 49, 1003 x 701 36.7 -> 31.5.  128 lanes instead of 256 waste less of ragged
+// rows, and in FP64, where a SIMD holds one wave, two workgroups fill each other's
+// barriers: 2048 x 2048 168 -> 143, 4 x 600 x 500 63 -> 45.  Rows far narrower than a
+// wave (1024 x 4 x 512: single step 72, here 313) stay with the other kernels.
 template <typename S>
 MarchPlan phase_march_plan(const PhaseK& k) {
     MarchPlan best{};
@@ -340,31 +358,37 @@ MarchPlan phase_march_plan(const PhaseK& k) {
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         return best;
     constexpr bool F32 = sizeof(S) == 4;
-    const double lam = F32 ? 0.82 : 0.97, row0 = F32 ? 0.43 : 1.2, beta = F32 ? 0.515 : 1.17;
-    const double t0 = F32 ? 11.9 : 0.6;
-    const int waves = phase_march_waves(k);
+    const double lam = F32 ? 0.61 : 0.915, row0 = F32 ? 0.79 : 0.4, beta = F32 ? 0.417 : 1.04;
+    const double t0 = F32 ? 5.7 : 1.9, one_wave = F32 ? 0.82 : 1.0, four_waves = F32 ? 1.14 : 1.55;
     const double plane = double(PhasePlanes<S>::NPL) * sizeof(S);
-    const double row_bytes = 2.0 * std::min(k.nx, kPmLanes) * plane;
     const double state = double(k.nx) * k.ny * k.batch * plane;
-    const double bw = 2 * state < 3e8 ? (F32 ? 24e6 : 11e6) : (F32 ? 9e6 : 8.1e6);  // bytes per us
-    for (int K = 2; K <= (F32 ? 3 : 2); ++K) {
-        const int resident = resident_workgroups(
-            K == 2 ? (const void*)phase_march_kernel<S, 2>(k) : (const void*)phase_march_kernel<S, F32 ? 3 : 2>(k),
-            waves);
-        if (resident < 1) continue;
-        const long long column = (long long)phase_march_tiles(k, K) * k.batch, cap = (long long)cus * resident;
-        for (int seg = k.ny; seg >= 1; --seg) {
-            const int nseg = (k.ny + seg - 1) / seg;
-            if (seg > 1 && (k.ny + seg - 2) / (seg - 1) == nseg) continue;  // shorter, the same count
-            const long long wgs = column * nseg;
-            if (wgs >= (1 << 21)) break;
-            auto row = [&](long long n) {
-                const double t = std::max(row0 + K * lam, K * beta * double((n + cus - 1) / cus) * waves / 4);
-                return std::hypot(t, row_bytes * double(n) / bw);
-            };
-            const double cost = (t0 + (seg + 4 * K - 2) * (double(wgs / cap) * row(cap) +
-                                                           (wgs % cap ? row(wgs % cap) : 0.0))) / K;
-            if (best.steps == 0 || cost < best.cost) best = MarchPlan{K, nseg, cost};
+    const double bw = 2 * state < 3e8 ? (F32 ? 19.6e6 : 14.3e6) : (F32 ? 9.2e6 : 9.7e6);  // bytes per us
+    for (int lanes = 64; lanes <= 256; lanes *= 2) {
+        // rows in one tile of the fewest lanes, longer ones in tiles of 128 or 256
+        if (k.nx <= 256 ? lanes < k.nx || (lanes > 64 && lanes / 2 >= k.nx) : lanes == 64) continue;
+        const int waves = phase_march_waves(k, lanes);
+        const double row_bytes = 2.0 * std::min(k.nx, lanes) * plane;
+        for (int K = 2; K <= (F32 ? 3 : 2); ++K) {
+            const int resident = resident_workgroups(
+                K == 2 ? (const void*)phase_march_kernel<S, 2>(k, lanes)
+                       : (const void*)phase_march_kernel<S, F32 ? 3 : 2>(k, lanes), waves);
+            if (resident < 1) continue;
+            const double chain = std::pow(row0 + K * lam * (waves == 1 ? one_wave : waves == 2 ? 1 : four_waves), 3);
+            const long long column = (long long)phase_march_tiles(k, lanes, K) * k.batch;
+            const long long cap = (long long)cus * resident;
+            for (int seg = k.ny; seg >= 1; --seg) {
+                const int nseg = (k.ny + seg - 1) / seg;
+                if (seg > 1 && (k.ny + seg - 2) / (seg - 1) == nseg) continue;  // shorter, the same count
+                const long long wgs = column * nseg;
+                if (wgs >= (1 << 21)) break;
+                auto row = [&](long long n) {
+                    const double issue = K * beta * double((n + cus - 1) / cus) * waves / 4;
+                    return std::hypot(std::cbrt(chain + issue * issue * issue), row_bytes * double(n) / bw);
+                };
+                const double cost = (t0 + (seg + 4 * K - 2) * (double(wgs / cap) * row(cap) +
+                                                               (wgs % cap ? row(wgs % cap) : 0.0))) / K;
+                if (best.steps == 0 || cost < best.cost) best = MarchPlan{K, nseg, cost, false, lanes};
+            }
         }
     }
     return best;
@@ -373,17 +397,19 @@ MarchPlan phase_march_plan(const PhaseK& k) {
 // K steps in one launch; the whole state (populations and (phi u)) moves from
 // buffer a to buffer b.
 template <typename S>
-hipError_t launch_phase_march(const PhaseK& k, int K, int nseg, const S* a, S* b, hipStream_t s) {
+hipError_t launch_phase_march(const PhaseK& k, int K, int lanes, int nseg, const S* a, S* b,
+                              hipStream_t s) {
     if (!phase_march_fits(k)) return hipErrorInvalidValue;
-    if (K == 2) return phase_march_launch<S, 2>(k, nseg, a, b, s);
+    if (K == 2) return phase_march_launch<S, 2>(k, lanes, nseg, a, b, s);
     if constexpr (sizeof(S) == 4)
-        if (K == 3) return phase_march_launch<S, 3>(k, nseg, a, b, s);
+        if (K == 3) return phase_march_launch<S, 3>(k, lanes, nseg, a, b, s);
     return hipErrorInvalidValue;
 }
 
 #define LBM_PMARCH_INST(S)                                                                         \
     template MarchPlan phase_march_plan<S>(const PhaseK&);                                         \
-    template hipError_t launch_phase_march<S>(const PhaseK&, int, int, const S*, S*, hipStream_t);
+    template hipError_t launch_phase_march<S>(const PhaseK&, int, int, int, const S*, S*, \
+                                                 hipStream_t);
 LBM_PMARCH_INST(float)
 LBM_PMARCH_INST(double)
 

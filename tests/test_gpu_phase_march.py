@@ -26,6 +26,10 @@ CASES = [
     ("tiles_of_three_steps", 488, 33, 2, False, "fp32", {"Fx": 2.0, "Fy": -1.0}),
     ("one_past_the_tiles", 497, 90, 1, False, "fp32", {}),
     ("aligned_tiles", 512, 70, 1, True, "fp32", {}),
+    ("one_wave", 33, 80, 3, True, "fp32", {}),
+    ("tiles_of_128_lanes", 360, 40, 2, False, "fp32", {}),
+    ("one_past_128_lane_tiles", 349, 21, 1, True, "fp32", {}),
+    ("one_past_128_lane_tiles_fp64", 361, 30, 1, False, "fp64", {}),
     ("whole_row_fp64", 128, 37, 2, False, "fp64", {}),
     ("tiles_fp64", 300, 5, 2, True, "fp64", {}),
     ("aligned_fp64", 320, 64, 1, False, "fp64", {"z_mrt": 0}),
