@@ -345,19 +345,19 @@ bool chan_march_fits(const ChanK& k) {
            k.bcx >= 0 && k.bcx <= 2 && k.bcy >= 0 && k.bcy <= 2 && k.nx >= 2 && k.ny >= 2;
 }
 
-// Steps per launch and segments by a cost model fitted to 900 plans on 10
-// channels of 32 k to 17 M nodes (8-10 %; its choice runs within 12 % of the best
+// Steps per launch and segments by a cost model fitted to 1300 plans on 15
+// channels of 32 k to 17 M nodes (10 %; its choice runs within 15 % of the best
 // measured plan).  All workgroups of a round march seg + 2 K rows; a row step is
 // the root sum square of
 //   the stages' time: row0 + K lam for one workgroup on a CU (the chain of a
 //   row), or K beta for each of the w workgroups of a CU (issue), and
-//   the bytes of the resident workgroups at 12 TB/s out of the caches, or 5.7
-//   to 6.7 TB/s where both buffers outgrow the 256 MB memory-side cache.
+//   the bytes of the resident workgroups at 12 to 13 TB/s out of the caches, or 5.7
+//   to 7.7 TB/s where both buffers outgrow the 256 MB memory-side cache.
 // Measured per step, single step -> K of the plan: 8192 x 1024 FP32 182 -> 65 us
 // (K = 4; two steps in the scheme this replaces, which accumulated three rows
 // of the next state in registers: 112), with the D2Q9 set 238 -> 97, FP64 325
-// -> 145, FP64 with the D2Q9 set 427 -> 259; 4000 x 500 FP32 45 -> 21; 1003 x
-// 701 FP64 29 -> 20.  Smaller grids go through the many-steps kernel.
+// -> 145, FP64 with the D2Q9 set 427 -> 260 (2500 x 700 92 -> 63, 3000 x 300 42 ->
+// 35); 4000 x 500 FP32 45 -> 21; 1003 x 701 FP64 29 -> 20.  Smaller grids go through the many-steps kernel.
 template <typename S>
 MarchPlan chan_march_plan(const ChanK& k) {
     MarchPlan best{};
@@ -366,12 +366,14 @@ MarchPlan chan_march_plan(const ChanK& k) {
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         return best;
     constexpr bool F32 = sizeof(S) == 4;
-    struct Cost { double lam, row0, beta, bw; };
-    const Cost c = F32 ? (k.tq == 9 ? Cost{0.72, 1.30, 0.225, 6.2e6} : Cost{0.55, 1.0, 0.25, 5.7e6})
-                       : (k.tq == 9 ? Cost{0.92, 1.88, 1.54, 5.7e6} : Cost{0.69, 1.37, 0.43, 6.7e6});
+    struct Cost { double t0, lam, row0, beta, near, far; };  // us, and bytes per us
+    const Cost c = F32 ? (k.tq == 9 ? Cost{0.5, 0.72, 1.30, 0.225, 12e6, 6.2e6}
+                                    : Cost{0.5, 0.55, 1.0, 0.25, 12e6, 5.7e6})
+                       : (k.tq == 9 ? Cost{3.7, 1.37, 0.37, 0.82, 13.4e6, 7.7e6}
+                                    : Cost{0.5, 0.69, 1.37, 0.43, 12e6, 6.7e6});
     const double row_bytes = 2.0 * kMarchLanes * k.npl * sizeof(S);
     const double state = double(k.nx) * k.ny * k.batch * k.npl * sizeof(S);
-    const double bw = 2 * state < 3e8 ? 12e6 : c.bw;  // bytes per us
+    const double bw = 2 * state < 3e8 ? c.near : c.far;
     for (int K = 2; K <= (F32 ? 4 : 3); ++K) {
         const int resident = K == 2   ? resident_workgroups((const void*)march_kernel<S, 2>(k), 4)
                              : K == 3 ? resident_workgroups((const void*)march_kernel<S, 3>(k), 4)
@@ -387,7 +389,7 @@ MarchPlan chan_march_plan(const ChanK& k) {
                 const double t = std::max(c.row0 + K * c.lam, K * c.beta * double((n + cus - 1) / cus));
                 return std::hypot(t, row_bytes * double(n) / bw);
             };
-            const double cost = (0.5 + (seg + 2 * K) * (double(wgs / cap) * row(cap) +
+            const double cost = (c.t0 + (seg + 2 * K) * (double(wgs / cap) * row(cap) +
                                                         (wgs % cap ? row(wgs % cap) : 0.0))) / K;
             if (best.steps == 0 || cost < best.cost) best = MarchPlan{K, nseg, cost};
         }
