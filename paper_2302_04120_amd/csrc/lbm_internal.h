@@ -245,7 +245,7 @@ struct lbm_ctx {
     // steps: 0 automatic, 1 single-step kernel only, 2 marching or two-step
     // kernels wherever they apply, 3 many steps per cooperative launch
     int fusion = 0;
-    lbm::MarchPlan cmarch;          // channel: several steps per marching launch
+    lbm::MarchPlan cmarch;              // channel: several steps per marching launch
     lbm::ChanMultiPlan cmulti;          // channel: many steps per launch (automatic mode)
     bool cplans_made = false;
     lbm::PhaseMultiPlan pmulti;         // two-phase D2Q9: many steps per launch (automatic mode)

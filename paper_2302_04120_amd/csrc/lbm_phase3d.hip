@@ -657,9 +657,9 @@ constexpr int p3_max_core() {
 //   where tiles cut the rows (pad) and more where rows start inside node blocks.
 // Measured per step, phi pass + step -> march: FP32 192^3 600 -> 493-515 us
 // (4.8 TB/s of 336 B per update), 128^3 179 -> 145, 100 x 120 x 130 162 -> 123,
-// 64^3 29 -> 19, 48^3 21.6 -> 13.3; FP64 128^3 356 -> 270 us.  1024-thread workgroups (128 registers, 144 B of spills) took
-// 613-740 us on 192^3; keeping the next plane's h in registers instead of LDS
-// took 201 registers.
+// 64^3 29 -> 19, 48^3 21.6 -> 13.3; FP64 128^3 356 -> 270 us.  1024-thread
+// workgroups (128 registers, 144 B of spills) took 613-740 us on 192^3; keeping
+// the next plane's h in registers instead of LDS took 201 registers.
 template <typename S>
 P3MarchPlan p3_march_plan(const P3K& k) {
     P3MarchPlan best{};

@@ -25,8 +25,8 @@
 // after them would wait for the stores too.
 //
 // Bound: at K = 3 in FP32 the vector ALU (1180 instructions a row step, two waves
-// per SIMD at 197 to 220 registers, 85 % of its cycles issue); 2048 x 2048 moves the
-// launch's bytes at 3.7 TB/s.  Four stages would need 91 KB of LDS a workgroup, one
+// per SIMD at 215 to 220 registers, 85 % of its cycles issue); 2048 x 2048 moves the
+// launch's bytes at 3.6 TB/s.  Four stages would need 91 KB of LDS a workgroup, one
 // per CU.  FP64 takes two steps: 310 registers, one wave per SIMD (held to 256
 // registers it spills and takes 1.9 times as long).  The scheme this replaces
 // accumulated three rows of the next state in registers (225) for two steps.
