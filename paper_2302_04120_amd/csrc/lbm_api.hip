@@ -201,13 +201,33 @@ lbm_status hip_fail(lbm_ctx* c, hipError_t e, const char* where) {
 }
 
 // Largest speed in a velocity component, in units of the lattice speed c = dx/dt;
-// a NaN counts as above every limit.
+// a NaN counts as above every limit.  Blocks without a NaN go eight values at a
+// time (one after the other is a chain of compares, 1.3 ns each).
 double speed_over_c(const double* u, long long n, double dt_over_dx) {
     double m = 0.0;
     if (!u) return m;
-    for (long long i = 0; i < n; ++i) {
-        const double a = std::fabs(u[i]) * dt_over_dx;
-        if (!(a <= m)) m = a;
+    constexpr long long kBlock = 1024;
+    for (long long i0 = 0; i0 < n; i0 += kBlock) {
+        const long long i1 = std::min(n, i0 + kBlock);
+        double top[8] = {};
+        long long i = i0;
+        bool nan = false;
+        for (; i + 8 <= i1; i += 8)
+            for (int k = 0; k < 8; ++k) {
+                const double a = std::fabs(u[i + k]) * dt_over_dx;
+                top[k] = a > top[k] ? a : top[k];
+                nan |= a != a;
+            }
+        if (nan) {
+            i = i0;  // in order: the values after a NaN decide
+        } else {
+            for (double a : top)
+                if (!(a <= m)) m = a;
+        }
+        for (; i < i1; ++i) {
+            const double a = std::fabs(u[i]) * dt_over_dx;
+            if (!(a <= m)) m = a;
+        }
     }
     return m;
 }
@@ -997,6 +1017,14 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
     return (lbm_status)warn;
 }
 
+// Enqueue the upload of a host field (zeros where it is NULL) to a staging plane.
+static hipError_t upload_field(lbm_ctx* c, int slot, const double* src) {
+    double* dst = c->staging + slot * c->P;
+    const size_t bytes = (size_t)c->N * sizeof(double);
+    return src ? hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream)
+               : hipMemsetAsync(dst, 0, bytes, c->stream);
+}
+
 lbm_status lbm_init_fields(lbm_ctx* c, const double* rho_or_p, const double* ux, const double* uy,
                            const double* T, const double* phi) {
     if (!c) return LBM_E_ARG;
@@ -1010,24 +1038,30 @@ lbm_status lbm_init_fields(lbm_ctx* c, const double* rho_or_p, const double* ux,
     if (d.lattice == LBM_D3Q19 || d.lattice == LBM_D3Q19_PHASE)
         return set_err(c, LBM_E_ARG, "3D lattices are initialised by lbm_init_fields3d");
     DeviceGuard g(c->device);
-    std::vector<double> host(5 * (size_t)N, 0.0);
-    auto put = [&](int slot, const double* src, double dflt) {
-        for (long long n = 0; n < N; ++n) host[slot * (size_t)N + n] = src ? src[n] : dflt;
-    };
-    put(0, d.lattice == LBM_D2Q9_PHASE ? rho_or_p : (d1 ? T : rho_or_p), 0.0);
-    put(1, ux, 0.0);
-    put(2, uy, 0.0);
-    put(3, T, c->sp.T_ref);
-    put(4, phi, 0.0);
-    for (int s = 0; s < 5; ++s) {
-        hipError_t e = hipMemcpyAsync(c->staging + s * P, host.data() + s * (size_t)N,
-                                      N * sizeof(double), hipMemcpyHostToDevice, c->stream);
-        if (e != hipSuccess) return hip_fail(c, e, "field upload");
+    // the fields that the lattice reads, straight from the caller's arrays
+    std::vector<double> T_ref;
+    hipError_t e = hipSuccess;
+    if (d1) {
+        e = upload_field(c, 0, T);
+    } else {
+        const bool chan = d.lattice == LBM_D2Q9_D2Q5;
+        if (chan && !T) T_ref.assign((size_t)N, c->sp.T_ref);
+        e = upload_field(c, 0, rho_or_p);
+        if (e == hipSuccess) e = upload_field(c, 1, ux);
+        if (e == hipSuccess) e = upload_field(c, 2, uy);
+        if (e == hipSuccess) e = chan ? upload_field(c, 3, T ? T : T_ref.data()) : upload_field(c, 4, phi);
+    }
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(c->stream);  // the copies read the caller's arrays
+        return hip_fail(c, e, "field upload");
     }
     c->cur = 0;
-    hipError_t e = reset_persist(c);
+    e = reset_persist(c);
     if (e == hipSuccess) e = reset_watch(c);
-    if (e != hipSuccess) return hip_fail(c, e, "step counter reset");
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(c->stream);
+        return hip_fail(c, e, "step counter reset");
+    }
     if (d1) {
         e = launch_d1_init(c->dk, c->staging, (double*)c->popA, c->stream);
     } else if (d.lattice == LBM_D2Q9_D2Q5) {
@@ -1041,14 +1075,14 @@ lbm_status lbm_init_fields(lbm_ctx* c, const double* rho_or_p, const double* ux,
         else
             e = launch_phase_init<float>(c->pk, c->staging, (float*)c->popA, c->stream);
     }
+    const double r = c->dt / c->dx;
+    const double speed = std::max(speed_over_c(ux, N, r), speed_over_c(uy, N, r));  // meanwhile
+    const hipError_t done = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "init kernel");
-    e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "init");
+    if (done != hipSuccess) return hip_fail(c, done, "init");
     c->t = 0;
     c->has_state = true;
-    const double r = c->dt / c->dx;
-    return mach_status(c, std::max(speed_over_c(ux, N, r), speed_over_c(uy, N, r)),
-                       "initial velocity");
+    return mach_status(c, speed, "initial velocity");
 }
 
 lbm_status lbm_init_fields3d(lbm_ctx* c, const double* rho_or_p, const double* ux,
@@ -1062,37 +1096,37 @@ lbm_status lbm_init_fields3d(lbm_ctx* c, const double* rho_or_p, const double* u
     if (lat == LBM_D3Q19_PHASE && !phi) return set_err(c, LBM_E_ARG, "phi is required");
     const long long N = c->N, P = c->P;
     DeviceGuard g(c->device);
-    std::vector<double> host((size_t)N);
     // staging slots: rho 0 or p 1, ux 2, uy 3, phi 5, uz 7
     const double* src[5] = {rho_or_p, ux, uy, uz, phi};
     const int slot[5] = {lat == LBM_D3Q19 ? 0 : 1, 2, 3, 7, 5};
-    for (int k = 0; k < 5; ++k) {
-        for (long long n = 0; n < N; ++n) host[n] = src[k] ? src[k][n] : 0.0;
-        hipError_t e = hipMemcpyAsync(c->staging + slot[k] * P, host.data(), N * sizeof(double),
-                                      hipMemcpyHostToDevice, c->stream);
-        // the host vector is reused: wait for each copy
-        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-        if (e != hipSuccess) return hip_fail(c, e, "field upload");
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < (lat == LBM_D3Q19 ? 4 : 5) && e == hipSuccess; ++k) e = upload_field(c, slot[k], src[k]);
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(c->stream);  // the copies read the caller's arrays
+        return hip_fail(c, e, "field upload");
     }
     c->cur = 0;
     const bool f64 = c->desc.prec == LBM_FP64;
-    hipError_t e = reset_watch(c);
-    if (e != hipSuccess) return hip_fail(c, e, "watch reset");
+    e = reset_watch(c);
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(c->stream);
+        return hip_fail(c, e, "watch reset");
+    }
     if (lat == LBM_D3Q19)
         e = f64 ? launch_d3_init<double>(c->d3k, c->staging, (double*)c->popA, c->stream)
                 : launch_d3_init<float>(c->d3k, c->staging, (float*)c->popA, c->stream);
     else
         e = f64 ? launch_p3_init<double>(c->p3k, c->staging, (double*)c->popA, c->stream)
                 : launch_p3_init<float>(c->p3k, c->staging, (float*)c->popA, c->stream);
+    const double r = c->dt / c->dx;
+    const double speed = std::max({speed_over_c(ux, N, r), speed_over_c(uy, N, r),
+                                   speed_over_c(uz, N, r)});  // meanwhile
+    const hipError_t done = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "init kernel");
-    e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "init");
+    if (done != hipSuccess) return hip_fail(c, done, "init");
     c->t = 0;
     c->has_state = true;
-    const double r = c->dt / c->dx;
-    return mach_status(c, std::max({speed_over_c(ux, N, r), speed_over_c(uy, N, r),
-                                    speed_over_c(uz, N, r)}),
-                       "initial velocity");
+    return mach_status(c, speed, "initial velocity");
 }
 
 }  // extern "C"
