@@ -399,24 +399,27 @@ __global__ __launch_bounds__(TX * TY) void k_phase_persist(PhaseK k, S* __restri
 // values come by a shift across the wave, and only a run of several waves
 // exchanges its ends through LDS (one barrier per step).  With one node per
 // thread, LDS streaming and two barriers of a 1024-thread workgroup a step took
-// 0.59 us whatever n.  Q = 2 (D1Q2) or 3 (D1Q3).
+// 0.59 us whatever n.  One wave then issues what a step costs, so instances spare
+// instructions: JE, the last node's place in its lane (its rule in that slot only,
+// and the first node's in slot 0), and no velocity factor in the equilibrium (the
+// 1D lattices have u = 0: it is one).  42 -> 31 vector instructions for Q = 2,
+// M = 2, 97 -> 73 ns a step at 101 nodes.  Q = 2 (D1Q2) or 3 (D1Q3).
 // ---------------------------------------------------------------------------
 // v of the lane before (shr) or after (shl) in the wave; 0 at its end
 __device__ __forceinline__ double wave_shr1(double v) {
     const int lo = __double2loint(v), hi = __double2hiint(v);
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x138, 0xf, 0xf, false),
-                            __builtin_amdgcn_update_dpp(0, lo, 0x138, 0xf, 0xf, false));
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x138, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, lo, 0x138, 0xf, 0xf, true));
 }
 __device__ __forceinline__ double wave_shl1(double v) {
     const int lo = __double2loint(v), hi = __double2hiint(v);
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x130, 0xf, 0xf, false),
-                            __builtin_amdgcn_update_dpp(0, lo, 0x130, 0xf, 0xf, false));
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x130, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, lo, 0x130, 0xf, 0xf, true));
 }
 
-template <int Q, int M, int WAVES>
+template <int Q, int M, int WAVES, int JE>
 __global__ __launch_bounds__(64 * WAVES) void k_d1(D1K k, double* __restrict__ g, int nsteps) {
     __shared__ double ends[2][WAVES + 2][2];  // per wave: leaving to the right, to the left
-    constexpr int ex[3] = {Q == 3 ? 0 : 1, Q == 3 ? 1 : -1, Q == 3 ? -1 : 0};
     constexpr double w[3] = {Q == 3 ? 4.0 / 6 : 0.5, Q == 3 ? 1.0 / 6 : 0.5, Q == 3 ? 1.0 / 6 : 0.0};
     constexpr int R = Q == 3 ? 1 : 0, L = Q == 3 ? 2 : 1;  // right and left movers
     const int n = k.n, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -436,7 +439,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_d1(D1K k, double* __restrict__ g
             T += 0.5 * k.qdt;
 #pragma unroll
             for (int i = 0; i < Q; ++i) {
-                const double geq = w[i] * T * (1.0 + k.ufac * ex[i]);
+                const double geq = w[i] * T;
                 sg[j][i] = v[j][i] - k.w_tau * (v[j][i] - geq) + (1.0 - 0.5 * k.w_tau) * w[i] * k.qdt;
             }
         }
@@ -455,8 +458,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_d1(D1K k, double* __restrict__ g
             v[j][L] = j < M - 1 ? sg[j < M - 1 ? j + 1 : 0][L] : from_right;
             // wet-node Dirichlet with the half source: the unknown population
             const int x = x0 + j;
-            if (x == 0) v[j][R] = k.T0 - 0.5 * k.qdt - (Q == 3 ? v[j][0] + v[j][L] : v[j][L]);
-            if (x == n - 1) v[j][L] = k.TL - 0.5 * k.qdt - (Q == 3 ? v[j][0] + v[j][R] : v[j][R]);
+            if (j == 0 && x == 0) v[j][R] = k.T0 - 0.5 * k.qdt - (Q == 3 ? v[j][0] + v[j][L] : v[j][L]);
+            if (j == JE && x == n - 1) v[j][L] = k.TL - 0.5 * k.qdt - (Q == 3 ? v[j][0] + v[j][R] : v[j][R]);
         }
     }
 #pragma unroll
@@ -915,18 +918,26 @@ hipError_t launch_phase_step(const PhaseK& k, const S* a, S* b, bool arith64, hi
 
 // One wave of 1, 2 or 4 nodes a lane up to 256 nodes, then four waves.
 hipError_t launch_d1(const D1K& k, double* g, int nsteps, hipStream_t s) {
-    if (k.n < 3 || k.n > 1024) return hipErrorInvalidValue;
+    if (k.n < 3 || k.n > 1024 || k.ufac != 0.0) return hipErrorInvalidValue;
     auto go = [&](auto kern, int waves) {
         hipLaunchKernelGGL(kern, dim3(1), dim3(64 * waves), 0, s, k, g, nsteps);
         return hipGetLastError();
     };
     auto pick = [&](auto q) {
         constexpr int Q = decltype(q)::value;
-        if (k.n <= 64) return go(k_d1<Q, 1, 1>, 1);
-        if (k.n <= 128) return go(k_d1<Q, 2, 1>, 1);
-        if (k.n <= 256) return go(k_d1<Q, 4, 1>, 1);
-        if (k.n <= 512) return go(k_d1<Q, 2, 4>, 4);
-        return go(k_d1<Q, 4, 4>, 4);
+        const int two = (k.n - 1) % 2, four = (k.n - 1) % 4;  // the last node's place in its lane
+        if (k.n <= 64) return go(k_d1<Q, 1, 1, 0>, 1);
+        if (k.n <= 128) return two ? go(k_d1<Q, 2, 1, 1>, 1) : go(k_d1<Q, 2, 1, 0>, 1);
+        if (k.n <= 256)
+            return four == 0   ? go(k_d1<Q, 4, 1, 0>, 1)
+                   : four == 1 ? go(k_d1<Q, 4, 1, 1>, 1)
+                   : four == 2 ? go(k_d1<Q, 4, 1, 2>, 1)
+                               : go(k_d1<Q, 4, 1, 3>, 1);
+        if (k.n <= 512) return two ? go(k_d1<Q, 2, 4, 1>, 4) : go(k_d1<Q, 2, 4, 0>, 4);
+        return four == 0   ? go(k_d1<Q, 4, 4, 0>, 4)
+               : four == 1 ? go(k_d1<Q, 4, 4, 1>, 4)
+               : four == 2 ? go(k_d1<Q, 4, 4, 2>, 4)
+                           : go(k_d1<Q, 4, 4, 3>, 4);
     };
     return k.q == 3 ? pick(std::integral_constant<int, 3>{}) : pick(std::integral_constant<int, 2>{});
 }
