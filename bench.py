@@ -49,9 +49,11 @@ def phase_steps_per_launch(prec, fusion):
 
 
 def phase_march_name(prec, whole, aligned, spl):
-    return "k_phase_march<%s, %s, %s, %d>" % ("float" if prec == "fp32" else "double",
-                                              "true" if whole else "false",
-                                              "true" if aligned else "false", spl)
+    """The instance at the benchmark's sizes (256 lanes; FP64 in x-tiles takes 128)."""
+    return "k_phase_march<%s, %s, %s, %d, %d>" % ("float" if prec == "fp32" else "double",
+                                                  "true" if whole else "false",
+                                                  "true" if aligned else "false",
+                                                  128 if prec == "fp64" and not whole else 256, spl)
 
 
 def kernel_source_hash():
