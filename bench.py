@@ -45,15 +45,16 @@ KERNEL_SOURCES = ("paper_2302_04120_amd/csrc/lbm_kernels.hip", "paper_2302_04120
 
 def phase_steps_per_launch(prec, fusion):
     """Steps per launch of the library's choice on grids that fill the GPU."""
-    return 1 if fusion == 1 or prec == "fp32_arith64" else 3 if prec == "fp32" else 2
+    return 1 if fusion == 1 else 3 if prec == "fp32" else 2
 
 
 def phase_march_name(prec, whole, aligned, spl):
     """The instance at the benchmark's sizes (256 lanes; FP64 in x-tiles takes 128)."""
-    return "k_phase_march<%s, %s, %s, %d, %d>" % ("float" if prec == "fp32" else "double",
-                                                  "true" if whole else "false",
-                                                  "true" if aligned else "false",
-                                                  128 if prec == "fp64" and not whole else 256, spl)
+    return "k_phase_march<%s, %s, %s, %s, %d, %d>" % ("double" if prec == "fp64" else "float",
+                                                      "float" if prec == "fp32" else "double",
+                                                      "true" if whole else "false",
+                                                      "true" if aligned else "false",
+                                                      256 if prec == "fp32" or whole else 128, spl)
 
 
 def kernel_source_hash():
@@ -654,7 +655,9 @@ def main():
                 windows=0 if args.no_extras else 5)
     mlups = r["nodes"] * args.steps / r["wall"] / 1e6
     bpl = BYTES_PER_LU[args.prec]
-    spl = phase_steps_per_launch(args.prec, args.fusion) if args.fusion == 2 else 1
+    # automatic mode marches too where the batch fills the GPU
+    march = args.fusion == 2 or (args.fusion == 0 and args.batch >= 32)
+    spl = phase_steps_per_launch(args.prec, args.fusion) if march else 1
     kname = (phase_march_name(args.prec, True, True, spl) if spl > 1 else
              "k_phase<%s>" % {"fp32": "float,float,false", "fp64": "double,double,false",
                               "fp32_arith64": "float,double,false"}[args.prec])
@@ -684,7 +687,7 @@ def main():
         r64 = run_gpu(max(1, args.batch // 4), s64, 6, "fp64", fusion=args.fusion)
         extras["fp64_mlups"] = r64["nodes"] * s64 / r64["wall"] / 1e6
         # the state (20 FP64 values per node) once in and once out per launch of spl64 steps
-        spl64 = phase_steps_per_launch("fp64", args.fusion) if args.fusion == 2 else 1
+        spl64 = phase_steps_per_launch("fp64", args.fusion) if march else 1
         l64 = r64["kernel_ms"] * spl64 * 1e-3
         extras["fp64_hbm_frac"] = BYTES_PER_LU["fp64"] * r64["nodes"] / l64 / 1e9 / HBM_PEAK_GBS
         extras["fp64_step_equivalent_GBps"] = BYTES_PER_LU["fp64"] * r64["nodes"] * spl64 / l64 / 1e9

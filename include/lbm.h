@@ -304,8 +304,8 @@ LBM_API lbm_status lbm_set_graph_steps(lbm_ctx* ctx, int steps);
  *   mode 0 (default), LBM_D2Q9_PHASE, and LBM_D2Q9_D2Q5 with flow and
  *           temperature: the kernel that a cost model expects to be fastest:
  *           single steps, mode 2, or runs of several steps per launch in LDS
- *           tiles on grids that do not fill the GPU (mode 2 never with
- *           LBM_FP32_DEV_ARITH64).
+ *           tiles on grids that do not fill the GPU (also with
+ *           LBM_FP32_DEV_ARITH64, which mode 2 itself refuses).
  *   LBM_D3Q19: mode 2 runs two steps per launch on boxes of at least 2 nodes
  *           per axis, mode 0 where a cost model expects that to be faster,
  *           the others single steps.

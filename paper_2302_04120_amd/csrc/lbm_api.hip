@@ -513,8 +513,9 @@ hipError_t advance(lbm_ctx* c, int left, int* done, int* swaps) {
         const int m = caller_captures(c) ? 2 : even_share(left, plan.steps);
         *done = m;
         if (c->desc.lattice == LBM_D2Q9_PHASE) {
-            e = launch_phase_march<S>(c->pk, m, plan.lanes, plan.nseg, (const S*)bufA(c), (S*)bufB(c),
-                                      c->stream);
+            e = launch_phase_march<S>(c->pk, m, plan.lanes, plan.nseg,
+                                      c->desc.prec == LBM_FP32_DEV_ARITH64, (const S*)bufA(c),
+                                      (S*)bufB(c), c->stream);
         } else {
             double mods[4];
             for (int i = 0; i < m; ++i) mods[i] = flux_mod_at(c, c->t + i);
@@ -928,9 +929,8 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
         DeviceGuard g(c->device);
         const bool f64 = d.prec == LBM_FP64, a64 = d.prec == LBM_FP32_DEV_ARITH64;
         c->pmulti = f64 ? phase_multi_plan<double>(pk, false) : phase_multi_plan<float>(pk, a64);
-        if (!a64)  // the marching kernel computes in the state's type
-            c->pmarch = f64 ? phase_march_plan<double>(pk) : phase_march_plan<float>(pk);
-        const double single = phase_single_cost(2.0 * c->N * (f64 ? 20 * 8 : 21 * 4), f64);
+        c->pmarch = f64 ? phase_march_plan<double>(pk, false) : phase_march_plan<float>(pk, a64);
+        const double single = phase_single_cost(2.0 * c->N * (f64 ? 20 * 8 : 21 * 4), f64, a64);
         c->pmarch.fast = c->pmarch.steps > 0 &&
                          1.05 * c->pmarch.cost < (c->pmulti.steps > 0 ? c->pmulti.cost : single);
         c->capture_pairs = capture_in_pairs(d, pk, ck);

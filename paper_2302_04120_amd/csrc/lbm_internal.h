@@ -139,7 +139,9 @@ inline double chan_single_cost(double bytes) { return 4.6 + bytes / 5.6e6; }
 // The same of a single two-phase D2Q9 step (measured: FP32 10.6 us on 4 x 256^2, 22 us
 // on 1003 x 701, 260 us on 128 x 256^2; FP64 14.5, 36.5 and 490 us; beyond the
 // memory-side cache at the rate of HBM, in FP64 below 100 MB at the caches' 9 TB/s).
-inline double phase_single_cost(double bytes, bool f64) {
+// FP64 arithmetic on an FP32 state: 28 us on 1003 x 701, 303 us on 128 x 256^2.
+inline double phase_single_cost(double bytes, bool f64, bool arith64) {
+    if (arith64) return 5.3 + bytes / (bytes < 3e8 ? 5.1e6 : 4.7e6);
     const double near = f64 ? (bytes < 1e8 ? 9.0e6 : 7.4e6) : 7.0e6;
     return (f64 ? 6.2 : 4.8) + bytes / (bytes < 3e8 ? near : 4.9e6);
 }
@@ -319,9 +321,9 @@ hipError_t launch_phase_multi(const PhaseK& k, const PhaseMultiPlan& plan, const
 // several steps in one launch (plan.steps, in FP64 two): a to b
 bool phase_march_fits(const PhaseK& k);
 template <typename S>
-MarchPlan phase_march_plan(const PhaseK& k);
+MarchPlan phase_march_plan(const PhaseK& k, bool arith64);
 template <typename S>
-hipError_t launch_phase_march(const PhaseK& k, int K, int lanes, int nseg, const S* a, S* b,
+hipError_t launch_phase_march(const PhaseK& k, int K, int lanes, int nseg, bool arith64, const S* a, S* b,
                               hipStream_t s);
 // *first = min(*first, t) if any node value of the nplanes planes is not
 // finite (plane stride P, or the node-block layout when blocked)

@@ -16,7 +16,8 @@
 // tile and runs on rows a - 2 (K - s) + 1 .. e + 2 (K - s) - 2 (between walls those
 // that exist): tiles and segments are independent.  The arithmetic per node is that
 // of the single-step kernel (phi_sum, phase_local, phase_collide): K steps here
-// equal K single steps bit for bit.
+// equal K single steps bit for bit.  C, the type of the arithmetic, may be wider than
+// the state's type S: every stage rounds to S where a single step stores.
 //
 // The stages share one exchange buffer: the first barrier of the next stage lies
 // between a stage's reads and the next writes.  Two row steps per loop iteration let
@@ -28,7 +29,8 @@
 // per SIMD at 215 to 220 registers, 85 % of its cycles issue); 2048 x 2048 moves the
 // launch's bytes at 3.6 TB/s.  Four stages would need 91 KB of LDS a workgroup, one
 // per CU.  FP64 takes two steps: 310 registers, one wave per SIMD (held to 256
-// registers it spills and takes 1.9 times as long).  The scheme this replaces
+// registers it spills and takes 1.9 times as long); FP64 arithmetic on an FP32 state,
+// which keeps the rows in FP32, two steps in 252.  The scheme this replaces
 // accumulated three rows of the next state in registers (225) for two steps.
 //
 // ALIGNED: nx a multiple of 64 and a row's node blocks under 2 GiB, so every row
@@ -52,18 +54,17 @@ struct PhaseMarchArgs {
 // The state of a node: h 0-8, z 0-8, (phi u), the low part of h_0 (FP32).
 constexpr int mH = 0, mZ = 9, mPU = 18, mLO = 20, mNS = 21;
 
-template <typename S, bool WHOLE, bool ALIGNED, int LANES, int K>
-__global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<S> p,
+template <typename S, typename C, bool WHOLE, bool ALIGNED, int LANES, int K>
+__global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<C> p,
                                                           const S* __restrict__ A,
                                                           S* __restrict__ B) {
-    using C = S;
     using PL = PhasePlanes<S>;
     constexpr bool RMASS = std::is_same<S, float>::value;
     constexpr int HALO = 2 * K, OUT = LANES - 2 * HALO;
     __shared__ C ring[K][4][LANES];  // phi of each stage's state, rows mod 4
-    __shared__ C xb[12][LANES];      // x-moving post-collision values
+    __shared__ S xb[12][LANES];      // x-moving post-collision values
     constexpr int NS = PL::NPL;         // LO last: FP64 has none
-    __shared__ C next[K > 1 ? K - 1 : 1][NS][LANES];  // the row stages after the first collide next
+    __shared__ S next[K > 1 ? K - 1 : 1][NS][LANES];  // the row stages after the first collide next
     const auto& k = p.k;
     const int nx = k.nx, ny = k.ny;
     int w, tx, sg, b;
@@ -110,20 +111,20 @@ __global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<S> p
             return P + pidx<S>(i, ro + boff);
         }
     };
-    auto load_h = [&](int row, C (&h)[9], C& lo) {
+    auto load_h = [&](int row, S (&h)[9], S& lo) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) h[i] = C(*at(A, row, PL::H + i));
-        lo = RMASS ? C(*at(A, row, PL::LO)) : C(0);
+        for (int i = 0; i < 9; ++i) h[i] = *at(A, row, PL::H + i);
+        lo = RMASS ? *at(A, row, PL::LO) : S(0);
     };
-    auto load_rest = [&](int row, C (&s)[mNS]) {
+    auto load_rest = [&](int row, S (&s)[mNS]) {
 #pragma unroll
-        for (int i = 0; i < 9; ++i) s[mZ + i] = C(*at(A, row, PL::Z + i));
-        s[mPU] = C(*at(A, row, PL::PU));
-        s[mPU + 1] = C(*at(A, row, PL::PU + 1));
+        for (int i = 0; i < 9; ++i) s[mZ + i] = *at(A, row, PL::Z + i);
+        s[mPU] = *at(A, row, PL::PU);
+        s[mPU + 1] = *at(A, row, PL::PU + 1);
     };
-    auto phi_of = [&](const C (&s)[mNS]) {
-        const C hh[9] = {s[0], s[1], s[2], s[3], s[4], s[5], s[6], s[7], s[8]};
-        return phi_sum(hh, s[mLO]);
+    auto phi_of = [&](const auto& s, S lo) {
+        const C hh[9] = {C(s[0]), C(s[1]), C(s[2]), C(s[3]), C(s[4]), C(s[5]), C(s[6]), C(s[7]), C(s[8])};
+        return phi_sum(hh, C(lo));
     };
     // first row and end of the collisions of stage s
     auto lo_of = [&](int s) { const int r = a - (2 * (K - s) - 1); return walls ? max(r, 0) : r; };
@@ -132,44 +133,43 @@ __global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<S> p
     // H0: the row stage 0 collides next, N: h of the row after it (its phi is
     // needed a row early); W[s], U[s]: of the state that stage s builds, the started
     // row and the values that move up from it
-    C N[9], Nlo, H0[mNS], W[K][mNS], U[K][6];
+    S N[9], Nlo, H0[mNS], W[K][mNS], U[K][6];
 #pragma unroll
     for (int s = 0; s < K; ++s) {
 #pragma unroll
-        for (int i = 0; i < mNS; ++i) W[s][i] = C(0);
+        for (int i = 0; i < mNS; ++i) W[s][i] = S(0);
         if (s > 0) {
 #pragma unroll
-            for (int i = 0; i < NS; ++i) next[s > 0 ? s - 1 : 0][i][lx] = C(0);
+            for (int i = 0; i < NS; ++i) next[s > 0 ? s - 1 : 0][i][lx] = S(0);
         }
 #pragma unroll
-        for (int i = 0; i < 6; ++i) U[s][i] = C(0);
+        for (int i = 0; i < 6; ++i) U[s][i] = S(0);
     }
     const int rlo = walls ? 0 : -(1 << 30), rhi = walls ? ny - 1 : 1 << 30;  // phi across a wall: the wall row's
     const int first = lo_of(0), lastrow = walls ? min(e + 2 * K, ny) - 1 : e + 2 * K - 1;
     if (!walls || first > 0) {
         load_h(rowof(first - 1), N, Nlo);
-        ring[0][(first - 1) & 3][lx] = phi_sum(N, Nlo);
+        ring[0][(first - 1) & 3][lx] = phi_of(N, Nlo);
     }
     load_h(rowof(first), N, Nlo);
 #pragma unroll
     for (int i = 0; i < 9; ++i) H0[mH + i] = N[i];
     H0[mLO] = Nlo;
     load_rest(rowof(first), H0);
-    ring[0][first & 3][lx] = phi_sum(N, Nlo);
+    ring[0][first & 3][lx] = phi_of(N, Nlo);
     int rn = rowof(min(first + 1, lastrow));  // the row of N
     load_h(rn, N, Nlo);
-    ring[0][(first + 1) & 3][lx] = phi_sum(N, Nlo);
+    ring[0][(first + 1) & 3][lx] = phi_of(N, Nlo);
 
     auto row_step = [&](const int v) __attribute__((always_inline)) {
-        C T[mNS];
+        S T[mNS];
 #pragma unroll
         for (int s = 0; s < K; ++s) {
             const int r = v - 2 * s;
             const bool on = r >= lo_of(s) && r < hi_of(s);
             __syncthreads();  // phi of row r + 1 is in this stage's ring
-            C hs[9], zst[9], pux = C(0), puy = C(0);
-            S h0hi = S(0), h0lo = S(0);
-            C hc[mNS];
+            // post-collision values, rounded to the storage type
+            S hs[9], zst[9], pux = S(0), puy = S(0), h0hi = S(0), h0lo = S(0), hc[mNS];
 #pragma unroll
             for (int i = 0; i < mNS; ++i) {
                 if (s == 0) {
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<S> p
                     hc[i] = next[s > 0 ? s - 1 : 0][i][lx];
                     next[s > 0 ? s - 1 : 0][i][lx] = T[i];
                 } else {
-                    hc[i] = C(0);
+                    hc[i] = S(0);
                 }
             }
             if (on) {
@@ -190,12 +190,20 @@ __global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<S> p
                 C h[9], z[9];
 #pragma unroll
                 for (int i = 0; i < 9; ++i) {
-                    h[i] = hc[mH + i];
-                    z[i] = hc[mZ + i];
+                    h[i] = C(hc[mH + i]);
+                    z[i] = C(hc[mZ + i]);
                 }
                 const PhaseLocal<C> L = phase_local<C>(k, pn, z);
-                phase_collide<S, C>(k, L, h, hc[mLO], z, hc[mPU], hc[mPU + 1], hs, h0hi, h0lo, zst,
-                                    pux, puy);
+                C hw[9], zw[9], pw[2];
+                phase_collide<S, C>(k, L, h, C(hc[mLO]), z, C(hc[mPU]), C(hc[mPU + 1]), hw, h0hi, h0lo,
+                                    zw, pw[0], pw[1]);
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    hs[i] = S(hw[i]);
+                    zst[i] = S(zw[i]);
+                }
+                pux = S(pw[0]);
+                puy = S(pw[1]);
                 const int xm[6] = {1, 3, 5, 6, 7, 8};
 #pragma unroll
                 for (int j = 0; j < 6; ++j) {
@@ -212,8 +220,8 @@ __global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<S> p
                 load_h(rn, N, Nlo);
             }
             __syncthreads();
-            C(&Ws)[mNS] = W[s];
-            C(&Us)[6] = U[s];
+            S(&Ws)[mNS] = W[s];
+            S(&Us)[6] = U[s];
             if (on) {  // row r - 1 receives the values that move down
                 Ws[mH + 4] = hs[4];
                 Ws[mH + 7] = xb[4][lxp];
@@ -224,7 +232,7 @@ __global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<S> p
             }
 #pragma unroll
             for (int i = 0; i < mNS; ++i) T[i] = Ws[i];
-            if (s + 1 < K) ring[s + 1 < K ? s + 1 : 0][(r - 1) & 3][lx] = phi_of(T);
+            if (s + 1 < K) ring[s + 1 < K ? s + 1 : 0][(r - 1) & 3][lx] = phi_of(T, T[mLO]);
             if (!on) continue;
             const bool bottom = walls && r == 0, top = walls && r == ny - 1;
             Ws[mH] = h0hi;
@@ -261,17 +269,17 @@ __global__ __launch_bounds__(LANES) void k_phase_march(const PhaseMarchArgs<S> p
 #pragma unroll
         for (int i = 0; i < 9; ++i) asm volatile("" : "+v"(N[i]), "+v"(H0[mZ + i]));
         asm volatile("" : "+v"(Nlo), "+v"(H0[mPU]), "+v"(H0[mPU + 1]));
-        ring[0][(v + 2) & 3][lx] = phi_sum(N, Nlo);
+        ring[0][(v + 2) & 3][lx] = phi_of(N, Nlo);
         const int r = v - 2 * (K - 1) - 1;
         if (own && r >= a && r < e) {
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
-                st(at(B, r, PL::H + i), S(T[mH + i]));
-                st(at(B, r, PL::Z + i), S(T[mZ + i]));
+                st(at(B, r, PL::H + i), T[mH + i]);
+                st(at(B, r, PL::Z + i), T[mZ + i]);
             }
-            if constexpr (RMASS) st(at(B, r, PL::LO), S(T[mLO]));
-            st(at(B, r, PL::PU), S(T[mPU]));
-            st(at(B, r, PL::PU + 1), S(T[mPU + 1]));
+            if constexpr (RMASS) st(at(B, r, PL::LO), T[mLO]);
+            st(at(B, r, PL::PU), T[mPU]);
+            st(at(B, r, PL::PU + 1), T[mPU + 1]);
         }
     };
     for (int v = first; v <= e + 2 * (K - 1); v += 2) {
@@ -284,23 +292,23 @@ template <typename S>
 bool phase_march_aligned(const PhaseK& k) {
     return k.nx % kBlk == 0 && (long long)k.nx * PhasePlanes<S>::NPL * (long long)sizeof(S) < (1LL << 31);
 }
-template <typename S, int LANES, int K>
+template <typename S, typename C, int LANES, int K>
 auto phase_march_kernel(const PhaseK& k) {
     if (k.nx <= LANES)
-        return phase_march_aligned<S>(k) ? k_phase_march<S, true, true, LANES, K>
-                                         : k_phase_march<S, true, false, LANES, K>;
+        return phase_march_aligned<S>(k) ? k_phase_march<S, C, true, true, LANES, K>
+                                         : k_phase_march<S, C, true, false, LANES, K>;
     if constexpr (LANES == 64)  // longer rows go in wider tiles
-        return k_phase_march<S, true, false, LANES, K>;
+        return k_phase_march<S, C, true, false, LANES, K>;
     else
-        return phase_march_aligned<S>(k) ? k_phase_march<S, false, true, LANES, K>
-                                         : k_phase_march<S, false, false, LANES, K>;
+        return phase_march_aligned<S>(k) ? k_phase_march<S, C, false, true, LANES, K>
+                                         : k_phase_march<S, C, false, false, LANES, K>;
 }
-template <typename S, int K>
+template <typename S, typename C, int K>
 auto phase_march_kernel(const PhaseK& k, int lanes) {
-    using Kernel = decltype(phase_march_kernel<S, 64, K>(k));
-    return lanes == 64    ? (Kernel)phase_march_kernel<S, 64, K>(k)
-           : lanes == 128 ? (Kernel)phase_march_kernel<S, 128, K>(k)
-                          : (Kernel)phase_march_kernel<S, 256, K>(k);
+    using Kernel = decltype(phase_march_kernel<S, C, 64, K>(k));
+    return lanes == 64    ? (Kernel)phase_march_kernel<S, C, 64, K>(k)
+           : lanes == 128 ? (Kernel)phase_march_kernel<S, C, 128, K>(k)
+                          : (Kernel)phase_march_kernel<S, C, 256, K>(k);
 }
 int phase_march_tiles(const PhaseK& k, int lanes, int K) {
     return k.nx <= lanes ? 1 : (k.nx + lanes - 4 * K - 1) / (lanes - 4 * K);
@@ -308,7 +316,7 @@ int phase_march_tiles(const PhaseK& k, int lanes, int K) {
 // waves of a workgroup: those of the row's columns, or all of a tile's lanes
 int phase_march_waves(const PhaseK& k, int lanes) { return std::min((k.nx + 63) / 64, lanes / 64); }
 
-template <typename S, int K>
+template <typename S, typename C, int K>
 hipError_t phase_march_launch(const PhaseK& k, int lanes, int nseg, const S* a, S* b, hipStream_t s) {
     if ((lanes != 64 && lanes != 128 && lanes != 256) || (lanes == 64 && k.nx > 64) || nseg < 1 ||
         nseg > k.ny)
@@ -316,13 +324,13 @@ hipError_t phase_march_launch(const PhaseK& k, int lanes, int nseg, const S* a, 
     const int ntx = phase_march_tiles(k, lanes, K);
     const long long wgs = (long long)ntx * nseg * k.batch;
     if (wgs >= (1 << 21)) return hipErrorInvalidValue;
-    PhaseMarchArgs<S> p{};
-    p.k = phase_kt<S>(k);
+    PhaseMarchArgs<C> p{};
+    p.k = phase_kt<C>(k);
     p.ntx = ntx;
     p.nseg = nseg;
     p.wy = k.ny / nseg;
     p.ey = k.ny % nseg;
-    hipLaunchKernelGGL((phase_march_kernel<S, K>(k, lanes)), dim3(unsigned((wgs + kXCD - 1) / kXCD * kXCD)),
+    hipLaunchKernelGGL((phase_march_kernel<S, C, K>(k, lanes)), dim3(unsigned((wgs + kXCD - 1) / kXCD * kXCD)),
                        dim3(unsigned(phase_march_waves(k, lanes) * 64)), 0, s, p, a, b);
     return hipGetLastError();
 }
@@ -338,31 +346,35 @@ bool phase_march_fits(const PhaseK& k) { return k.ny >= 4 && k.nx >= 1; }
 //   the stages' time, the cubic mean of row0 + K lam (the chain of a row: more
 //   where four waves meet at the barriers, less in one) and K beta for every four
 //   waves of a CU (issue), and
-//   the bytes of the resident workgroups at 19.6 (FP64: 14.3) TB/s out of the
-//   caches, at 9.2 (9.7) TB/s where both buffers outgrow the 256 MB memory-side
-//   cache.
+//   the bytes of the resident workgroups at 19.6 (FP64: 14.3; FP64 arithmetic on an
+//   FP32 state: 40, where issue hides them) TB/s out of the caches, at 9.2 to 10 TB/s
+//   where both buffers outgrow the 256 MB memory-side cache.
 // Measured per step, before (the faster of single steps, the two-step scheme above
 // and LDS tiles, as automatic mode took them) -> here: FP32 128 replicas of 256^2
 // 147 -> 112 us, 32 replicas 73 -> 36, 2048 x 2048 138 -> 66, 4096 x 3000 386 -> 157,
 // 4 x 1003 x 701 100 -> 48, 40 x 300 x 280 117 -> 61, 128 x 128^2 73 -> 34, 256 x 64^2
 // 32 -> 21; FP64 64 replicas of 256^2 255 -> 151, 2048 x 2048 262 -> 143, 450 x 460 x
-// 6 90 -> 49, 1003 x 701 36.7 -> 31.5.  128 lanes instead of 256 waste less of ragged
-// rows, and in FP64, where a SIMD holds one wave, two workgroups fill each other's
+// 6 90 -> 49, 1003 x 701 36.7 -> 31.5; FP64 arithmetic on an FP32 state (single steps
+// before) 128 x 256^2 303 -> 177, 2048 x 2048 151 -> 94, 4 x 600 x 500 44 -> 35.  128
+// lanes instead of 256 waste less of ragged rows, and in FP64, where a SIMD holds one wave, two workgroups fill each other's
 // barriers: 2048 x 2048 168 -> 143, 4 x 600 x 500 63 -> 45.  Rows far narrower than a
 // wave (1024 x 4 x 512: single step 72, here 313) stay with the other kernels.
-template <typename S>
-MarchPlan phase_march_plan(const PhaseK& k) {
+template <typename S, typename C>
+MarchPlan march_plan(const PhaseK& k) {
     MarchPlan best{};
     int dev = 0, cus = 0;
     if (!phase_march_fits(k) || hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         return best;
-    constexpr bool F32 = sizeof(S) == 4;
-    const double lam = F32 ? 0.61 : 0.915, row0 = F32 ? 0.79 : 0.4, beta = F32 ? 0.417 : 1.04;
-    const double t0 = F32 ? 5.7 : 1.9, one_wave = F32 ? 0.82 : 1.0, four_waves = F32 ? 1.14 : 1.55;
+    constexpr bool F32 = sizeof(C) == 4;
+    constexpr bool A64 = !F32 && sizeof(S) == 4;
+    const double lam = F32 ? 0.61 : A64 ? 0.76 : 0.915, row0 = F32 ? 0.79 : A64 ? 0.98 : 0.4;
+    const double beta = F32 ? 0.417 : A64 ? 0.83 : 1.04, t0 = F32 ? 5.7 : A64 ? 8.9 : 1.9;
+    const double one_wave = F32 ? 0.82 : A64 ? 0.6 : 1.0, four_waves = F32 ? 1.14 : A64 ? 0.88 : 1.55;
     const double plane = double(PhasePlanes<S>::NPL) * sizeof(S);
     const double state = double(k.nx) * k.ny * k.batch * plane;
-    const double bw = 2 * state < 3e8 ? (F32 ? 19.6e6 : 14.3e6) : (F32 ? 9.2e6 : 9.7e6);  // bytes per us
+    const double near = F32 ? 19.6e6 : A64 ? 40e6 : 14.3e6, far = F32 ? 9.2e6 : A64 ? 10e6 : 9.7e6;
+    const double bw = 2 * state < 3e8 ? near : far;  // bytes per us
     for (int lanes = 64; lanes <= 256; lanes *= 2) {
         // rows in one tile of the fewest lanes, longer ones in tiles of 128 or 256
         if (k.nx <= 256 ? lanes < k.nx || (lanes > 64 && lanes / 2 >= k.nx) : lanes == 64) continue;
@@ -370,8 +382,8 @@ MarchPlan phase_march_plan(const PhaseK& k) {
         const double row_bytes = 2.0 * std::min(k.nx, lanes) * plane;
         for (int K = 2; K <= (F32 ? 3 : 2); ++K) {
             const int resident = resident_workgroups(
-                K == 2 ? (const void*)phase_march_kernel<S, 2>(k, lanes)
-                       : (const void*)phase_march_kernel<S, F32 ? 3 : 2>(k, lanes), waves);
+                K == 2 ? (const void*)phase_march_kernel<S, C, 2>(k, lanes)
+                       : (const void*)phase_march_kernel<S, C, F32 ? 3 : 2>(k, lanes), waves);
             if (resident < 1) continue;
             const double chain = std::pow(row0 + K * lam * (waves == 1 ? one_wave : waves == 2 ? 1 : four_waves), 3);
             const long long column = (long long)phase_march_tiles(k, lanes, K) * k.batch;
@@ -394,22 +406,28 @@ MarchPlan phase_march_plan(const PhaseK& k) {
     return best;
 }
 
+template <typename S>
+MarchPlan phase_march_plan(const PhaseK& k, bool arith64) {
+    return arith64 ? march_plan<S, double>(k) : march_plan<S, S>(k);
+}
+
 // K steps in one launch; the whole state (populations and (phi u)) moves from
 // buffer a to buffer b.
 template <typename S>
-hipError_t launch_phase_march(const PhaseK& k, int K, int lanes, int nseg, const S* a, S* b,
+hipError_t launch_phase_march(const PhaseK& k, int K, int lanes, int nseg, bool arith64, const S* a, S* b,
                               hipStream_t s) {
     if (!phase_march_fits(k)) return hipErrorInvalidValue;
-    if (K == 2) return phase_march_launch<S, 2>(k, lanes, nseg, a, b, s);
+    if (arith64) return K == 2 ? phase_march_launch<S, double, 2>(k, lanes, nseg, a, b, s) : hipErrorInvalidValue;
+    if (K == 2) return phase_march_launch<S, S, 2>(k, lanes, nseg, a, b, s);
     if constexpr (sizeof(S) == 4)
-        if (K == 3) return phase_march_launch<S, 3>(k, lanes, nseg, a, b, s);
+        if (K == 3) return phase_march_launch<S, S, 3>(k, lanes, nseg, a, b, s);
     return hipErrorInvalidValue;
 }
 
 #define LBM_PMARCH_INST(S)                                                                         \
-    template MarchPlan phase_march_plan<S>(const PhaseK&);                                         \
-    template hipError_t launch_phase_march<S>(const PhaseK&, int, int, int, const S*, S*, \
-                                                 hipStream_t);
+    template MarchPlan phase_march_plan<S>(const PhaseK&, bool);                                   \
+    template hipError_t launch_phase_march<S>(const PhaseK&, int, int, int, bool, const S*, S*,    \
+                                              hipStream_t);
 LBM_PMARCH_INST(float)
 LBM_PMARCH_INST(double)
 

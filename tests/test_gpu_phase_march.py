@@ -50,16 +50,26 @@ def test_marching_phase_kernel_bit_identical(case):
     _compare(_state(case, 1), _state(case, 2))
 
 
-@pytest.mark.parametrize("prec", ["fp32", "fp64"])
-def test_automatic_choice_on_a_batch(prec):
-    case = ("auto", 256, 256, 32, False, prec, {})
-    print_case(test="phase-march-auto", prec=prec)
+@pytest.mark.parametrize("nx,ny,batch,walls,prec", [
+    (256, 256, 32, False, "fp32"),
+    (256, 256, 32, False, "fp64"),
+    # FP64 arithmetic on the FP32 state: whole rows of one, two and four waves, tiles
+    (256, 256, 32, False, "fp32_arith64"),
+    (61, 64, 400, True, "fp32_arith64"),
+    (100, 130, 130, True, "fp32_arith64"),
+    (601, 500, 5, False, "fp32_arith64"),
+    (512, 800, 4, True, "fp32_arith64"),
+])
+def test_automatic_choice_on_grids_that_fill_the_gpu(nx, ny, batch, walls, prec):
+    case = ("auto", nx, ny, batch, walls, prec, {})
+    print_case(test="phase-march-auto", nx=nx, ny=ny, batch=batch, prec=prec)
     _compare(_state(case, 1), _state(case, 0))
 
 
 @pytest.mark.parametrize("kind,nx,ny,batch,prec,steps", [
     ("phase", 256, 256, 32, "fp32", 2),   # single steps: two swaps
     ("phase", 256, 256, 128, "fp32", 4),  # pairs: two swaps
+    ("phase", 256, 256, 128, "fp32_arith64", 2),  # always single steps
     ("channel", 4096, 500, 1, "fp64", 2),
 ])
 def test_captured_steps_of_automatic_mode_replay(kind, nx, ny, batch, prec, steps):
