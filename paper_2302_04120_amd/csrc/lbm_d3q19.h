@@ -113,5 +113,27 @@ __host__ __device__ __forceinline__ void inverse19(const C m[19], C f[19]) {
     }
 }
 
+// Neighbours of a lane in the LDS plane of a tile of k_d3_tb2: the tile's wc columns
+// with one of overlap on either side (none where the tile is as wide as the grid and
+// its rows wrap: whole) in rh rows, overlap included.  A lane at column rx (-1 .. wc)
+// of row ry sits at t; the values it pulls lie at t plus these offsets, 0 where the
+// region ends (or an x wall ends a whole row: xlo, xhi).  Lanes that hold no node
+// (in false: the last wave's rest) sit at t = 0 and pull from there, never beside the
+// plane: what they pull is not used, but it is read.
+struct TileOffsets {
+    int om, op, od, ou;  // to x - 1, x + 1, y - 1, y + 1
+};
+__host__ __device__ __forceinline__ TileOffsets tile_offsets(bool in, bool whole, int rx, int ry,
+                                                             int wc, int rh, bool xlo, bool xhi) {
+    if (!in) return TileOffsets{0, 0, 0, 0};
+    const int rw = whole ? wc : wc + 2;
+    TileOffsets o;
+    o.om = rx > (whole ? 0 : -1) ? -1 : whole && !xlo ? wc - 1 : 0;
+    o.op = rx < (whole ? wc - 1 : wc) ? 1 : whole && !xhi ? 1 - wc : 0;
+    o.od = ry > 0 ? -rw : 0;
+    o.ou = ry < rh - 1 ? rw : 0;
+    return o;
+}
+
 }  // namespace
 }  // namespace lbm

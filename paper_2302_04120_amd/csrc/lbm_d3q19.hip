@@ -244,10 +244,7 @@ __global__ __launch_bounds__(NT) void k_d3_tb2(const D3Tb2Args<S> p, const S* __
     const bool ylo = k.bcy && y == 0, yhi = k.bcy && y == ny - 1;
     const bool edge = xlo || xhi || ylo || yhi;
     const bool plain = !__any(edge);  // no lane of this wave stands at an x or y wall
-    // LDS offsets to the neighbours (0 where there is none in the region)
-    const int om = rx > (whole ? 0 : -1) ? -1 : whole && !xlo ? wc - 1 : 0;
-    const int op = rx < (whole ? wc - 1 : wc) ? 1 : whole && !xhi ? 1 - wc : 0;
-    const int od = in && ry > 0 ? -rw : 0, ou = ry < rh - 1 ? rw : 0;
+    const TileOffsets off = tile_offsets(in, whole, rx, ry, wc, rh, xlo, xhi);
     const int plane = nx * ny;
     const long long base = (long long)b * nz * plane;
     auto zof = [&](int v) { return v < 0 ? v + nz : (v >= nz ? v - nz : v); };
@@ -277,8 +274,8 @@ __global__ __launch_bounds__(NT) void k_d3_tb2(const D3Tb2Args<S> p, const S* __
                (E3Y[j] > 0 ? ylo : E3Y[j] < 0 ? yhi : false);
     };
     auto pull = [&](const C(&xb)[16][NT], int j) {
-        return xb[d3_plane(j)][t + (E3X[j] > 0 ? om : E3X[j] < 0 ? op : 0) +
-                               (E3Y[j] > 0 ? od : E3Y[j] < 0 ? ou : 0)];
+        return xb[d3_plane(j)][t + (E3X[j] > 0 ? off.om : E3X[j] < 0 ? off.op : 0) +
+                               (E3Y[j] > 0 ? off.od : E3Y[j] < 0 ? off.ou : 0)];
     };
 
     const int s1 = k.bcz ? max(a - 1, 0) : a - 1;   // first plane of step n
