@@ -335,7 +335,8 @@ LBM_API lbm_status lbm_set_step_fusion(lbm_ctx* ctx, int mode);
  *   LBM_M_T (K), LBM_M_PHI, LBM_M_MU (chemical potential, Pa), LBM_M_UZ (m/s,
  *   3D lattices).  LBM_D3Q19_PHASE offers RHO, P, UX, UY, UZ, PHI and MU.
  * out_on_device != 0: out is a device pointer (written on the stream,
- * asynchronous); otherwise a host pointer (synchronous). */
+ * asynchronous; the context's own GPU by the kernels, other memory by a copy);
+ * otherwise a host pointer (synchronous). */
 enum { LBM_M_RHO = 1, LBM_M_P = 2, LBM_M_UX = 4, LBM_M_UY = 8, LBM_M_T = 16,
        LBM_M_PHI = 32, LBM_M_MU = 64, LBM_M_UZ = 128 };
 LBM_API lbm_status lbm_macros(lbm_ctx* ctx, unsigned mask, double* out, int out_on_device);

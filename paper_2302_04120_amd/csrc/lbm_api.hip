@@ -1256,11 +1256,17 @@ lbm_status lbm_macros(lbm_ctx* c, unsigned mask, double* out, int out_on_device)
     hipError_t e;
     const bool f64 = c->desc.prec == LBM_FP64;
     char* a = bufA(c);
-    // the kernels write the wanted fields only, for the device straight into out
+    // the kernels write the wanted fields only, into this GPU's memory straight away
     // (256 x 256 x 128 D3Q19: 285 us by way of the staging planes, 175 us so)
+    bool direct = false;
+    if (out_on_device) {
+        hipPointerAttribute_t at{};
+        if (hipPointerGetAttributes(&at, out) == hipSuccess) direct = kernel_may_write(at, c->device);
+        else (void)hipGetLastError();  // not an error of this call: the copy below reports its own
+    }
     MacroOut mo;
     for (int bit = 0, k = 0; bit < 8; ++bit)
-        if (mask & (1u << bit)) mo.p[bit] = out_on_device ? out + (size_t)k++ * N : c->staging + bit * P;
+        if (mask & (1u << bit)) mo.p[bit] = direct ? out + (size_t)k++ * N : c->staging + bit * P;
     if (lat == LBM_D3Q19) {
         if (f64) e = launch_d3_macros<double>(c->d3k, (double*)a, mo, c->stream);
         else e = launch_d3_macros<float>(c->d3k, (float*)a, mo, c->stream);
@@ -1278,10 +1284,10 @@ lbm_status lbm_macros(lbm_ctx* c, unsigned mask, double* out, int out_on_device)
     }
     if (e != hipSuccess) return hip_fail(c, e, "macros kernel");
     int k = 0;
-    for (int bit = 0; bit < 8 && !out_on_device; ++bit) {
+    for (int bit = 0; bit < 8 && !direct; ++bit) {
         if (!(mask & (1u << bit))) continue;
         e = hipMemcpyAsync(out + (size_t)k * N, c->staging + bit * P, N * sizeof(double),
-                           hipMemcpyDeviceToHost, c->stream);
+                           out_on_device ? hipMemcpyDefault : hipMemcpyDeviceToHost, c->stream);
         if (e != hipSuccess) return hip_fail(c, e, "macros copy");
         ++k;
     }

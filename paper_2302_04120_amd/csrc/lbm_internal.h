@@ -131,6 +131,13 @@ struct MacroOut {
     }
 };
 
+// Whether kernels on GPU `device` may write to memory of these attributes straight
+// away: its own device memory.  Another GPU's needs peer access that nobody need have
+// enabled, and host memory that is not registered faults; a copy reaches all of them.
+inline bool kernel_may_write(const hipPointerAttribute_t& a, int device) {
+    return a.type == hipMemoryTypeDevice && a.device == device;
+}
+
 // Expected time of a single channel step that reads and writes that many bytes,
 // in us (measured: 5.2 us on 800 x 40, 22.2 us on 3000 x 300, 182 us on 8192 x 1024
 // in FP32).
