@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -200,36 +201,37 @@ lbm_status hip_fail(lbm_ctx* c, hipError_t e, const char* where) {
     return set_err(c, LBM_E_DEVICE, std::string(where) + ": " + hipGetErrorString(e));
 }
 
-// Largest speed in a velocity component, in units of the lattice speed c = dx/dt;
-// a NaN counts as above every limit.  Blocks without a NaN go eight values at a
-// time (one after the other is a chain of compares, 1.3 ns each).
-double speed_over_c(const double* u, long long n, double dt_over_dx) {
-    double m = 0.0;
-    if (!u) return m;
-    constexpr long long kBlock = 1024;
-    for (long long i0 = 0; i0 < n; i0 += kBlock) {
-        const long long i1 = std::min(n, i0 + kBlock);
-        double top[8] = {};
-        long long i = i0;
-        bool nan = false;
-        for (; i + 8 <= i1; i += 8)
-            for (int k = 0; k < 8; ++k) {
-                const double a = std::fabs(u[i + k]) * dt_over_dx;
-                top[k] = a > top[k] ? a : top[k];
-                nan |= a != a;
-            }
-        if (nan) {
-            i = i0;  // in order: the values after a NaN decide
-        } else {
-            for (double a : top)
-                if (!(a <= m)) m = a;
-        }
-        for (; i < i1; ++i) {
-            const double a = std::fabs(u[i]) * dt_over_dx;
-            if (!(a <= m)) m = a;
-        }
-    }
-    return m;
+// Largest speed in velocity components, in units of the lattice speed c = dx/dt, and
+// whether any value is NaN.  (A NaN in the last place of the first component is the
+// largest itself: its warning has always said so.)
+struct Speed {
+    double top = 0.0;
+    bool nan = false;
+};
+// Eight values at a time: one after the other is a chain of compares, 1.3 ns each.
+void speed_over_c(const double* u, long long n, double dt_over_dx, Speed* s) {
+    if (!u || n < 1) return;
+    double top[8] = {};
+    bool nan = false;
+    auto take = [&](long long i, int k) {
+        const double a = std::fabs(u[i]) * dt_over_dx;
+        top[k] = a > top[k] ? a : top[k];  // a NaN compares false
+        nan |= a != a;
+    };
+    long long i = 0;
+    for (; i + 8 <= n; i += 8)
+        for (int k = 0; k < 8; ++k) take(i + k, k);
+    for (; i < n; ++i) take(i, 0);
+    for (double a : top)
+        if (a > s->top) s->top = a;
+    s->nan |= nan;
+}
+Speed speed_over_c(std::initializer_list<const double*> u, long long n, double dt_over_dx) {
+    Speed s;
+    for (const double* v : u) speed_over_c(v, n, dt_over_dx, &s);
+    const double* first = *u.begin();
+    if (first && n > 0 && std::isnan(first[n - 1])) s.top = first[n - 1];
+    return s;
 }
 
 // Speed limit of the warning, in units of c = dx/dt.  The equilibria are expanded
@@ -237,13 +239,18 @@ double speed_over_c(const double* u, long long n, double dt_over_dx) {
 // (Ma = u / c_s = 0.52) a step is neither accurate nor reliably stable.
 constexpr double kMachLimit = 0.3;
 
-// Informational LBM_W_MACH when a given speed reaches kMachLimit of c.
-lbm_status mach_status(lbm_ctx* c, double u_over_c, const char* what) {
-    if (u_over_c <= kMachLimit) return LBM_OK;
+// Informational LBM_W_MACH when a given speed reaches kMachLimit of c or is NaN.
+lbm_status mach_status(lbm_ctx* c, const Speed& s, const char* what) {
     char m[200];
-    std::snprintf(m, sizeof m, "%s: max |u| dt / dx = %.3g above %.2g (Ma = |u| / c_s = %.3g); "
-                  "the second-order equilibria lose accuracy and stability", what, u_over_c,
-                  kMachLimit, u_over_c * std::sqrt(3.0));
+    if (!(s.top <= kMachLimit))
+        std::snprintf(m, sizeof m, "%s: max |u| dt / dx = %.3g above %.2g (Ma = |u| / c_s = %.3g); "
+                      "the second-order equilibria lose accuracy and stability", what, s.top,
+                      kMachLimit, s.top * std::sqrt(3.0));
+    else if (s.nan)
+        std::snprintf(m, sizeof m, "%s: holds NaN (the other values reach |u| dt / dx = %.3g)", what,
+                      s.top);
+    else
+        return LBM_OK;
     return set_err(c, LBM_W_MACH, m);
 }
 
@@ -1009,7 +1016,7 @@ lbm_status lbm_set_params_SI(lbm_ctx* c, const lbm_params_si* p) {
         msg = m;
     }
     if (d.lattice == LBM_D2Q9_D2Q5 && (d.flags & LBM_FLAG_FLOW) && d.bc[0] == LBM_BC_VEL_INLET &&
-        mach_status(c, speed_over_c(p->inlet_u, d.ny, dt / dx), "inlet profile") != LBM_OK) {
+        mach_status(c, speed_over_c({p->inlet_u}, d.ny, dt / dx), "inlet profile") != LBM_OK) {
         warn |= LBM_W_MACH;
         msg = msg.empty() ? c->err : msg + "; " + c->err;
     }
@@ -1075,8 +1082,7 @@ lbm_status lbm_init_fields(lbm_ctx* c, const double* rho_or_p, const double* ux,
         else
             e = launch_phase_init<float>(c->pk, c->staging, (float*)c->popA, c->stream);
     }
-    const double r = c->dt / c->dx;
-    const double speed = std::max(speed_over_c(ux, N, r), speed_over_c(uy, N, r));  // meanwhile
+    const Speed speed = speed_over_c({ux, uy}, N, c->dt / c->dx);  // meanwhile
     const hipError_t done = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "init kernel");
     if (done != hipSuccess) return hip_fail(c, done, "init");
@@ -1118,9 +1124,7 @@ lbm_status lbm_init_fields3d(lbm_ctx* c, const double* rho_or_p, const double* u
     else
         e = f64 ? launch_p3_init<double>(c->p3k, c->staging, (double*)c->popA, c->stream)
                 : launch_p3_init<float>(c->p3k, c->staging, (float*)c->popA, c->stream);
-    const double r = c->dt / c->dx;
-    const double speed = std::max({speed_over_c(ux, N, r), speed_over_c(uy, N, r),
-                                   speed_over_c(uz, N, r)});  // meanwhile
+    const Speed speed = speed_over_c({ux, uy, uz}, N, c->dt / c->dx);  // meanwhile
     const hipError_t done = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "init kernel");
     if (done != hipSuccess) return hip_fail(c, done, "init");
