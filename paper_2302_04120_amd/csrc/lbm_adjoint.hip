@@ -548,17 +548,9 @@ hipError_t launch_adj_step(const ChanK& k, const AdjK& a, const S* st, const S* 
     return k.Ft[0] != 0.0 || k.Ft[1] != 0.0 ? go(k_adj_step<S, true>) : go(k_adj_step<S, false>);
 }
 
-// A reverse step is three times the arithmetic of a forward one (600 VALU
-// instructions a node in FP32 without a body force), so the overlap weighs
-// more: the many-steps kernel is taken while the plan puts at most four waves
-// on a SIMD, two in FP64.  Measured per reverse step with its share of the
-// recomputed tape, single -> many: 1600 x 80 FP32 (four waves) 13.8 -> 12.0 us,
-// 300 x 20 10.7 -> 7.8 us; 1600 x 80 FP64 (eight) 21.2 -> 21.9 us.
 template <typename S>
 bool adj_multi_fast(const ChanK& k, const ChanMultiPlan& plan) {
-    const long long waves = (chan_multi_region(k, plan, plan.steps) + 63) / 64;
-    const long long tiles = (long long)plan.ntx * plan.nty;
-    return (tiles + 255) / 256 * waves <= (sizeof(S) == 4 ? 16 : 8);
+    return adj_multi_pays(plan, (chan_multi_region(k, plan, plan.steps) + 63) / 64, sizeof(S));
 }
 
 // The many-steps reverse kernel takes the tiles of the channel's plan (the grid

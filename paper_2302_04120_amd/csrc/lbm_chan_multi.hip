@@ -299,6 +299,7 @@ ChanMultiPlan chan_multi_plan(const ChanK& k) {
                 if (cost < best_cost) {
                     best_cost = best.cost = cost;
                     best.steps = h;
+                    best.cus = cus;
                     best.ntx = ntx;
                     best.nty = nty;
                 }

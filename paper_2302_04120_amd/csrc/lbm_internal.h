@@ -159,7 +159,20 @@ constexpr int kChanMultiMax = 16;
 struct ChanMultiPlan {
     int steps = 0, ntx = 0, nty = 0;
     double cost = 0.0;  // expected time of a step (us)
+    int cus = 0;        // compute units it was made for
 };
+
+// Whether the many-steps reverse kernel beats single reverse steps on a plan's tiles,
+// `waves` waves each.  A reverse step is three times the arithmetic of a forward one
+// (600 VALU instructions a node in FP32 without a body force), so the overlap weighs
+// more: it is taken while the plan puts at most four waves on a SIMD, two in FP64.
+// Measured per reverse step with its share of the recomputed tape, single -> many:
+// 1600 x 80 FP32 (four waves) 13.8 -> 12.0 us, 300 x 20 10.7 -> 7.8 us; 1600 x 80 FP64
+// (eight) 21.2 -> 21.9 us.
+inline bool adj_multi_pays(const ChanMultiPlan& p, long long waves, size_t value_bytes) {
+    const long long tiles = (long long)p.ntx * p.nty;
+    return p.cus > 0 && (tiles + p.cus - 1) / p.cus * waves <= (value_bytes == 4 ? 16 : 8);
+}
 
 // Steps per launch (2 to 4) and row segments per replica of a marching 2D kernel,
 // with the expected time of a step (us); steps 0: not usable.
