@@ -323,6 +323,20 @@ LBM_API lbm_status lbm_set_graph_steps(lbm_ctx* ctx, int steps);
  * mode. */
 LBM_API lbm_status lbm_set_step_fusion(lbm_ctx* ctx, int mode);
 
+/* The launches that a long lbm_step call goes through with the present parameters
+ * and step fusion mode (as lbm_set_step_fusion describes; while the caller captures
+ * the stream, those of the capture).  Not an operation of the paper: it tells a
+ * benchmark or a test what was timed or compared.  LBM_E_STATE before
+ * lbm_set_params_SI. */
+typedef struct {
+    const char* kernel;   /* name of the kernel, without template arguments (static storage) */
+    int steps;            /* steps per launch at most; 0: all steps of a call in one launch  */
+    int threads;          /* per workgroup; 0 for the single-step kernels                    */
+    int tiles_x, tiles_y; /* tiles per replica (of one plane or row segment); 0 likewise     */
+    int segments;         /* row or plane segments per replica; 0 where tiles do not march   */
+} lbm_step_plan;
+LBM_API lbm_status lbm_query_step_plan(const lbm_ctx* ctx, lbm_step_plan* plan);
+
 /* Macroscopic fields of the current state, evaluated in FP64 from the stored
  * populations: rho = sum f_i (Eq. zero_moment_f), u = (sum c_i f_i + dt F/2) /
  * rho (Eq. first_moment_f), T = sum g_i + dt qdot/2 (Eq. zero_moment_g); for

@@ -710,7 +710,7 @@ lbm_status lbm_set_step_fusion(lbm_ctx* c, int mode) {
         return set_err(c, LBM_E_UNSUPPORTED,
                        "many-steps kernel needs at most 16 tiles of 512 nodes over all replicas");
     if (mode == 2 && c->desc.lattice == LBM_D2Q9_PHASE && c->desc.prec == LBM_FP32_DEV_ARITH64)
-        return set_err(c, LBM_E_UNSUPPORTED, "marching kernel: not with FP64 arithmetic on FP32 storage");
+        return set_err(c, LBM_E_UNSUPPORTED, "step fusion mode 2 is not offered with FP64 arithmetic on FP32 storage");
     if (mode == 2 && c->desc.lattice == LBM_D2Q9_D2Q5 && c->has_params && !chan_march_fits(c->ck))
         return set_err(c, LBM_E_UNSUPPORTED,
                        "marching channel kernel: needs both flow and temperature");
@@ -719,6 +719,59 @@ lbm_status lbm_set_step_fusion(lbm_ctx* c, int mode) {
         drop_graphs(c);
         c->fusion = mode;
     }
+    return LBM_OK;
+}
+
+lbm_status lbm_query_step_plan(const lbm_ctx* c, lbm_step_plan* plan) {
+    if (!c || !plan) return LBM_E_ARG;
+    if (!c->has_params) return LBM_E_STATE;
+    auto waves = [](long long threads) { return int((threads + 63) / 64 * 64); };
+    auto march_steps = [&](const MarchPlan& m) { return caller_captures(c) ? 2 : m.steps; };
+    lbm_step_plan p{};
+    p.steps = 1;
+    switch (c->desc.lattice) {
+        case LBM_D1Q2:
+        case LBM_D1Q3:
+            p.kernel = "k_d1";
+            p.steps = 0;
+            break;
+        case LBM_D2Q9_D2Q5:
+            p.kernel = "k_chan_step";
+            if (use_march(c))
+                p = {"k_chan_march", march_steps(c->cmarch), c->cmarch.lanes,
+                     chan_march_tiles(c->ck, march_steps(c->cmarch)), 1, c->cmarch.nseg};
+            else if (use_chan_multi(c))
+                p = {"k_chan_multi", c->cmulti.steps,
+                     waves(chan_multi_region(c->ck, c->cmulti, c->cmulti.steps)), c->cmulti.ntx,
+                     c->cmulti.nty, 0};
+            break;
+        case LBM_D2Q9_PHASE:
+            p.kernel = "k_phase";
+            if (use_persist(c))
+                p = {"k_phase_persist", kPersistChunk, 0, 0, 0, 0};
+            else if (use_march(c))
+                p = {"k_phase_march", march_steps(c->pmarch),
+                     phase_march_threads(c->pk, c->pmarch.lanes),
+                     phase_march_tiles(c->pk, c->pmarch.lanes, march_steps(c->pmarch)), 1,
+                     c->pmarch.nseg};
+            else if (use_phase_multi(c))
+                p = {"k_phase_multi", c->pmulti.steps,
+                     waves(phase_multi_region(c->pk, c->pmulti, c->pmulti.steps)), c->pmulti.ntx,
+                     c->pmulti.nty, 0};
+            break;
+        case LBM_D3Q19:
+            p.kernel = "k_d3_step";
+            if (use_d3_tb2(c))
+                p = {"k_d3_tb2", 2, waves(d3_tb2_threads(c->d3k, c->d3tb2)), c->d3tb2.ntx,
+                     c->d3tb2.nty, c->d3tb2.nseg};
+            break;
+        default:
+            p.kernel = "k_p3_step";
+            if (c->fusion != 1 && c->p3march.ntx > 0)
+                p = {"k_p3_march", 1, waves(p3_march_threads(c->p3k, c->p3march)), c->p3march.ntx,
+                     c->p3march.nty, c->p3march.nseg};
+    }
+    *plan = p;
     return LBM_OK;
 }
 

@@ -300,10 +300,6 @@ bool march_aligned(const ChanK& k) {
     return k.nx % kBlk == 0 && (long long)k.nx * march_nv(k.tq) * (long long)sizeof(S) < (1LL << 31);
 }
 
-int march_tiles(const ChanK& k, int K) {
-    return (k.nx + kMarchLanes - 2 * K - 1) / (kMarchLanes - 2 * K);
-}
-
 // The instance for a configuration (FP64 up to three steps: four fill the LDS).
 template <typename S, int K>
 auto march_kernel(const ChanK& k) {
@@ -321,7 +317,7 @@ auto march_kernel(const ChanK& k) {
 template <typename S, int K>
 hipError_t march_launch(const ChanK& k, const S* a, S* b, const S* qw, const S* uin, const S* tin,
                         const double* mods, int nseg, hipStream_t s) {
-    const int ntx = march_tiles(k, K);
+    const int ntx = chan_march_tiles(k, K);
     const long long wgs = (long long)ntx * nseg * k.batch;
     if (nseg < 1 || nseg > k.ny || wgs >= (1 << 21)) return hipErrorInvalidValue;
     ChanMarchArgs<S, K> p{};
@@ -337,6 +333,10 @@ hipError_t march_launch(const ChanK& k, const S* a, S* b, const S* qw, const S* 
 }
 
 }  // namespace
+
+int chan_march_tiles(const ChanK& k, int K) {
+    return (k.nx + kMarchLanes - 2 * K - 1) / (kMarchLanes - 2 * K);
+}
 
 // The marching kernel covers flow with temperature (D2Q5 or the D2Q9 set, with
 // or without the Boussinesq force) and every boundary of the channel lattice.
@@ -379,7 +379,7 @@ MarchPlan chan_march_plan(const ChanK& k) {
                              : K == 3 ? resident_workgroups((const void*)march_kernel<S, 3>(k), 4)
                                       : resident_workgroups((const void*)march_kernel<S, F32 ? 4 : 3>(k), 4);
         if (resident < 1) continue;
-        const long long column = (long long)march_tiles(k, K) * k.batch, cap = (long long)cus * resident;
+        const long long column = (long long)chan_march_tiles(k, K) * k.batch, cap = (long long)cus * resident;
         for (int seg = k.ny; seg >= 1; --seg) {
             const int nseg = (k.ny + seg - 1) / seg;
             if (seg > 1 && (k.ny + seg - 2) / (seg - 1) == nseg) continue;  // shorter, the same count

@@ -443,11 +443,6 @@ bool d3_tb2_aligned(const D3K& k) {
     const long long plane = (long long)k.nx * k.ny;
     return plane % kBlk == 0 && plane * 19 * (long long)sizeof(S) < (1LL << 31);
 }
-// threads of a plan's widest tile
-long long d3_tb2_threads(const D3K& k, const D3Tb2Plan& p) {
-    return (long long)((k.nx + p.ntx - 1) / p.ntx + (p.ntx > 1 ? 2 : 0)) *
-           ((k.ny + p.nty - 1) / p.nty + 2);
-}
 template <typename S>
 constexpr int d3_max_threads() {
     return sizeof(S) == 4 ? 1024 : 512;
@@ -462,6 +457,11 @@ auto d3_tb2_kernel(bool aligned, int threads) {
 }
 
 }  // namespace
+
+long long d3_tb2_threads(const D3K& k, const D3Tb2Plan& p) {
+    return (long long)((k.nx + p.ntx - 1) / p.ntx + (p.ntx > 1 ? 2 : 0)) *
+           ((k.ny + p.nty - 1) / p.nty + 2);
+}
 
 // Tiles and segments by a cost model fitted to 1200 plans on 30 boxes of 0.1 M
 // to 17 M nodes (10 %; its choice runs 3 to 4 % behind the best measured plan on

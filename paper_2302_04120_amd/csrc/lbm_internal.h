@@ -306,6 +306,7 @@ hipError_t launch_chan_step(const ChanK& k, const S* a, S* b, const S* qw, const
 // where chan_march_fits; mods: the wall-flux modulation of each step, nseg: row
 // segments per replica (chan_march_plan, made with the parameters)
 bool chan_march_fits(const ChanK& k);
+int chan_march_tiles(const ChanK& k, int K);  // x-tiles per row
 template <typename S>
 MarchPlan chan_march_plan(const ChanK& k);
 template <typename S>
@@ -335,11 +336,15 @@ hipError_t launch_phase_step(const PhaseK& k, const S* a, S* b, bool arith64, hi
 // gives steps 0 where another kernel is faster
 template <typename S>
 PhaseMultiPlan phase_multi_plan(const PhaseK& k, bool arith64);
+long long phase_multi_region(const PhaseK& k, const PhaseMultiPlan& p, int steps);
 template <typename S>
 hipError_t launch_phase_multi(const PhaseK& k, const PhaseMultiPlan& plan, const S* a, S* b,
                               bool arith64, int nsteps, hipStream_t s);
 // several steps in one launch (plan.steps, in FP64 two): a to b
 bool phase_march_fits(const PhaseK& k);
+// x-tiles per row and threads of a workgroup
+int phase_march_tiles(const PhaseK& k, int lanes, int K);
+int phase_march_threads(const PhaseK& k, int lanes);
 template <typename S>
 MarchPlan phase_march_plan(const PhaseK& k, bool arith64);
 template <typename S>
@@ -379,6 +384,7 @@ hipError_t launch_d3_step(const D3K& k, const S* fc, S* fn, hipStream_t s);
 // two steps in one launch; d3_tb2_plan gives ntx 0 where single steps are faster
 template <typename S>
 D3Tb2Plan d3_tb2_plan(const D3K& k);
+long long d3_tb2_threads(const D3K& k, const D3Tb2Plan& p);  // of a plan's widest tile
 template <typename S>
 hipError_t launch_d3_tb2(const D3K& k, const D3Tb2Plan& plan, const S* fc, S* fn, hipStream_t s);
 template <typename S>
@@ -393,6 +399,7 @@ hipError_t launch_d3_macros(const D3K& k, const S* f, const MacroOut& out, hipSt
 // of h_0 at 38 (FP32 only), then (phi u) of the previous step (3 planes).
 template <typename S>
 P3MarchPlan p3_march_plan(const P3K& k);
+long long p3_march_threads(const P3K& k, const P3MarchPlan& p);  // of a plan's widest tile
 template <typename S>
 hipError_t launch_p3_step(const P3K& k, const P3MarchPlan& plan, const S* a, S* b, S* phi,
                           hipStream_t s);

@@ -648,6 +648,11 @@ constexpr int p3_max_core() {
 
 }  // namespace
 
+long long p3_march_threads(const P3K& k, const P3MarchPlan& p) {
+    return (long long)((k.nx + p.ntx - 1) / p.ntx + (p.ntx > 1 ? 2 : 0)) *
+           ((k.ny + p.nty - 1) / p.nty + 2);
+}
+
 // Tiles and segments by a cost model fitted to 600 plans on 15 boxes of 0.1 M to
 // 7 M nodes (11-15 %; its choice runs within 5 % of the best measured plan on 13
 // of them, within 25 % on all).  A plane step takes the cubic mean of
@@ -713,7 +718,7 @@ namespace {
 template <typename S>
 hipError_t launch_p3_march(const P3K& k, const P3MarchPlan& plan, const S* a, S* b, hipStream_t s) {
     const long long w = (k.nx + plan.ntx - 1) / plan.ntx, h = (k.ny + plan.nty - 1) / plan.nty;
-    const long long threads = (w + (plan.ntx > 1 ? 2 : 0)) * (h + 2);
+    const long long threads = p3_march_threads(k, plan);
     const long long wgs = (long long)plan.ntx * plan.nty * plan.nseg * k.batch;
     if (threads > p3_max_threads<S>() || w * h > p3_max_core<S>() || wgs < 1 || wgs >= (1 << 21) ||
         plan.nseg > k.nz || k.nx < 2 || k.ny < 2 || k.nz < 2)

@@ -310,9 +310,6 @@ auto phase_march_kernel(const PhaseK& k, int lanes) {
            : lanes == 128 ? (Kernel)phase_march_kernel<S, C, 128, K>(k)
                           : (Kernel)phase_march_kernel<S, C, 256, K>(k);
 }
-int phase_march_tiles(const PhaseK& k, int lanes, int K) {
-    return k.nx <= lanes ? 1 : (k.nx + lanes - 4 * K - 1) / (lanes - 4 * K);
-}
 // waves of a workgroup: those of the row's columns, or all of a tile's lanes
 int phase_march_waves(const PhaseK& k, int lanes) { return std::min((k.nx + 63) / 64, lanes / 64); }
 
@@ -338,6 +335,10 @@ hipError_t phase_march_launch(const PhaseK& k, int lanes, int nseg, const S* a, 
 }  // namespace
 
 bool phase_march_fits(const PhaseK& k) { return k.ny >= 4 && k.nx >= 1; }
+int phase_march_tiles(const PhaseK& k, int lanes, int K) {
+    return k.nx <= lanes ? 1 : (k.nx + lanes - 4 * K - 1) / (lanes - 4 * K);
+}
+int phase_march_threads(const PhaseK& k, int lanes) { return 64 * phase_march_waves(k, lanes); }
 
 // Lanes per workgroup, steps per launch and segments by a cost model fitted to 1900
 // plans on 60 grids of 0.2 M to 12 M nodes (5 %; its choice runs within 4 % of the

@@ -250,6 +250,10 @@ hipError_t pm_launch(const PhaseK& k, const PhaseMultiPlan& plan, const S* a, S*
 
 }  // namespace
 
+long long phase_multi_region(const PhaseK& k, const PhaseMultiPlan& p, int steps) {
+    return p.ntx > 0 && p.nty > 0 ? pm_region(k, p.ntx, p.nty, 2 * steps) : 0;
+}
+
 template <typename S>
 PhaseMultiPlan phase_multi_plan(const PhaseK& k, bool arith64) {
     return arith64 ? pm_plan<S, double>(k) : pm_plan<S, S>(k);

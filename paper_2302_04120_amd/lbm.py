@@ -44,7 +44,7 @@ EXPORTS = ("lbm_query_bytes", "lbm_create", "lbm_destroy", "lbm_set_params_SI",
            "lbm_query_record_bytes", "lbm_record", "lbm_grad", "lbm_time",
            "lbm_save_state", "lbm_load_state", "lbm_last_error", "lbm_set_graph_steps",
            "lbm_set_step_fusion", "lbm_init_fields3d", "lbm_reduce_noalloc",
-           "lbm_set_nonfinite_check", "lbm_first_nonfinite_step")
+           "lbm_set_nonfinite_check", "lbm_first_nonfinite_step", "lbm_query_step_plan")
 
 
 class LbmError(RuntimeError):
@@ -65,6 +65,11 @@ _dp = C.POINTER(C.c_double)
 
 class Objective(C.Structure):
     _fields_ = [("x_dev", C.c_int), ("w_tout", C.c_double), ("w_nu", C.c_double)]
+
+
+class StepPlan(C.Structure):
+    _fields_ = [("kernel", C.c_char_p), ("steps", C.c_int), ("threads", C.c_int),
+                ("tiles_x", C.c_int), ("tiles_y", C.c_int), ("segments", C.c_int)]
 
 
 class ParamsSI(C.Structure):
@@ -120,6 +125,7 @@ def lib():
         L.lbm_grad.argtypes = [vp, C.c_double, _dp, _dp]
         L.lbm_set_graph_steps.argtypes = [vp, C.c_int]
         L.lbm_set_step_fusion.argtypes = [vp, C.c_int]
+        L.lbm_query_step_plan.argtypes = [vp, C.POINTER(StepPlan)]
         for name in EXPORTS:
             if name not in ("lbm_destroy", "lbm_time", "lbm_last_error"):
                 getattr(L, name).restype = C.c_int
@@ -339,6 +345,14 @@ class Lattice:
         """Step kernel choice: 0 automatic, 1 single-step, 2 marching or two-step kernels, 3 (two-phase
         D2Q9) many steps per cooperative launch, grids of at most 16 tiles."""
         self._check(lib().lbm_set_step_fusion(self.ctx, int(mode)))
+
+    def step_plan(self):
+        """The launches that a long step() goes through now: dict of kernel (name), steps per
+        launch (0: all of a call), threads per workgroup, tiles_x, tiles_y and segments."""
+        p = StepPlan()
+        self._check(lib().lbm_query_step_plan(self.ctx, C.byref(p)))
+        return dict(kernel=p.kernel.decode(), steps=p.steps, threads=p.threads, tiles_x=p.tiles_x,
+                    tiles_y=p.tiles_y, segments=p.segments)
 
     @property
     def t(self):
