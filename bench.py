@@ -5,8 +5,8 @@ conservative Allen-Cahn populations, 256 x 256 periodic cell, liquid/gas
 density ratio ~43 300, viscosity ratio ~470, radii cycling over 20/30/40/50
 nodes with seeded centre jitter) run as a batch of independent replicas, FP32
 deviation storage.  One step = one stream-collide update of every node of
-every replica; by default the library's marching kernel performs three steps
-per launch (two in FP64; --fusion 1 times the single-step kernel instead).  Inputs are
+every replica; by default the library's marching kernel performs several steps
+per launch, as its plan says (--fusion 1 times the single-step kernel instead).  Inputs are
 synthetic and resident in HBM before timing starts.
 
 Prints ONE JSON line (see the keys below).  ``--gpus`` above 1 is refused:
@@ -43,18 +43,30 @@ KERNEL_SOURCES = ("paper_2302_04120_amd/csrc/lbm_kernels.hip", "paper_2302_04120
                   "paper_2302_04120_amd/csrc/lbm_phase_march.hip")
 
 
-def phase_steps_per_launch(prec, fusion):
-    """Steps per launch of the library's choice on grids that fill the GPU."""
-    return 1 if fusion == 1 else 3 if prec == "fp32" else 2
-
-
-def phase_march_name(prec, whole, aligned, spl):
-    """The instance at the benchmark's sizes (256 lanes; FP64 in x-tiles takes 128)."""
-    return "k_phase_march<%s, %s, %s, %s, %d, %d>" % ("double" if prec == "fp64" else "float",
-                                                      "float" if prec == "fp32" else "double",
-                                                      "true" if whole else "false",
-                                                      "true" if aligned else "false",
-                                                      256 if prec == "fp32" or whole else 128, spl)
+def launches(L, prec):
+    """(kernel instance, steps per launch) of a long step() call on L, from the library's
+    own plan; the template arguments as the kernel sources order them."""
+    p = L.step_plan()
+    k, spl = p["kernel"], p["steps"]
+    S = "double" if prec == "fp64" else "float"
+    args = [S]
+    yes = lambda v: "true" if v else "false"
+    if k.startswith("k_phase"):
+        args.append("float" if prec == "fp32" else "double")  # the type it computes in
+    if k == "k_phase":
+        args.append("false")
+    elif k == "k_phase_march":
+        whole = L.nx <= 256 and p["tiles_x"] == 1
+        lanes = next(n for n in (64, 128, 256) if n >= p["threads"])
+        args += [yes(whole), yes(L.nx % 64 == 0), lanes, spl]
+    elif k == "k_chan_march":
+        from paper_2302_04120_amd import lbm
+        ends = L.desc.bc[0] == lbm.BC_DIRICHLET or L.desc.bc[3] == lbm.BC_SYMMETRY
+        args += [yes(L.nx % 64 == 0), yes(ends), 9 if L.desc.flags & lbm.FLAG_THERMAL_D2Q9 else 5, spl]
+    elif k == "k_chan_step":
+        from paper_2302_04120_amd import lbm
+        args.append(9 if L.desc.flags & lbm.FLAG_THERMAL_D2Q9 else 5)
+    return "%s<%s>" % (k, ", ".join(map(str, args))), spl
 
 
 def kernel_source_hash():
@@ -136,6 +148,7 @@ def run_gpu(batch, steps, warmup, prec, n=256, fusion=0, windows=0):
     nodes = batch * n * n
     out = dict(wall=wall, ev_ms=ev_ms, nodes=nodes, kernel_ms=ev_ms / steps,
                bytes_gb=L.bytes / 1e9)
+    out["kernel"], out["steps_per_launch"] = launches(L, prec)
     if windows:
         out["sustained"] = sustained(L, nodes, ev_ms / steps, windows)
     red = L.reduce(("phase", "nonfinite"))
@@ -168,14 +181,14 @@ def run_wide(cells, steps, warmup, prec, fusion=0):
     ms, wall = timed(L, steps)
     if L.reduce(("nonfinite",))["nonfinite"].sum() != 0:
         raise RuntimeError("non-finite populations after the timed steps")
+    kernel, spl = launches(L, prec)
     L.close()
     nodes = n * n
-    spl = phase_steps_per_launch(prec, fusion)
     launch_ms = ms / -(-steps // spl)
     return dict(mlups=nodes * steps / (ms * 1e-3) / 1e6, grid="%dx%d" % (n, n),
                 ms_per_step=ms / steps, launch_ms=launch_ms,
                 hbm_frac=BYTES_PER_LU[prec] * nodes / (launch_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                kernel=phase_march_name(prec, False, n % 64 == 0, spl) if spl > 1 else "k_phase")
+                kernel=kernel)
 
 
 def run_channel(nx, ny, steps, warmup, prec, fusion=1):
@@ -207,16 +220,13 @@ def run_channel(nx, ny, steps, warmup, prec, fusion=1):
     nodes = nx * ny
     if L.reduce(("nonfinite",))["nonfinite"].sum() != 0:
         raise RuntimeError("non-finite populations after the timed steps")
+    kernel, spl = launches(L, prec)
     L.close()
-    S = "float" if prec == "fp32" else "double"
-    # steps per launch of the library's choice at this size
-    spl = 1 if fusion == 1 else (4 if prec == "fp32" else 3)
     per_step = CHAN_BYTES_PER_LU[prec] * nodes / spl  # bytes a step moves
     return dict(mlups=nodes * steps / wall / 1e6, kernel_ms=kernel_ms,
                 hbm_frac=per_step / (kernel_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                 grid="%dx%d" % (nx, ny), fusion=fusion,
-                kernel=("k_chan_march<%s, %s, false, 5, %d>" % (S, "true" if nx % 64 == 0 else "false", spl)
-                        if spl > 1 else "k_chan_step<%s, 5>" % S))
+                kernel=kernel)
 
 
 def run_d3(n, steps, warmup, prec, mrt=True):
@@ -244,12 +254,13 @@ def run_d3(n, steps, warmup, prec, mrt=True):
         raise RuntimeError("non-finite populations after the timed steps")
     kernel_ms = e0.elapsed_time(e1) / steps
     nodes = n ** 3
+    kernel, spl = launches(L, prec)
     L.close()
-    # two steps per launch: the state crosses HBM once per two steps
-    gbs = D3_BYTES_PER_LU[prec] / 2 * nodes / (kernel_ms * 1e-3) / 1e9
+    # the state crosses HBM once per launch
+    gbs = D3_BYTES_PER_LU[prec] / spl * nodes / (kernel_ms * 1e-3) / 1e9
     return dict(mlups=nodes * steps / wall / 1e6, kernel_ms=kernel_ms, hbm_GBps=gbs,
                 hbm_frac=gbs / HBM_PEAK_GBS, grid="%d^3" % n, collision="mrt" if mrt else "bgk",
-                kernel="k_d3_tb2<%s>" % ("float" if prec == "fp32" else "double"))
+                kernel=kernel)
 
 
 def run_p3(n, steps, warmup, prec, cell=64, R_nodes=16.0):
@@ -282,11 +293,12 @@ def run_p3(n, steps, warmup, prec, cell=64, R_nodes=16.0):
         raise RuntimeError("non-finite populations after the timed steps")
     step_ms = e0.elapsed_time(e1) / steps
     nodes = n ** 3
+    kernel, _ = launches(L, prec)
     L.close()
     gbs = P3_BYTES_PER_LU[prec] * nodes / (step_ms * 1e-3) / 1e9
     return dict(mlups=nodes * steps / wall / 1e6, step_ms=step_ms, state_GBps=gbs,
                 state_frac=gbs / HBM_PEAK_GBS, grid="%d^3" % n,
-                kernel="k_p3_march<%s>" % ("float" if prec == "fp32" else "double"))
+                kernel=kernel)
 
 
 def run_layered_batch(batch, steps, warmup, prec):
@@ -322,14 +334,15 @@ def run_layered_batch(batch, steps, warmup, prec):
 
 def run_c4_single(steps=20000, warmup=200, prec="fp32"):
     """One C4 replica (4 x 512 nodes, walls), launch-bound: microseconds per
-    step with graph replay of single-step launches and with the many-steps
-    kernel (step fusion mode 3), and whether the two end in the same state."""
+    step with graph replay of single-step launches, with the many-steps
+    kernel (step fusion mode 3) and in automatic mode, what a program gets that
+    sets neither, and whether they end in the same state."""
     import torch
     from paper_2302_04120_amd import lbm, workloads as WL
     prm, ini, _ = WL.layered(nx=4, ny=512, batch=1, seed=0)
     out = {}
     states = {}
-    for name, fusion, graph in (("graph_replay", 1, 64), ("many_steps", 3, 0)):
+    for name, fusion, graph in (("graph_replay", 1, 64), ("many_steps", 3, 0), ("automatic", 0, 64)):
         L = lbm.Lattice("phase", 4, 512, batch=1, prec=prec, bc=(0, 0, lbm.BC_WALL, lbm.BC_WALL))
         L.set_step_fusion(fusion)
         L.set_graph_steps(graph)
@@ -345,8 +358,10 @@ def run_c4_single(steps=20000, warmup=200, prec="fp32"):
         torch.cuda.synchronize()
         out[name + "_us_per_step"] = e0.elapsed_time(e1) / steps * 1e3
         states[name] = L.save_state()
+        if name == "automatic":
+            out["automatic_kernel"], out["automatic_steps_per_launch"] = launches(L, prec)
         L.close()
-    out["bit_identical"] = states["graph_replay"] == states["many_steps"]
+    out["bit_identical"] = len(set(states.values())) == 1
     out["steps"] = steps
     return out
 
@@ -354,7 +369,7 @@ def run_c4_single(steps=20000, warmup=200, prec="fp32"):
 def run_c4_steady(system="sat_water_25C", prec="fp32", decay_times=6.5, chunk=2_000_000):
     """C4's layered Poiseuille flow at the paper's finest grid (dx = 1.25 um,
     dt = 12.5 ns, W = 20 dx = 25 um, 512 nodes across: H = 0.64 mm) run from
-    rest to steady state with the many-steps kernel: decay_times times the
+    rest to steady state: decay_times times the
     liquid layer's slowest decay time 4 h^2 / (pi^2 nu_l).  Reports the E2 of
     the final profile against the steady momentum balance of Eq.
     NSE_for_layered_poiseuille integrated with the simulated phi (diffuse
@@ -370,7 +385,6 @@ def run_c4_steady(system="sat_water_25C", prec="fp32", decay_times=6.5, chunk=2_
     ny = 512
     prm, ini, offs = WL.layered(nx=4, ny=ny, seed=0, dx=1.25e-6, dt=1.25e-8, W_nodes=20.0, **props)
     L = lbm.Lattice("phase", 4, ny, prec=prec, bc=(0, 0, lbm.BC_WALL, lbm.BC_WALL))
-    L.set_step_fusion(3)
     L.set_params(prm)
     L.init(ini["p"], ini["ux"], ini["uy"], None, ini["phi"])
     H = ny * prm["dx"]
@@ -655,12 +669,7 @@ def main():
                 windows=0 if args.no_extras else 5)
     mlups = r["nodes"] * args.steps / r["wall"] / 1e6
     bpl = BYTES_PER_LU[args.prec]
-    # automatic mode marches too where the batch fills the GPU
-    march = args.fusion == 2 or (args.fusion == 0 and args.batch >= 32)
-    spl = phase_steps_per_launch(args.prec, args.fusion) if march else 1
-    kname = (phase_march_name(args.prec, True, True, spl) if spl > 1 else
-             "k_phase<%s>" % {"fp32": "float,float,false", "fp64": "double,double,false",
-                              "fp32_arith64": "float,double,false"}[args.prec])
+    kname, spl = r["kernel"], r["steps_per_launch"]
     lu_per_launch = r["nodes"] * args.steps / -(-args.steps // spl)  # the last launch may be shorter
     launch_ms = r["kernel_ms"] * lu_per_launch / r["nodes"]
     # Bytes one launch must move: the stored state (21 FP32 values per node: h,
@@ -687,7 +696,7 @@ def main():
         r64 = run_gpu(max(1, args.batch // 4), s64, 6, "fp64", fusion=args.fusion)
         extras["fp64_mlups"] = r64["nodes"] * s64 / r64["wall"] / 1e6
         # the state (20 FP64 values per node) once in and once out per launch of spl64 steps
-        spl64 = phase_steps_per_launch("fp64", args.fusion) if march else 1
+        spl64 = r64["steps_per_launch"]
         l64 = r64["kernel_ms"] * spl64 * 1e-3
         extras["fp64_hbm_frac"] = BYTES_PER_LU["fp64"] * r64["nodes"] / l64 / 1e9 / HBM_PEAK_GBS
         extras["fp64_step_equivalent_GBps"] = BYTES_PER_LU["fp64"] * r64["nodes"] * spl64 / l64 / 1e9
@@ -698,7 +707,7 @@ def main():
             hbm_GBps=BYTES_PER_LU["fp32"] * r1["nodes"] / (r1["kernel_ms"] * 1e-3) / 1e9,
             hbm_frac=BYTES_PER_LU["fp32"] * r1["nodes"] / (r1["kernel_ms"] * 1e-3) / 1e9
             / HBM_PEAK_GBS,
-            kernel="k_phase<float, float, false, 64, 4>")
+            kernel=r1["kernel"])
         log("bench: paper-sized leg (4 replicas)")
         # launch-bound: graph replay; 128 warm-up steps (twice the graph length)
         # capture the graph before the timed steps
@@ -708,7 +717,7 @@ def main():
         extras["wide_domain_fp32"] = run_wide(32, 100, 10, "fp32")
         log("bench: C4 layered batch leg (4096 x 4 x 512)")
         extras["layered_batch_fp32"] = run_layered_batch(4096, 200, 20, "fp32")
-        log("bench: C4 single replica, graph replay and many-steps kernel")
+        log("bench: C4 single replica, graph replay, many-steps kernel and automatic mode")
         extras["c4_single_replica"] = run_c4_single()
         log("bench: heated-channel leg (16384 x 2048)")
         extras["channel_fp32"] = run_channel(16384, 2048, 100, 10, "fp32", fusion=2)
