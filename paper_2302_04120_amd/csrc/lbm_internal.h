@@ -185,7 +185,7 @@ struct MarchPlan {
 
 // Tiles and steps per launch of the many-steps two-phase kernel
 // (lbm_phase_multi.hip); steps 0: not used.
-constexpr int kPhaseMultiMax = 8;
+constexpr int kPhaseMultiMax = 8;  // the plan search ends here; longer launches are not measured
 struct PhaseMultiPlan {
     int steps = 0, ntx = 0, nty = 0;
     double cost = 0.0;
@@ -208,7 +208,7 @@ struct D1K {
     int n, q;
     double w_tau;         // dt / tau
     double qdt;           // qdot * dt
-    double ufac;          // c u / c_s^2 (multiplies e_i in the equilibrium)
+    double ufac;          // always 0; its bytes belong to the parameter hash of saved states
     double T0, TL;
 };
 

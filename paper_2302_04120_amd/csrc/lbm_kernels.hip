@@ -537,11 +537,10 @@ __global__ void k_d1_init(D1K k, const double* __restrict__ T, double* __restric
     if (x >= k.n) return;
     if (k.q == 3) {
         const double w[3] = {4.0 / 6, 1.0 / 6, 1.0 / 6};
-        const int ex[3] = {0, 1, -1};
-        for (int i = 0; i < 3; ++i) g[i * k.n + x] = w[i] * T[x] * (1 + k.ufac * ex[i]);
+        for (int i = 0; i < 3; ++i) g[i * k.n + x] = w[i] * T[x];
     } else {
-        g[x] = 0.5 * T[x] * (1 + k.ufac);
-        g[k.n + x] = 0.5 * T[x] * (1 - k.ufac);
+        g[x] = 0.5 * T[x];
+        g[k.n + x] = 0.5 * T[x];
     }
 }
 
@@ -918,7 +917,7 @@ hipError_t launch_phase_step(const PhaseK& k, const S* a, S* b, bool arith64, hi
 
 // One wave of 1, 2 or 4 nodes a lane up to 256 nodes, then four waves.
 hipError_t launch_d1(const D1K& k, double* g, int nsteps, hipStream_t s) {
-    if (k.n < 3 || k.n > 1024 || k.ufac != 0.0) return hipErrorInvalidValue;
+    if (k.n < 3 || k.n > 1024) return hipErrorInvalidValue;
     auto go = [&](auto kern, int waves) {
         hipLaunchKernelGGL(kern, dim3(1), dim3(64 * waves), 0, s, k, g, nsteps);
         return hipGetLastError();

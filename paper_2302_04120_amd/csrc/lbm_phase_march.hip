@@ -26,7 +26,7 @@
 // after them would wait for the stores too.
 //
 // Bound: at K = 3 in FP32 the vector ALU (1180 instructions a row step, two waves
-// per SIMD at 215 to 220 registers, 85 % of its cycles issue); 2048 x 2048 moves the
+// per SIMD at 215 to 220 registers, 79 % of its cycles issue); 2048 x 2048 moves the
 // launch's bytes at 3.6 TB/s.  Four stages would need 91 KB of LDS a workgroup, one
 // per CU.  FP64 takes two steps: 310 registers, one wave per SIMD (held to 256
 // registers it spills and takes 1.9 times as long); FP64 arithmetic on an FP32 state,
@@ -358,7 +358,10 @@ int phase_march_threads(const PhaseK& k, int lanes) { return 64 * phase_march_wa
 // 6 90 -> 49, 1003 x 701 36.7 -> 31.5; FP64 arithmetic on an FP32 state (single steps
 // before) 128 x 256^2 303 -> 177, 2048 x 2048 151 -> 94, 4 x 600 x 500 44 -> 35.  128
 // lanes instead of 256 waste less of ragged rows, and in FP64, where a SIMD holds one wave, two workgroups fill each other's
-// barriers: 2048 x 2048 168 -> 143, 4 x 600 x 500 63 -> 45.  Rows far narrower than a
+// barriers: 2048 x 2048 168 -> 143, 4 x 600 x 500 63 -> 45.  Calls of exactly two or four
+// FP32 steps, and captured pairs, go at K = 2 on the segments of K = 3 (others are no
+// faster); against the two-step scheme: 2048 x 2048 118 -> 93, 64 x 256^2 87 -> 78, but
+// 128 x 256^2 144 -> 150 and 1024 x 256^2 1120 -> 1150.  Rows far narrower than a
 // wave (1024 x 4 x 512: single step 72, here 313) stay with the other kernels.
 template <typename S, typename C>
 MarchPlan march_plan(const PhaseK& k) {
