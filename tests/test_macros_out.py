@@ -78,3 +78,34 @@ def test_fields_are_the_same_in_every_memory(lattice):
         assert np.array_equal(dev.cpu().numpy(), ref)
         assert np.array_equal(pinned.numpy(), ref)
     L.close()
+
+
+@pytest.mark.gpu
+def test_captured_fields_replay():
+    """Steps and fields captured by the caller: every replay writes the fields of its own
+    state, into the tensor of the capture."""
+    import torch
+    from paper_2302_04120_amd import lbm
+    print_case(test="macros-capture")
+    prm, ini, _ = WL.bubble(n=40, ny=36, radii=(9.0,), batch=2, seed=1)
+    s = torch.cuda.Stream()
+    L, ref = lbm.Lattice("phase", 40, 36, batch=2, stream=s), lbm.Lattice("phase", 40, 36, batch=2)
+    for q in (L, ref):
+        q.set_params(prm)
+        q.init(ini["p"], ini["ux"], ini["uy"], None, ini["phi"])
+    names = [f for f in lbm.MACRO_BITS if f in ref.macros()]
+    mask = sum(lbm.MACRO_BITS[f] for f in names)
+    out = torch.zeros((len(names), 2, 36, 40), dtype=torch.float64, device="cuda:0")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        L.step(2)
+        assert lbm.lib().lbm_macros(L.ctx, mask, C.cast(out.data_ptr(), C.POINTER(C.c_double)), 1) == 0
+    for rep in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        ref.step(2)
+        want = ref.macros()
+        assert np.array_equal(out.cpu().numpy(), np.stack([want[f] for f in names])), rep
+    L.close()
+    ref.close()
